@@ -303,6 +303,7 @@ static int geom_create(int nbodies, const int32_t *nodes_per_body, const double 
   // the caller's samples (device memory) are checked on the host before anything is built
   int warn = BIE_OK;
   std::string warn_msg;
+  double pair_scale = 1.0;
   {
     hipStream_t s0 = as_stream(stream);
     std::vector<double> hc(6 * (size_t)M), hi(interior ? 2 * (size_t)nbodies : 0);
@@ -319,6 +320,10 @@ static int geom_create(int nbodies, const int32_t *nodes_per_body, const double 
       set_error("bie_geom_create: " + warn_msg);
       return BIE_EINVAL;
     }
+    const auto x = std::minmax_element(hc.begin(), hc.begin() + M);
+    const auto y = std::minmax_element(hc.begin() + M, hc.begin() + 2 * M);
+    const double diag = std::hypot(*x.second - *x.first, *y.second - *y.first);
+    pair_scale = std::ldexp(1.0, -std::max(-1000, std::min(1000, std::ilogb(diag))));
   }
   bie_geom *g = new (std::nothrow) bie_geom();
   if (!g) {
@@ -330,6 +335,7 @@ static int geom_create(int nbodies, const int32_t *nodes_per_body, const double 
   g->N = nbodies;
   g->M = (int)M;
   g->max_nodes = maxn;
+  g->pair_scale = pair_scale;
   hipGetDevice(&g->device);
   g->h_body_ptr.resize(nbodies + 1);
   g->h_body_ptr[0] = 0;
@@ -338,13 +344,20 @@ static int geom_create(int nbodies, const int32_t *nodes_per_body, const double 
     g->max_nb = std::max(g->max_nb, nodes_per_body[b]);
   }
   plan_splits(g);
+  std::vector<int2> small;  // body-aligned target tiles of the one-launch direct apply
+  if (M <= kSmallTiles * kSmallTile)
+    for (int b = 0; b < nbodies; ++b)
+      for (int i = g->h_body_ptr[b]; i < g->h_body_ptr[b + 1]; i += kSmallTile)
+        small.push_back(make_int2(b, i));
+  if ((int)small.size() > kSmallTiles) small.clear();
+  g->nsmall = (int)small.size();
   g->far_pairs = (long long)M * M;
   for (int b = 0; b < nbodies; ++b) g->far_pairs -= (long long)nodes_per_body[b] * nodes_per_body[b];
   const size_t Md = (size_t)M, Nd = (size_t)nbodies;
   // arena: doubles first (8 node arrays, xy (2M), 4 body arrays, pint (2N), area, the
-  // double-layer length scale), then floats, ints
+  // double-layer length scale), then floats, the small tiles, ints
   const size_t nd = 8 * Md + 2 * Md + 4 * Nd + 2 * Nd + Nd + 1;
-  const size_t bytes = nd * 8 + Md * 8 /*xr*/ + (Nd + 1 + Md + g->h_split_body.size()) * 4 + 256;
+  const size_t bytes = nd * 8 + Md * 8 /*xr*/ + small.size() * 8 + (Nd + 1 + Md + g->h_split_body.size()) * 4 + 256;
   int rc = g->arena.reserve(bytes);
   if (rc != BIE_OK) {
     delete g;
@@ -373,7 +386,8 @@ static int geom_create(int nbodies, const int32_t *nodes_per_body, const double 
   g->area = take(Nd);
   g->dl_scale = take(1);
   g->xr = reinterpret_cast<float2 *>(p);
-  int *ip = reinterpret_cast<int *>(g->xr + Md);
+  g->small_tile = reinterpret_cast<int2 *>(g->xr + Md);
+  int *ip = reinterpret_cast<int *>(g->small_tile + small.size());
   g->body_ptr = ip;
   ip += Nd + 1;
   g->body_of = ip;
@@ -387,7 +401,9 @@ static int geom_create(int nbodies, const int32_t *nodes_per_body, const double 
   if (hipMemcpyAsync(g->body_ptr, g->h_body_ptr.data(), (Nd + 1) * 4, hipMemcpyHostToDevice, s) !=
           hipSuccess ||
       hipMemcpyAsync(g->split_body, g->h_split_body.data(), g->h_split_body.size() * 4,
-                     hipMemcpyHostToDevice, s) != hipSuccess) {
+                     hipMemcpyHostToDevice, s) != hipSuccess ||
+      (!small.empty() && hipMemcpyAsync(g->small_tile, small.data(), small.size() * 8,
+                                        hipMemcpyHostToDevice, s) != hipSuccess)) {
     set_error("bie_geom_create: host to device copy failed");
     return fail(BIE_EDEVICE);
   }

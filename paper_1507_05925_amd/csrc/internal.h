@@ -180,6 +180,13 @@ struct bie_geom {
   double *dl_scale = nullptr;  // [1] length scale R of the completed double layers
   double2 *xy = nullptr;    // [M] float64 source coordinates
   float2 *xr = nullptr;     // [M] float32 coordinates relative to the body centroid
+  // power of two that brings the nodes' bounding-box diagonal into [1, 2): the pair sums work in
+  // scaled lengths, so that products of several squared distances stay in range
+  double pair_scale = 1.0;
+  // targets of the one-launch direct apply (direct.hip): (body, first node) per tile; none for
+  // geometries that take the split sweep
+  int nsmall = 0;
+  int2 *small_tile = nullptr;
   // source-body splits of the far-field sweep
   int nsplit = 1;
   int *split_body = nullptr;  // [nsplit+1] device
@@ -236,6 +243,26 @@ int read_off(bie_geom *g, int kind, int nrhs, const double *dens, double *res, h
 int eval_points(bie_geom *g, int kind, int nrhs, const double *dens, int npts, const double *pts,
                 bool rigid, double *res, hipStream_t st, int method = BIE_DIRECT);
 int geometry_build(bie_geom *g, const double *curve, const double *interior, hipStream_t s);
+
+// ---- direct.hip: the float64 direct apply ---------------------------------------------------
+// Geometries whose bodies make at most kSmallTiles tiles of kSmallTile targets (one workgroup per
+// compute unit; about 4,000 nodes) take their direct applies, in either precision, in one float64
+// launch; larger ones a sweep over source splits and a finishing launch. 3,000 nodes (210 tiles)
+// take 10.9 us in one launch; 4,000 (280 tiles, some compute units with two) 19.6 us, the split
+// sweep 18.4 us at 4,264.
+constexpr int kSmallTile = 16;
+constexpr int kSmallTiles = 256;
+// Sums per target of the sweep of kind (PairKind) for R right-hand sides, and its source splits on
+// a geometry of M nodes.
+inline int pair_values(int kind, int R) { return (kind & 1) ? 2 * R : kind == 0 && R == 1 ? 2 : R; }
+int pair_splits(int M, int V);
+// Raw pair sums of kind (0 Laplace, 1 Stokes) for R right-hand sides (1..4, Laplace also 8) into
+// partial [pair_splits][R][len].
+int pair_sweep(bie_geom *g, int kind, int R, const double *mu, double *partial, hipStream_t s);
+// out = alpha (1/2 I + K [+ L]) mu for R right-hand sides (as above); partial holds
+// pair_splits R len doubles (unused for small geometries).
+int direct_apply(bie_geom *g, int kind, int with_L, double alpha, int R, const double *mu,
+                 double *out, double *partial, hipStream_t s);
 
 // ---- dirichlet.hip: capacitance and resistance problems (completed double layers) --------
 // kind 2 (Laplace) and 3 (Stokes) of apply_operator / solve_system

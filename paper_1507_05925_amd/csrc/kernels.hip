@@ -1,8 +1,9 @@
 // Operator kernels of the bie2d library for gfx950.
 //
-// The apply of (1/2 I + K + L) (elastance, eq. ModRep2) and (1/2 I + Kcal + L) (mobility,
-// eq. ModRep2Stokes) is split into
-//   (1) a far-field sweep over all (target, source) pairs whose bodies differ, and
+// The direct apply of (1/2 I + K + L) (elastance, eq. ModRep2) and (1/2 I + Kcal + L) (mobility,
+// eq. ModRep2Stokes) is in direct.hip for float64 and for small geometries. In mixed precision it is
+// split here into
+//   (1) a float32 far-field sweep over all (target, source) pairs whose bodies differ, and
 //   (2) a per-body epilogue: the self-body block in float64 with the smooth diagonal limit, the
 //       identity, the completion L (per-body charge / force and torque reductions), and the sum
 //       of the far-field partials in a fixed order.
@@ -156,8 +157,8 @@ __global__ void k_pack(long long total, int M, int comps, const double *__restri
 // ------------------------------------------------------------------------------------------
 // a3: far-field sweeps. Lane = target i; loop over source bodies c of this split, c != body(i).
 // ------------------------------------------------------------------------------------------
-constexpr float kFar32 = 1.0e18f;   // parking coordinate for lanes whose own body is swept
-constexpr double kFar64 = 1.0e100;  // (their sum is discarded; it only has to stay finite)
+constexpr float kFar32 = 1.0e18f;  // parking coordinate for lanes whose own body is swept (their
+                                   // sum is discarded; it only has to stay finite)
 
 template <int R>
 __global__ __launch_bounds__(kBlock) void k_lap_far_f32(
@@ -205,58 +206,6 @@ __global__ __launch_bounds__(kBlock) void k_lap_far_f32(
       for (int r = 0; r < R; ++r) {
         Gx[r] += (double)gx[r];
         Gy[r] += (double)gy[r];
-      }
-    }
-  }
-  if (valid) {
-    const double a = nx[i], b = ny[i];
-#pragma unroll
-    for (int r = 0; r < R; ++r)
-      partial[((size_t)split * R + r) * M + i] = -(a * Gx[r] + b * Gy[r]) / (2.0 * kPi);
-  }
-}
-
-template <int R>
-__global__ __launch_bounds__(kBlock) void k_lap_far_f64(
-    int M, const int *__restrict__ body_ptr, const int *__restrict__ body_of,
-    const double2 *__restrict__ xy, const double *__restrict__ s64, const double *__restrict__ nx,
-    const double *__restrict__ ny, const int *__restrict__ split_body, double *__restrict__ partial) {
-  const int split = blockIdx.y;
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  const bool valid = i < M;
-  const int ii = valid ? i : M - 1;
-  const int bi = body_of[ii];
-  const double2 p = xy[ii];
-  double Gx[R], Gy[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) Gx[r] = Gy[r] = 0.0;
-  const int c0 = split_body[split], c1 = split_body[split + 1];
-  for (int c = c0; c < c1; ++c) {
-    const bool self = (c == bi);
-    if (__all(self)) continue;
-    const double tx = self ? kFar64 : p.x;
-    const double ty = self ? kFar64 : p.y;
-    double gx[R], gy[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) gx[r] = gy[r] = 0.0;
-    const int k0 = body_ptr[c], k1 = body_ptr[c + 1];
-#pragma unroll 2
-    for (int k = k0; k < k1; ++k) {
-      const double2 q = xy[k];
-      const double dx = tx - q.x, dy = ty - q.y;
-      const double inv = rcp64(fma(dx, dx, dy * dy));
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const double t = s64[(size_t)r * M + k] * inv;
-        gx[r] = fma(dx, t, gx[r]);
-        gy[r] = fma(dy, t, gy[r]);
-      }
-    }
-    if (!self) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        Gx[r] += gx[r];
-        Gy[r] += gy[r];
       }
     }
   }
@@ -317,63 +266,6 @@ __global__ __launch_bounds__(kBlock) void k_stk_far_f32(
       for (int r = 0; r < R; ++r) {
         Gx[r] += (double)gx[r];
         Gy[r] += (double)gy[r];
-      }
-    }
-  }
-  if (valid) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      double *o = partial + ((size_t)split * R + r) * 2 * M;
-      o[2 * i] = -Gx[r] / kPi;
-      o[2 * i + 1] = -Gy[r] / kPi;
-    }
-  }
-}
-
-template <int R>
-__global__ __launch_bounds__(kBlock) void k_stk_far_f64(
-    int M, const int *__restrict__ body_ptr, const int *__restrict__ body_of,
-    const double2 *__restrict__ xy, const double2 *__restrict__ s64, const double *__restrict__ nx,
-    const double *__restrict__ ny, const int *__restrict__ split_body, double *__restrict__ partial) {
-  const int split = blockIdx.y;
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  const bool valid = i < M;
-  const int ii = valid ? i : M - 1;
-  const int bi = body_of[ii];
-  const double2 p = xy[ii];
-  const double nxi = nx[ii], nyi = ny[ii];
-  double Gx[R], Gy[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) Gx[r] = Gy[r] = 0.0;
-  const int c0 = split_body[split], c1 = split_body[split + 1];
-  for (int c = c0; c < c1; ++c) {
-    const bool self = (c == bi);
-    if (__all(self)) continue;
-    const double tx = self ? kFar64 : p.x;
-    const double ty = self ? kFar64 : p.y;
-    double gx[R], gy[R];
-#pragma unroll
-    for (int r = 0; r < R; ++r) gx[r] = gy[r] = 0.0;
-    const int k0 = body_ptr[c], k1 = body_ptr[c + 1];
-#pragma unroll 2
-    for (int k = k0; k < k1; ++k) {
-      const double2 q = xy[k];
-      const double dx = tx - q.x, dy = ty - q.y;
-      const double inv = rcp64(fma(dx, dx, dy * dy));
-      const double a = fma(dx, nxi, dy * nyi) * (inv * inv);
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const double2 sv = s64[(size_t)r * M + k];
-        const double cc = fma(dx, sv.x, dy * sv.y) * a;
-        gx[r] = fma(cc, dx, gx[r]);
-        gy[r] = fma(cc, dy, gy[r]);
-      }
-    }
-    if (!self) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        Gx[r] += gx[r];
-        Gy[r] += gy[r];
       }
     }
   }
@@ -704,29 +596,17 @@ __global__ void k_rigid_fin(int N, int nrhs, int S, const double *__restrict__ p
 inline unsigned nblocks(long long n, int bs = kBlock) { return (unsigned)((n + bs - 1) / bs); }
 
 template <int R>
-void launch_far(bie_geom *g, int kind, int precision, const double *s64, const float *s32,
-                double *partial, hipStream_t st, size_t off) {
+void launch_far(bie_geom *g, int kind, const float *s32, double *partial, hipStream_t st,
+                size_t off) {
   dim3 grid(nblocks(g->M), g->nsplit), block(kBlock);
-  const int kc = kind == 0 ? (precision == BIE_MIXED ? BIE_K_FAR_LAPLACE_F32 : BIE_K_FAR_LAPLACE_F64)
-                           : (precision == BIE_MIXED ? BIE_K_FAR_STOKES_F32 : BIE_K_FAR_STOKES_F64);
-  ProfScope prof(kc, st, g->far_pairs * R);
-  if (kind == 0) {
-    if (precision == BIE_MIXED)
-      hipLaunchKernelGGL(k_lap_far_f32<R>, grid, block, 0, st, g->M, g->body_ptr, g->body_of, g->xc,
-                         g->yc, g->xr, s32 + off, g->nx, g->ny, g->split_body, partial);
-    else
-      hipLaunchKernelGGL(k_lap_far_f64<R>, grid, block, 0, st, g->M, g->body_ptr, g->body_of, g->xy,
-                         s64 + off, g->nx, g->ny, g->split_body, partial);
-  } else {
-    if (precision == BIE_MIXED)
-      hipLaunchKernelGGL(k_stk_far_f32<R>, grid, block, 0, st, g->M, g->body_ptr, g->body_of, g->xc,
-                         g->yc, g->xr, reinterpret_cast<const float2 *>(s32 + off), g->nx, g->ny,
-                         g->split_body, partial);
-    else
-      hipLaunchKernelGGL(k_stk_far_f64<R>, grid, block, 0, st, g->M, g->body_ptr, g->body_of, g->xy,
-                         reinterpret_cast<const double2 *>(s64 + off), g->nx, g->ny,
-                         g->split_body, partial);
-  }
+  ProfScope prof(kind == 0 ? BIE_K_FAR_LAPLACE_F32 : BIE_K_FAR_STOKES_F32, st, g->far_pairs * R);
+  if (kind == 0)
+    hipLaunchKernelGGL(k_lap_far_f32<R>, grid, block, 0, st, g->M, g->body_ptr, g->body_of, g->xc,
+                       g->yc, g->xr, s32 + off, g->nx, g->ny, g->split_body, partial);
+  else
+    hipLaunchKernelGGL(k_stk_far_f32<R>, grid, block, 0, st, g->M, g->body_ptr, g->body_of, g->xc,
+                       g->yc, g->xr, reinterpret_cast<const float2 *>(s32 + off), g->nx, g->ny,
+                       g->split_body, partial);
 }
 
 }  // namespace
@@ -750,6 +630,19 @@ size_t apply_workspace_bytes(const bie_geom *g, int kind, int method, int nrhs) 
          (size_t)nsplit * maxR * len * sizeof(double);
 }
 
+// Bytes of the float64 direct sweep's partial sums, over the right-hand side counts a call may
+// use. Where the sources are split, splits x target tiles stay within four rounds of resident
+// workgroups (a few tens of MiB at most); else one partial per target.
+static size_t direct_workspace_bytes(const bie_geom *g, int kind) {
+  if (g->nsmall > 0) return 0;
+  const size_t len = (size_t)g->M * (kind == 0 ? 1 : 2);
+  size_t most = 0;
+  for (int R : {1, 2, 3, 4, 8})
+    if (kind == 0 || R <= 4)
+      most = std::max(most, (size_t)pair_splits(g->M, pair_values(kind, R)) * R * len * sizeof(double));
+  return most;
+}
+
 // Far-field partials per rhs chunk and the epilogue. Chunks of <= 8 (Laplace) / 4 (Stokes) rhs
 // share each pair's geometry work.
 int apply_operator(bie_geom *g, int kind, int precision, int method, int with_L, double alpha,
@@ -760,7 +653,8 @@ int apply_operator(bie_geom *g, int kind, int precision, int method, int with_L,
     set_error("apply: nrhs >= 1 required");
     return BIE_EINVAL;
   }
-  BIE_TRY(g->ws_apply.reserve(apply_workspace_bytes(g, kind, method, nrhs)));
+  BIE_TRY(g->ws_apply.reserve(std::max(apply_workspace_bytes(g, kind, method, nrhs),
+                                       direct_workspace_bytes(g, kind))));
   return apply_operator_ws(g, kind, precision, method, with_L, alpha, nrhs, mu, out,
                            g->ws_apply.ptr, g->ws_apply.bytes, st);
 }
@@ -789,6 +683,22 @@ int apply_operator_ws(bie_geom *g, int kind, int precision, int method, int with
     set_error("apply: workspace too small");
     return BIE_EINVAL;
   }
+  // the direct apply in float64, and in either precision on small geometries, where the float32
+  // sweep (with its float64 self blocks) takes more launches and no less time per pair
+  if (method == BIE_DIRECT && (precision == BIE_FP64 || g->nsmall > 0)) {
+    if (ws_bytes < direct_workspace_bytes(g, kind)) {
+      set_error("apply: workspace too small");
+      return BIE_EINVAL;
+    }
+    for (int r0 = 0; r0 < nrhs;) {
+      const int left = nrhs - r0, R = left >= maxR ? maxR : std::min(left, 4);
+      const size_t off = (size_t)r0 * len;
+      BIE_TRY(direct_apply(g, kind, with_L, alpha, R, mu + off, out + off,
+                           static_cast<double *>(ws), st));
+      r0 += R;
+    }
+    return BIE_OK;
+  }
   double *s64 = static_cast<double *>(ws);
   float *s32 = reinterpret_cast<float *>(s64 + (size_t)nrhs * len);
   double *partial = reinterpret_cast<double *>(
@@ -796,7 +706,7 @@ int apply_operator_ws(bie_geom *g, int kind, int precision, int method, int with
   const long long tot = (long long)nrhs * len;
   if (method != BIE_FMM) {  // the FMM gather forms the strengths itself
     hipLaunchKernelGGL(k_pack, dim3(nblocks(tot)), dim3(kBlock), 0, st, tot, g->M, comps, g->w, mu,
-                       s64, precision == BIE_MIXED ? s32 : nullptr);
+                       s64, s32);
     BIE_HIP_CHECK(hipGetLastError());
   }
   for (int r0 = 0; r0 < nrhs;) {
@@ -821,10 +731,10 @@ int apply_operator_ws(bie_geom *g, int kind, int precision, int method, int with
                             leaf));
     } else {
       switch (R) {
-        case 8: launch_far<8>(g, kind, precision, s64, s32, partial, st, off); break;
-        case 4: launch_far<4>(g, kind, precision, s64, s32, partial, st, off); break;
-        case 2: launch_far<2>(g, kind, precision, s64, s32, partial, st, off); break;
-        default: launch_far<1>(g, kind, precision, s64, s32, partial, st, off); break;
+        case 8: launch_far<8>(g, kind, s32, partial, st, off); break;
+        case 4: launch_far<4>(g, kind, s32, partial, st, off); break;
+        case 2: launch_far<2>(g, kind, s32, partial, st, off); break;
+        default: launch_far<1>(g, kind, s32, partial, st, off); break;
       }
       BIE_HIP_CHECK(hipGetLastError());
     }

@@ -1,0 +1,133 @@
+// Device pieces of the direct pair sums in float64, shared by the operator's direct apply
+// (direct.hip) and the double layers of the capacitance and resistance problems (dirichlet.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+namespace bie {
+
+// The pair kernels, r = target - source, s the source's strength (w times the density):
+//   kPairLap    (r . n_target) s / |r|^2                      kPairLapDl  (r . n_source) s / |r|^2
+//   kPairStk    (r . n_target)(r . s) r / |r|^4               kPairStkDl  (r . n_source)(r . s) r / |r|^4
+// kPairLap with one right-hand side accumulates s r / |r|^2 (two values) and takes the normal
+// component at the end, one multiply-add less per pair.
+enum PairKind { kPairLap = 0, kPairStk = 1, kPairLapDl = 2, kPairStkDl = 3 };
+
+template <int KIND, int R>
+struct PairShape {
+  static constexpr bool STK = KIND == kPairStk || KIND == kPairStkDl;
+  static constexpr bool DL = KIND == kPairLapDl || KIND == kPairStkDl;
+  static constexpr int COMPS = STK ? 2 : 1;                      // components of a density
+  static constexpr int V = STK ? 2 * R : (KIND == kPairLap && R == 1 ? 2 : R);  // sums per target
+  static constexpr int ARR = 2 + (DL ? 2 : 0) + COMPS * R;       // staged values per source
+};
+
+// The reciprocals of four positive numbers from one reciprocal of their product: v_rcp_f64 issues
+// at a quarter of the rate of a multiply-add (17.6 against 5.2 cycles per wave), so four of them
+// and their refinements cost more than the nine multiplies that share one. The hardware
+// estimate (relative error below 5e-8) takes one third-order step, which leaves rounding errors
+// only. The callers scale lengths by the geometry's diameter (bie_geom::pair_scale), so that the
+// product stays far inside the range of a float64.
+__device__ __forceinline__ void rcp4(const double (&a)[4], double (&o)[4]) {
+  const double p = a[0] * a[1], q = a[2] * a[3], d = p * q;
+  double y = __builtin_amdgcn_rcp(d);
+  const double e = fma(-d, y, 1.0);
+  y = fma(y, fma(e, e, e), y);
+  const double yp = y * q, yq = y * p;
+  o[0] = yp * a[1];
+  o[1] = yp * a[0];
+  o[2] = yq * a[3];
+  o[3] = yq * a[2];
+}
+
+// Adds the four staged sources at position k of `buf` (arrays of `stride` doubles: x, y, [n_x w,
+// n_y w,] then the strengths) to one target's sums. With MASK, source `self` (its index relative
+// to the staged block) is the target itself and adds nothing: |r|^2 = 0 is replaced by 1, and
+// r = 0 makes every term zero.
+template <int KIND, int R, bool MASK>
+__device__ __forceinline__ void pair_quad(const double *buf, int stride, int k, int self, double tx,
+                                          double ty, double tnx, double tny,
+                                          double (&acc)[PairShape<KIND, R>::V]) {
+  using S = PairShape<KIND, R>;
+  double dx[4], dy[4], rr[4], inv[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    dx[u] = tx - buf[k + u];
+    dy[u] = ty - buf[stride + k + u];
+    rr[u] = fma(dx[u], dx[u], dy[u] * dy[u]);
+    if (MASK) rr[u] = k + u == self ? 1.0 : rr[u];
+  }
+  rcp4(rr, inv);
+  const double *st = buf + (S::DL ? 4 : 2) * stride + k;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if constexpr (KIND == kPairLap && R == 1) {
+      const double t = st[u] * inv[u];
+      acc[0] = fma(dx[u], t, acc[0]);
+      acc[1] = fma(dy[u], t, acc[1]);
+    } else {
+      const double nx = S::DL ? buf[2 * stride + k + u] : tnx;
+      const double ny = S::DL ? buf[3 * stride + k + u] : tny;
+      const double a = fma(dx[u], nx, dy[u] * ny) * inv[u];
+      if constexpr (S::STK) {
+        const double b = a * inv[u];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const double c = fma(dx[u], st[2 * r * stride + u], dy[u] * st[(2 * r + 1) * stride + u]) * b;
+          acc[2 * r] = fma(c, dx[u], acc[2 * r]);
+          acc[2 * r + 1] = fma(c, dy[u], acc[2 * r + 1]);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] = fma(a, st[r * stride + u], acc[r]);
+      }
+    }
+  }
+}
+
+// The sources a pair sweep stages: coordinates and strengths are scaled as they are read.
+struct PairSources {
+  const double2 *xy;
+  const double *nx, *ny, *w;
+  const double *mu;  // [R][len], node-major
+  long long len;
+  double scale;
+};
+
+// Source k as it lies in memory (kk: any source of the geometry where k is past the end), and its
+// staged values at position t of the block: a source past the end (valid false) gets no strength
+// and a place away from source kk. The loads are issued a block ahead and used only here, so that
+// a block's loads overlap the previous block's pairs.
+template <int KIND, int R>
+struct PairRaw {
+  using S = PairShape<KIND, R>;
+  double2 z;
+  double w, nx, ny, mu[S::COMPS * R];
+  __device__ __forceinline__ void load(const PairSources &a, int kk) {
+    z = a.xy[kk];
+    w = a.w[kk];
+    if (S::DL) {
+      nx = a.nx[kk];
+      ny = a.ny[kk];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int c = 0; c < S::COMPS; ++c)
+        mu[r * S::COMPS + c] = a.mu[(size_t)r * a.len + (size_t)S::COMPS * kk + c];
+  }
+  __device__ __forceinline__ void store(double scale, bool valid, double *buf, int stride, int t) const {
+    const double away = valid ? 0.0 : 16.0;  // the geometry's scaled diameter lies in [1, 2)
+    buf[t] = fma(z.x, scale, away);
+    buf[stride + t] = fma(z.y, scale, away);
+    if (S::DL) {
+      buf[2 * stride + t] = nx;
+      buf[3 * stride + t] = ny;
+    }
+    constexpr int st = S::DL ? 4 : 2;
+#pragma unroll
+    for (int v = 0; v < S::COMPS * R; ++v) buf[(st + v) * stride + t] = valid ? w * mu[v] : 0.0;
+  }
+};
+
+}  // namespace bie
