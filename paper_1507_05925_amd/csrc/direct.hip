@@ -21,85 +21,13 @@
 namespace bie {
 namespace {
 
-constexpr int kSweepT = 2;                 // targets per lane of the split sweep
-constexpr int kSweepTile = 64 * kSweepT;   // targets per workgroup
-constexpr int kStage = kBlock;             // sources staged at a time: one per thread
-
-// Split sweep: grid (target tiles, source splits), raw sums of split sp to
-// partial[sp][r][target comp]. Wave w takes the quads w, w + 4, ... of each staged block; the four
-// waves' sums are added in wave order through LDS. Blocks that hold one of the tile's own nodes
-// (a uniform test) mask the pair of a node with itself.
-// Waves per SIMD that the sweep's registers leave room for (its launch bound).
-constexpr int sweep_occupancy(int V) { return V <= 2 ? 4 : V <= 4 ? 3 : 2; }
-
+// Split sweep: grid (target tiles, source splits of `per` sources), raw sums of split sp to
+// partial[sp][r][target comp].
 template <int KIND, int R>
-__global__ __launch_bounds__(kBlock, sweep_occupancy(PairShape<KIND, R>::V)) void k_pair_sweep(int M, int per, PairSources src,
-                                                       double factor,
-                                                       double *__restrict__ partial) {
-  using P = PairShape<KIND, R>;
-  constexpr int kRed = 4 * kSweepTile * P::V;
-  __shared__ double buf[P::ARR * kStage > kRed ? P::ARR * kStage : kRed];
-  const int i0 = blockIdx.x * kSweepTile, sp = blockIdx.y;
-  const int lane = threadIdx.x & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int k0 = sp * per, k1 = min(k0 + per, M);
-  double tx[kSweepT], ty[kSweepT], nx[kSweepT], ny[kSweepT], acc[kSweepT][P::V];
-#pragma unroll
-  for (int u = 0; u < kSweepT; ++u) {
-    const int i = min(i0 + lane + 64 * u, M - 1);
-    const double2 z = src.xy[i];
-    tx[u] = z.x * src.scale;
-    ty[u] = z.y * src.scale;
-    nx[u] = P::DL ? 0.0 : src.nx[i];
-    ny[u] = P::DL ? 0.0 : src.ny[i];
-#pragma unroll
-    for (int v = 0; v < P::V; ++v) acc[u][v] = 0.0;
-  }
-  PairRaw<KIND, R> rec;
-  const int t = threadIdx.x;
-  rec.load(src, min(k0 + t, k1 - 1));
-  for (int base = k0; base < k1; base += kStage) {
-    rec.store(src.scale, base + t < k1, buf, kStage, t);
-    __syncthreads();
-    rec.load(src, min(base + kStage + t, k1 - 1));  // the next block, during this block's pairs
-    const int nq = (min(k1 - base, kStage) + 3) >> 2;  // quads (the last one padded)
-    if (base < i0 + kSweepTile && base + kStage > i0) {
-      for (int q = wv; q < nq; q += 4)
-#pragma unroll
-        for (int u = 0; u < kSweepT; ++u)
-          pair_quad<KIND, R, true>(buf, kStage, 4 * q, i0 + lane + 64 * u - base, tx[u], ty[u],
-                                   nx[u], ny[u], acc[u]);
-    } else {
-      for (int q = wv; q < nq; q += 4)
-#pragma unroll
-        for (int u = 0; u < kSweepT; ++u)
-          pair_quad<KIND, R, false>(buf, kStage, 4 * q, -1, tx[u], ty[u], nx[u], ny[u], acc[u]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int u = 0; u < kSweepT; ++u)
-#pragma unroll
-    for (int v = 0; v < P::V; ++v) buf[(wv * P::V + v) * kSweepTile + lane + 64 * u] = acc[u][v];
-  __syncthreads();
-  const double f = factor * src.scale;
-  constexpr int kOut = KIND == kPairLap ? R : P::V;  // values per target after the normal component
-  for (int e = t; e < kSweepTile * kOut; e += kBlock) {
-    const int j = e % kSweepTile, v = e / kSweepTile, i = i0 + j;
-    if (i >= M) continue;
-    auto sum = [&](int c) {
-      const double *b = buf + c * kSweepTile + j;
-      constexpr int w = P::V * kSweepTile;
-      return (b[0] + b[w]) + (b[2 * w] + b[3 * w]);
-    };
-    if constexpr (KIND == kPairLap && R == 1) {
-      partial[(size_t)sp * M + i] = f * (src.nx[i] * sum(0) + src.ny[i] * sum(1));
-    } else if constexpr (P::STK) {
-      partial[((size_t)sp * R + v / 2) * 2 * M + 2 * i + (v & 1)] = f * sum(v);
-    } else {
-      partial[((size_t)sp * R + v) * M + i] = f * sum(v);
-    }
-  }
+__global__ __launch_bounds__(kBlock, sweep_occupancy(PairShape<KIND, R>::V)) void k_pair_sweep(
+    int M, int per, PairSources src, double factor, double *__restrict__ partial) {
+  __shared__ double buf[kSweepLds<KIND, R>];
+  pair_sweep_tile<KIND, R>(M, per, blockIdx.x, blockIdx.y, src, factor, partial, buf);
 }
 
 // The rest of a split apply: grid (N bodies x target tiles of kBlock, R). A workgroup forms its
@@ -302,16 +230,8 @@ PairSources sources_of(const bie_geom *g, const double *mu, long long len) {
   return PairSources{g->xy, g->nx, g->ny, g->w, mu, len, g->pair_scale};
 }
 
-// The constants of the sums: the traction kernels' -1/(2 pi) and -1/pi, the double layers' signs
-// the other way round.
-double pair_factor(int kind) {
-  switch (kind) {
-    case kPairLap: return -1.0 / (2.0 * kPi);
-    case kPairStk: return -1.0 / kPi;
-    case kPairLapDl: return 1.0 / (2.0 * kPi);
-    default: return 1.0 / kPi;
-  }
-}
+// The traction kernels' constants, -1/(2 pi) and -1/pi.
+constexpr double pair_factor(int kind) { return (kind == kPairStk ? -1.0 : -0.5) / kPi; }
 
 template <int KIND, int R>
 void sweep(bie_geom *g, int S, const double *mu, long long len, double *partial, hipStream_t st) {
@@ -331,14 +251,18 @@ void small(bie_geom *g, const FinishArgs &a, long long len, hipStream_t st) {
 
 // Source splits of the sweep: workgroups all take about the same time and `resident` of them run
 // at once, so the count that fills whole rounds best is taken, the smallest within 3 % (more splits
-// cost more partial sums), with at least kBlock sources per split and at most four rounds: 25,600
-// nodes take 238 us per Laplace apply with 10 splits (2,000 workgroups in two rounds of 1,024)
-// and 246 with 11 (three rounds); 12,139 nodes 63 us with 21 and 68 with 43.
+// cost more partial sums), with at least kBlock sources per split (64 up to 12 splits) and at
+// most four rounds: 25,600 nodes take 238 us per Laplace apply with 10 splits (2,000 workgroups
+// in two rounds of 1,024) and 246 with 11 (three rounds); 12,139 nodes 63 us with 21 and 68 with
+// 43. Below one round more splits shorten the sweep but lengthen the sum over them: the Stokes
+// double layer of three densities on 1,000 nodes takes 23 us with 3 splits and 14 with 7, on
+// 2,560 nodes 19 us with 10 and 22 with 20.
 int pair_splits(int M, int V) {
   const int tiles = (M + kSweepTile - 1) / kSweepTile, resident = 256 * sweep_occupancy(V);
+  const int most = std::max({1, M / kBlock, std::min(12, M / 64)});
   int best = 1;
   double fill = 0.0;
-  for (int S = 1; S <= std::max(1, M / kBlock) && S * tiles <= std::max(4 * resident, tiles); ++S) {
+  for (int S = 1; S <= most && S * tiles <= std::max(4 * resident, tiles); ++S) {
     const int W = S * tiles, rounds = (W + resident - 1) / resident;
     const double f = (double)W / ((double)rounds * resident);
     if (f > fill + 0.03) {

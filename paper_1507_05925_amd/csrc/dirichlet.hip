@@ -15,9 +15,8 @@
 // a constant, net charge / force zero) is a combination of the data solve with the solves for
 // f = 1 (Laplace), resp. f = e_x and e_y (Stokes).
 //
-// The double-layer sweep is float64 over all pairs (the self pair masked without a branch; its
-// smooth diagonal limit is added in the epilogue): lane = target, sources streamed through scalar
-// registers, source range split over grid.y with one partial per split, summed in a fixed order.
+// The double-layer sweep is the float64 pair sweep of the direct apply with the sources' normals
+// (pairs.h), over all pairs; the smooth diagonal limit is added in the epilogue.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -25,17 +24,11 @@
 #include <cmath>
 
 #include "internal.h"
+#include "pairs.h"
 
 namespace bie {
 
 namespace {
-
-// float64 reciprocal: hardware estimate refined by one Newton step (about 2e-15 relative).
-__device__ inline double rcp_nr(double a) {
-  const double y = __builtin_amdgcn_rcp(a);
-  const double e = fma(-a, y, 1.0);
-  return fma(y, e, y);
-}
 
 __device__ inline double wg_sum(double v, double *sh) {
 #pragma unroll
@@ -49,82 +42,30 @@ __device__ inline double wg_sum(double v, double *sh) {
   return t;
 }
 
-// Double-layer pair sums over the sources of split blockIdx.y, R densities at a time.
-// Laplace: (1/2pi) sum_k w_k mu_k (r.n_k) / |r|^2; Stokes: (1/pi) sum_k (r.n_k)(r.w_k mu_k) r / |r|^4.
-template <bool STOKES, int R>
-__global__ __launch_bounds__(kBlock) void k_dl_sweep(int M, int S, const double2 *__restrict__ xy,
-                                                     const double *__restrict__ nx,
-                                                     const double *__restrict__ ny,
-                                                     const double *__restrict__ w,
-                                                     const double *__restrict__ mu, long long len,
-                                                     double *__restrict__ partial) {
-  const int sp = blockIdx.y;
-  const int i = blockIdx.x * kBlock + threadIdx.x;
-  const bool valid = i < M;
-  const int ii = valid ? i : M - 1;
-  const double2 p = xy[ii];
-  const int k0 = (int)((long long)M * sp / S), k1 = (int)((long long)M * (sp + 1) / S);
-  double g1[R], g2[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) g1[r] = g2[r] = 0.0;
-#pragma unroll 2
-  for (int k = k0; k < k1; ++k) {
-    const double2 q = xy[k];
-    const double dx = p.x - q.x, dy = p.y - q.y;
-    const double rr = fma(dx, dx, dy * dy);
-    const double inv = k == ii ? 0.0 : rcp_nr(rr);  // self pair: r = 0, contributes nothing
-    const double rn = fma(dx, nx[k], dy * ny[k]) * inv * w[k];
-    if (!STOKES) {
-#pragma unroll
-      for (int r = 0; r < R; ++r) g1[r] = fma(rn, mu[(size_t)r * len + k], g1[r]);
-    } else {
-      const double a = rn * inv;
-#pragma unroll
-      for (int r = 0; r < R; ++r) {
-        const double m1 = mu[(size_t)r * len + 2 * k], m2 = mu[(size_t)r * len + 2 * k + 1];
-        const double c = fma(dx, m1, dy * m2) * a;
-        g1[r] = fma(c, dx, g1[r]);
-        g2[r] = fma(c, dy, g2[r]);
-      }
-    }
-  }
-  if (!valid) return;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    double *o = partial + ((size_t)sp * R + r) * len;
-    if (!STOKES) {
-      o[i] = g1[r] / (2.0 * kPi);
-    } else {
-      o[2 * i] = g1[r] / kPi;
-      o[2 * i + 1] = g2[r] / kPi;
-    }
-  }
-}
+// Moments of density r over body b: Laplace int mu (one value); Stokes a = int mu (two) and
+// t = int ((y - z)^perp, mu) about the body's interior point z. One workgroup; sh: 4 doubles of LDS.
+struct MomentArgs {
+  const int *body_ptr;
+  const double *x, *y, *w, *pint, *mu;
+  long long len;
+  double *mom;
+  int N;
+};
 
-// Per (body, density): Laplace int mu (one value); Stokes a = int mu (two) and
-// t = int ((y - z)^perp, mu) about the body's interior point z.
 template <bool STOKES>
-__global__ __launch_bounds__(kBlock) void k_dl_moments(int N, const int *__restrict__ body_ptr,
-                                                       const double *__restrict__ x,
-                                                       const double *__restrict__ y,
-                                                       const double *__restrict__ w,
-                                                       const double *__restrict__ pint,
-                                                       const double *__restrict__ mu,
-                                                       long long len, double *__restrict__ mom) {
-  __shared__ double sh[4];
-  const int b = blockIdx.x, r = blockIdx.y;
-  const int k0 = body_ptr[b], k1 = body_ptr[b + 1];
-  const double *m = mu + (size_t)r * len;
-  const double zx = pint[2 * b], zy = pint[2 * b + 1];
+__device__ void moments(const MomentArgs &a, int b, int r, double *sh) {
+  const int k0 = a.body_ptr[b], k1 = a.body_ptr[b + 1];
+  const double *m = a.mu + (size_t)r * a.len;
+  const double zx = a.pint[2 * b], zy = a.pint[2 * b + 1];
   double a1 = 0.0, a2 = 0.0, t = 0.0;
   for (int k = k0 + threadIdx.x; k < k1; k += kBlock) {
     if (!STOKES) {
-      a1 += w[k] * m[k];
+      a1 += a.w[k] * m[k];
     } else {
-      const double m1 = w[k] * m[2 * k], m2 = w[k] * m[2 * k + 1];
+      const double m1 = a.w[k] * m[2 * k], m2 = a.w[k] * m[2 * k + 1];
       a1 += m1;
       a2 += m2;
-      t += (x[k] - zx) * m2 - (y[k] - zy) * m1;
+      t += (a.x[k] - zx) * m2 - (a.y[k] - zy) * m1;
     }
   }
   a1 = wg_sum(a1, sh);
@@ -134,9 +75,9 @@ __global__ __launch_bounds__(kBlock) void k_dl_moments(int N, const int *__restr
   }
   if (threadIdx.x == 0) {
     if (!STOKES) {
-      mom[(size_t)r * N + b] = a1;
+      a.mom[(size_t)r * a.N + b] = a1;
     } else {
-      double *o = mom + ((size_t)r * N + b) * 3;
+      double *o = a.mom + ((size_t)r * a.N + b) * 3;
       o[0] = a1;
       o[1] = a2;
       o[2] = t;
@@ -144,16 +85,42 @@ __global__ __launch_bounds__(kBlock) void k_dl_moments(int N, const int *__restr
   }
 }
 
+// Grid (bodies, densities).
+template <bool STOKES>
+__global__ __launch_bounds__(kBlock) void k_dl_moments(MomentArgs a) {
+  __shared__ double sh[4];
+  moments<STOKES>(a, blockIdx.x, blockIdx.y, sh);
+}
+
+// Double-layer pair sums of R densities (pairs.h), Laplace (1/2pi) sum_k w_k mu_k (r.n_k) / |r|^2,
+// Stokes (1/pi) sum_k (r.n_k)(r.w_k mu_k) r / |r|^4, and in the same launch the densities'
+// moments: workgroups [0, N R) form those (few and short; they start first), the others take
+// (tile, split) of the sweep.
+template <int KIND, int R>
+__global__ __launch_bounds__(kBlock, sweep_occupancy(PairShape<KIND, R>::V)) void k_dl_sweep(
+    int M, int per, int tiles, int nmom, MomentArgs ma, PairSources src, double factor,
+    double *__restrict__ partial) {
+  __shared__ double buf[kSweepLds<KIND, R>];
+  const int w = blockIdx.x - nmom;
+  if (w < 0) {
+    moments<KIND == kPairStkDl>(ma, blockIdx.x % ma.N, blockIdx.x / ma.N, buf);
+    return;
+  }
+  pair_sweep_tile<KIND, R>(M, per, w % tiles, w / tiles, src, factor, partial, buf);
+}
+
 // out = alpha (1/2 mu + diagonal limit + sum of the split partials + completion), one lane per
 // node, grid.y = density. The completion loops over all bodies (wave-uniform).
+constexpr int kEpi = 64;  // one wave per workgroup: the paper's geometries have few nodes
+
 template <bool STOKES>
-__global__ __launch_bounds__(kBlock) void k_dl_epilogue(
+__global__ __launch_bounds__(kEpi) void k_dl_epilogue(
     int M, int N, int S, int R, const double2 *__restrict__ xy, const double *__restrict__ nx,
     const double *__restrict__ ny, const double *__restrict__ w, const double *__restrict__ kappa,
     const double *__restrict__ pint, const double *__restrict__ scale, const double *__restrict__ mu,
     long long len, const double *__restrict__ partial, const double *__restrict__ mom,
     int with_C, double alpha, double *__restrict__ out) {
-  const int i = blockIdx.x * kBlock + threadIdx.x;
+  const int i = blockIdx.x * kEpi + threadIdx.x;
   const int r = blockIdx.y;
   if (i >= M) return;
   const double2 p = xy[i];
@@ -324,39 +291,38 @@ __global__ void k_dl_density(long long len, int nrhs, int extra, const double *_
 
 inline unsigned nb(long long n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
-// source splits: about 1024 workgroups, each split at least 256 sources
-int dl_splits(int M) {
-  const int tb = (M + kBlock - 1) / kBlock;
-  int S = std::max(1, std::min(32, (1024 + tb - 1) / tb));
-  return std::max(1, std::min(S, M / 256));
+MomentArgs moment_args(const bie_geom *g, long long len, const double *mu, double *mom) {
+  return MomentArgs{g->body_ptr, g->x, g->y, g->w, g->pint, mu, len, mom, g->N};
 }
 
-template <bool STOKES, int R>
-void launch_sweep(bie_geom *g, int S, const double *mu, long long len, double *partial,
-                  hipStream_t st) {
-  hipLaunchKernelGGL((k_dl_sweep<STOKES, R>), dim3(nb(g->M), S), dim3(kBlock), 0, st, g->M, S,
-                     g->xy, g->nx, g->ny, g->w, mu, len, partial);
+template <int KIND, int R>
+void launch_sweep(bie_geom *g, int S, bool with_C, const double *mu, long long len, double *mom,
+                  double *partial, hipStream_t st) {
+  const int tiles = (g->M + kSweepTile - 1) / kSweepTile, nmom = with_C ? g->N * R : 0;
+  hipLaunchKernelGGL((k_dl_sweep<KIND, R>), dim3(nmom + tiles * S), dim3(kBlock), 0, st, g->M,
+                     (g->M + S - 1) / S, tiles, nmom, moment_args(g, len, mu, mom),
+                     PairSources{g->xy, g->nx, g->ny, g->w, mu, len, g->pair_scale},
+                     (KIND == kPairStkDl ? 1.0 : 0.5) / kPi, partial);
 }
 
-template <bool STOKES>
-void sweep_chunk(bie_geom *g, int S, int R, const double *mu, long long len, double *partial,
-                 hipStream_t st) {
+template <int KIND>
+void sweep_chunk(bie_geom *g, int S, int R, bool with_C, const double *mu, long long len,
+                 double *mom, double *partial, hipStream_t st) {
   switch (R) {
-    case 8: launch_sweep<STOKES, 8>(g, S, mu, len, partial, st); break;
-    case 4: launch_sweep<STOKES, 4>(g, S, mu, len, partial, st); break;
-    case 2: launch_sweep<STOKES, 2>(g, S, mu, len, partial, st); break;
-    default: launch_sweep<STOKES, 1>(g, S, mu, len, partial, st); break;
+    case 4: launch_sweep<KIND, 4>(g, S, with_C, mu, len, mom, partial, st); break;
+    case 3: launch_sweep<KIND, 3>(g, S, with_C, mu, len, mom, partial, st); break;
+    case 2: launch_sweep<KIND, 2>(g, S, with_C, mu, len, mom, partial, st); break;
+    case 1: launch_sweep<KIND, 1>(g, S, with_C, mu, len, mom, partial, st); break;
+    default:
+      if constexpr (KIND == kPairLapDl) launch_sweep<KIND, 8>(g, S, with_C, mu, len, mom, partial, st);
   }
 }
 
 int dl_moments(bie_geom *g, int stokes, int nrhs, const double *mu, double *mom, hipStream_t st) {
   const long long len = stokes ? 2LL * g->M : g->M;
-  if (stokes)
-    hipLaunchKernelGGL(k_dl_moments<true>, dim3(g->N, nrhs), dim3(kBlock), 0, st, g->N,
-                       g->body_ptr, g->x, g->y, g->w, g->pint, mu, len, mom);
-  else
-    hipLaunchKernelGGL(k_dl_moments<false>, dim3(g->N, nrhs), dim3(kBlock), 0, st, g->N,
-                       g->body_ptr, g->x, g->y, g->w, g->pint, mu, len, mom);
+  const MomentArgs a = moment_args(g, len, mu, mom);
+  if (stokes) hipLaunchKernelGGL(k_dl_moments<true>, dim3(g->N, nrhs), dim3(kBlock), 0, st, a);
+  else hipLaunchKernelGGL(k_dl_moments<false>, dim3(g->N, nrhs), dim3(kBlock), 0, st, a);
   BIE_HIP_CHECK(hipGetLastError());
   return BIE_OK;
 }
@@ -372,32 +338,35 @@ int dl_apply(bie_geom *g, int stokes, int with_C, double alpha, int nrhs, const 
   const int comps = stokes ? 2 : 1, C = stokes ? 3 : 1;
   const long long len = (long long)g->M * comps;
   const int maxR = stokes ? 4 : 8;
-  const int S = dl_splits(g->M);
-  // workspace: partial [S][maxR][len], moments [nrhs][N][C]
-  const size_t need = ((size_t)S * maxR * len + (size_t)nrhs * g->N * C) * sizeof(double);
-  BIE_TRY(g->ws_apply.reserve(need));
+  // chunks of up to maxR densities; workspace: partial [S][R][len] (the largest chunk's), moments
+  // [nrhs][N][C]
+  const int kind = stokes ? kPairStkDl : kPairLapDl;
+  auto chunk = [&](int left) { return left >= maxR ? maxR : std::min(left, 4); };
+  size_t part = 0;
+  for (int r0 = 0; r0 < nrhs; r0 += chunk(nrhs - r0)) {
+    const int R = chunk(nrhs - r0);
+    part = std::max(part, (size_t)pair_splits(g->M, pair_values(kind, R)) * R * (size_t)len);
+  }
+  BIE_TRY(g->ws_apply.reserve((part + (size_t)nrhs * g->N * C) * sizeof(double)));
   double *partial = g->ws_apply.as<double>();
-  double *mom = partial + (size_t)S * maxR * len;
+  double *mom = partial + part;
   ProfScope prof(BIE_K_DOUBLE_LAYER, st, (long long)nrhs * g->M * (long long)g->M);
-  if (with_C) BIE_TRY(dl_moments(g, stokes, nrhs, mu, mom, st));
   for (int r0 = 0; r0 < nrhs;) {
-    const int left = nrhs - r0;
-    const int R = left >= maxR ? maxR : (left >= 4 ? 4 : (left >= 2 ? 2 : 1));
+    const int R = chunk(nrhs - r0), S = pair_splits(g->M, pair_values(kind, R));
     const size_t off = (size_t)r0 * len;
-    if (stokes)
-      sweep_chunk<true>(g, S, R, mu + off, len, partial, st);
-    else
-      sweep_chunk<false>(g, S, R, mu + off, len, partial, st);
-    BIE_HIP_CHECK(hipGetLastError());
-    const double *mo = mom + (size_t)r0 * g->N * C;
-    if (stokes)
-      hipLaunchKernelGGL(k_dl_epilogue<true>, dim3(nb(g->M), R), dim3(kBlock), 0, st, g->M, g->N,
+    double *mo = mom + (size_t)r0 * g->N * C;
+    const unsigned nt = (unsigned)((g->M + kEpi - 1) / kEpi);
+    if (stokes) {
+      sweep_chunk<kPairStkDl>(g, S, R, with_C != 0, mu + off, len, mo, partial, st);
+      hipLaunchKernelGGL(k_dl_epilogue<true>, dim3(nt, R), dim3(kEpi), 0, st, g->M, g->N,
                          S, R, g->xy, g->nx, g->ny, g->w, g->kappa, g->pint, g->dl_scale,
                          mu + off, len, partial, mo, with_C, alpha, out + off);
-    else
-      hipLaunchKernelGGL(k_dl_epilogue<false>, dim3(nb(g->M), R), dim3(kBlock), 0, st, g->M,
+    } else {
+      sweep_chunk<kPairLapDl>(g, S, R, with_C != 0, mu + off, len, mo, partial, st);
+      hipLaunchKernelGGL(k_dl_epilogue<false>, dim3(nt, R), dim3(kEpi), 0, st, g->M,
                          g->N, S, R, g->xy, g->nx, g->ny, g->w, g->kappa, g->pint, g->dl_scale,
                          mu + off, len, partial, mo, with_C, alpha, out + off);
+    }
     BIE_HIP_CHECK(hipGetLastError());
     r0 += R;
   }

@@ -4,6 +4,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include "internal.h"
+
 namespace bie {
 
 // The pair kernels, r = target - source, s the source's strength (w times the density):
@@ -129,5 +131,90 @@ struct PairRaw {
     for (int v = 0; v < S::COMPS * R; ++v) buf[(st + v) * stride + t] = valid ? w * mu[v] : 0.0;
   }
 };
+
+// Split sweep over the sources [sp per, (sp + 1) per) for one tile of targets.
+constexpr int kSweepT = 2;                // targets per lane
+constexpr int kSweepTile = 64 * kSweepT;  // targets per workgroup
+constexpr int kStage = kBlock;            // sources staged at a time: one per thread
+
+// Waves per SIMD that the sweep's registers leave room for (its launch bound), by the number of
+// sums per target.
+constexpr int sweep_occupancy(int V) { return V <= 2 ? 4 : V <= 4 ? 3 : 2; }
+
+template <int KIND, int R>
+constexpr int kSweepLds = PairShape<KIND, R>::ARR * kStage > 4 * kSweepTile * PairShape<KIND, R>::V
+                              ? PairShape<KIND, R>::ARR * kStage
+                              : 4 * kSweepTile * PairShape<KIND, R>::V;
+
+// A workgroup of kBlock threads; buf: kSweepLds doubles of LDS. Wave w takes the quads w, w + 4, ...
+// of each staged block; the four waves' sums are added in wave order through LDS. Blocks that
+// hold one of the tile's own nodes (a uniform test) mask the pair of a node with itself.
+template <int KIND, int R>
+__device__ __forceinline__ void pair_sweep_tile(int M, int per, int tile, int sp,
+                                                const PairSources &src, double factor,
+                                                double *__restrict__ partial, double *buf) {
+  using P = PairShape<KIND, R>;
+  const int i0 = tile * kSweepTile;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int k0 = sp * per, k1 = min(k0 + per, M);
+  double tx[kSweepT], ty[kSweepT], nx[kSweepT], ny[kSweepT], acc[kSweepT][P::V];
+#pragma unroll
+  for (int u = 0; u < kSweepT; ++u) {
+    const int i = min(i0 + lane + 64 * u, M - 1);
+    const double2 z = src.xy[i];
+    tx[u] = z.x * src.scale;
+    ty[u] = z.y * src.scale;
+    nx[u] = P::DL ? 0.0 : src.nx[i];
+    ny[u] = P::DL ? 0.0 : src.ny[i];
+#pragma unroll
+    for (int v = 0; v < P::V; ++v) acc[u][v] = 0.0;
+  }
+  PairRaw<KIND, R> rec;
+  const int t = threadIdx.x;
+  rec.load(src, min(k0 + t, k1 - 1));
+  for (int base = k0; base < k1; base += kStage) {
+    rec.store(src.scale, base + t < k1, buf, kStage, t);
+    __syncthreads();
+    rec.load(src, min(base + kStage + t, k1 - 1));  // the next block, during this block's pairs
+    const int nq = (min(k1 - base, kStage) + 3) >> 2;  // quads (the last one padded)
+    if (base < i0 + kSweepTile && base + kStage > i0) {
+      for (int q = wv; q < nq; q += 4)
+#pragma unroll
+        for (int u = 0; u < kSweepT; ++u)
+          pair_quad<KIND, R, true>(buf, kStage, 4 * q, i0 + lane + 64 * u - base, tx[u], ty[u],
+                                   nx[u], ny[u], acc[u]);
+    } else {
+      for (int q = wv; q < nq; q += 4)
+#pragma unroll
+        for (int u = 0; u < kSweepT; ++u)
+          pair_quad<KIND, R, false>(buf, kStage, 4 * q, -1, tx[u], ty[u], nx[u], ny[u], acc[u]);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int u = 0; u < kSweepT; ++u)
+#pragma unroll
+    for (int v = 0; v < P::V; ++v) buf[(wv * P::V + v) * kSweepTile + lane + 64 * u] = acc[u][v];
+  __syncthreads();
+  const double f = factor * src.scale;
+  constexpr int kOut = KIND == kPairLap ? R : P::V;  // values per target after the normal component
+  for (int e = t; e < kSweepTile * kOut; e += kBlock) {
+    const int j = e % kSweepTile, v = e / kSweepTile, i = i0 + j;
+    if (i >= M) continue;
+    auto sum = [&](int c) {
+      const double *b = buf + c * kSweepTile + j;
+      constexpr int w = P::V * kSweepTile;
+      return (b[0] + b[w]) + (b[2 * w] + b[3 * w]);
+    };
+    if constexpr (KIND == kPairLap && R == 1) {
+      partial[(size_t)sp * M + i] = f * (src.nx[i] * sum(0) + src.ny[i] * sum(1));
+    } else if constexpr (P::STK) {
+      partial[((size_t)sp * R + v / 2) * 2 * M + 2 * i + (v & 1)] = f * sum(v);
+    } else {
+      partial[((size_t)sp * R + v) * M + i] = f * sum(v);
+    }
+  }
+}
 
 }  // namespace bie

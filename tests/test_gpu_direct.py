@@ -7,6 +7,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
+from oracle import dirichlet as di  # noqa: E402
 from oracle import nystrom as ny  # noqa: E402
 from paper_1507_05925_amd import bie2d  # noqa: E402
 from paper_1507_05925_amd import workloads as wl  # noqa: E402
@@ -44,3 +45,21 @@ def test_direct_apply_edges(name, scale):
             tol = 64 * np.finfo(float).eps * (np.abs(A) @ np.abs(mu).T).max()
             out = f(g, torch.as_tensor(mu, device="cuda")).cpu().numpy()
             assert np.abs(out - mu @ A.T).max() <= tol, kind
+
+
+@pytest.mark.parametrize("nodes", [[3], [64, 65], [127, 129, 5], [500, 500], [257, 511, 900]])
+def test_double_layer_apply_edges(nodes):
+    """The double-layer applies at the edges of their tiles and splits, every grouping of
+    densities, against the dense oracle."""
+    rng = np.random.default_rng(len(nodes))
+    c = wl.mixed_grid(rng, len(nodes), np.array(nodes))
+    geo = ny.geometry_of(c)
+    g = bie2d.Geometry.from_curves(c)
+    for kind, rhs in ((0, (1, 2, 3, 6, 8, 11)), (1, (1, 2, 3, 4, 7))):
+        A = di.capacitance_operator(geo) if kind == 0 else di.resistance_operator(geo)
+        f = bie2d.bie_laplace_dl_apply if kind == 0 else bie2d.bie_stokes_dl_apply
+        for R in rhs:
+            mu = rng.standard_normal((R, g.M * (1 + kind)))
+            tol = 64 * np.finfo(float).eps * (np.abs(A) @ np.abs(mu).T).max()
+            out = f(g, torch.as_tensor(mu, device="cuda")).cpu().numpy()
+            assert np.abs(out - mu @ A.T).max() <= tol, (kind, R)
