@@ -67,25 +67,7 @@ struct FmmTree {
   double *fact_out = nullptr, *fact_in = nullptr;  // (-1)^n c^n / n!  and  c^n / n!
   double *inv_h = nullptr;  // [L+1]
   DevBuf work;              // charges + expansions
-  // evaluation at arbitrary points (treecode over this tree): per box its level, centre,
-  // children and run [lo, hi) of sorted nodes (host); the log-expansion factors
-  // T_log[m] = (m - 1)! / s^m (device); the interaction lists of the geometry's read-off points
-  std::vector<int> h_level, h_child, h_lo, h_hi;
-  std::vector<double2> h_center;
-  double *T_log = nullptr;
-  struct PointLists *rd = nullptr;
-};
-
-// Interaction lists of a set of evaluation points: boxes whose multipoles are evaluated at the
-// point (every box at level >= 2 with |z - c| >= sqrt(2) h, i.e. twice its half-diagonal, whose
-// parent is not), and the runs [k0, k1) of sorted nodes of the remaining leaves, summed directly.
-struct PointLists {
-  int npts = 0;
-  long long nbox_total = 0, direct_pairs = 0;
-  DevBuf buf;
-  int *box_ptr = nullptr, *run_ptr = nullptr;  // [npts + 1] each
-  int2 *box = nullptr;                         // (box, level)
-  int2 *run = nullptr;                         // [k0, k1)
+  double *T_log = nullptr;  // log-expansion factors (m - 1)! / s^m
 };
 
 struct FmmPlan {
@@ -100,10 +82,6 @@ struct FmmPlan {
     if (fork) (void)hipEventDestroy(fork);
     if (join) (void)hipEventDestroy(join);
     for (auto &kv : trees) {
-      if (kv.second->rd) {
-        kv.second->rd->buf.release();
-        delete kv.second->rd;
-      }
       kv.second->buf.release();
       kv.second->work.release();
       delete kv.second;
@@ -1195,22 +1173,106 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// The boxes and leaves that a point interacts with, found by one wave on the device: from the
+// level-2 boxes down, a box at level l with |z - c| >= sqrt(2) h_l (twice its half-diagonal: the
+// multipole's terms fall at least as 2^-m) is evaluated by its multipole, a leaf closer than that
+// contributes its nodes directly, any other box is replaced by its children. The boxes of a level
+// closer than that are lattice points in an open disc of radius sqrt(2) spacings, at most nine,
+// so a level has at most 36 candidates, one per lane (a point whose distances are not numbers
+// accepts every level-2 box). Lists built on the host for every call took 9.4 of 10 ms for the
+// potential at 30,000 points around 76,800 nodes.
+struct TreeWalk {
+  int L, b2, n2, leaf0;  // depth, first level-2 box and their count, first leaf box
+  double size;
+  const int *child, *leaf_start;
+  const double2 *center;
+};
+constexpr int kWalkBoxes = 16 + 36 * 12;  // accepted boxes of a point: levels 2 .. 14
+constexpr int kWalkLeaves = 36;
+
+struct WalkLists {
+  int2 box[kWalkBoxes];    // (box, level), evaluated by multipole
+  int2 leaf[kWalkLeaves];  // (first node, nodes before this leaf in the list)
+  int front[2][64];
+  int nbox, nleaf, nnode;
+};
+
+__device__ __forceinline__ void walk_tree(const TreeWalk &t, double2 z, WalkLists &w) {
+  const int lane = threadIdx.x;
+  const unsigned long long below = (1ull << lane) - 1;
+  int n = t.n2, nbox = 0, nleaf = 0, nnode = 0, cur = 0;
+  int b = lane < n ? t.b2 + lane : -1;
+  for (int l = 2; l <= t.L; ++l) {
+    const double h = t.size / (double)(1 << l);
+    bool close = false;
+    if (b >= 0) {
+      const double2 c = t.center[b];
+      const double dx = z.x - c.x, dy = z.y - c.y;
+      close = dx * dx + dy * dy < 2.0 * h * h;
+    }
+    const bool far = b >= 0 && !close;
+    const unsigned long long mf = __ballot(far);
+    const int at = nbox + __popcll(mf & below);
+    if (far && at < kWalkBoxes) w.box[at] = make_int2(b, l);
+    nbox = min(nbox + __popcll(mf), kWalkBoxes);
+    if (l == t.L) {  // the close leaves, with their nodes' offsets in the concatenated list
+      int s = 0, cnt = 0;
+      if (close) {
+        s = t.leaf_start[b - t.leaf0];
+        cnt = t.leaf_start[b - t.leaf0 + 1] - s;
+      }
+      unsigned long long m = __ballot(close);
+      while (m && nleaf < kWalkLeaves) {
+        const int src = __ffsll(m) - 1;
+        m &= m - 1;
+        if (lane == src) w.leaf[nleaf] = make_int2(s, nnode);
+        nnode += __shfl(cnt, src, 64);
+        ++nleaf;
+      }
+      break;
+    }
+    cur ^= 1;
+    n = 0;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int ch = close ? t.child[4 * b + c] : -1;
+      const unsigned long long m = __ballot(ch >= 0);
+      const int k = n + __popcll(m & below);
+      if (ch >= 0 && k < 64) w.front[cur][k] = ch;
+      n = min(n + __popcll(m), 64);
+    }
+    __syncthreads();
+    b = lane < n ? w.front[cur][lane] : -1;
+  }
+  w.nbox = nbox;  // (every lane writes the same values)
+  w.nleaf = nleaf;
+  w.nnode = nnode;
+  __syncthreads();
+}
+
+// Node k of the concatenated list of close leaves.
+__device__ __forceinline__ int walk_node(const WalkLists &w, int k) {
+  int e = 0;
+  while (e + 1 < w.nleaf && w.leaf[e + 1].y <= k) ++e;
+  return w.leaf[e].x + (k - w.leaf[e].y);
+}
+
 // Laplace: phi(z) = -(1/2pi) sum_k q_k log|z - zeta_k|. Grid (points, R), one wave each.
 template <int P>
 __global__ __launch_bounds__(64) void k_eval_lap(
-    int M, int nbox, double size, const double2 *__restrict__ pts, double ox, double oy,
-    const int *__restrict__ box_ptr, const int2 *__restrict__ boxes,
-    const int *__restrict__ run_ptr, const int2 *__restrict__ runs,
-    const double2 *__restrict__ center, const double *__restrict__ T_log,
-    const double2 *__restrict__ xs, const double2 *__restrict__ Q,
-    const double2 *__restrict__ Mexp, int npts, double *__restrict__ out) {
+    int M, int nbox, TreeWalk tree, const double2 *__restrict__ pts, double ox, double oy,
+    const double *__restrict__ T_log, const double2 *__restrict__ xs,
+    const double2 *__restrict__ Q, const double2 *__restrict__ Mexp, int npts,
+    double *__restrict__ out) {
+  __shared__ WalkLists w;
   const int p = blockIdx.x, r = blockIdx.y, lane = threadIdx.x;
   const double2 z = make_double2(pts[p].x - ox, pts[p].y - oy);
+  walk_tree(tree, z, w);
   double acc = 0.0;
-  for (int e = box_ptr[p] + lane; e < box_ptr[p + 1]; e += 64) {
-    const int2 bl = boxes[e];
-    const double h = size / (double)(1 << bl.y);
-    const double2 c = center[bl.x];
+  for (int e = lane; e < w.nbox; e += 64) {
+    const int2 bl = w.box[e];
+    const double h = tree.size / (double)(1 << bl.y);
+    const double2 c = tree.center[bl.x];
     const double2 dz = make_double2(z.x - c.x, z.y - c.y);
     const double2 id = cdiv1(dz);
     const double2 t = make_double2(h * id.x, h * id.y);
@@ -1223,13 +1285,11 @@ __global__ __launch_bounds__(64) void k_eval_lap(
     acc += u[0].x * 0.5 * log(fma(dz.x, dz.x, dz.y * dz.y)) - S.x;
   }
   const double2 *q = Q + (size_t)r * M;
-  for (int e = run_ptr[p]; e < run_ptr[p + 1]; ++e) {
-    const int2 kr = runs[e];
-    for (int k = kr.x + lane; k < kr.y; k += 64) {
-      const double2 zk = xs[k];
-      const double dx = z.x - zk.x, dy = z.y - zk.y;
-      acc = fma(q[k].x, 0.5 * log(fma(dx, dx, dy * dy)), acc);
-    }
+  for (int e = lane; e < w.nnode; e += 64) {
+    const int k = walk_node(w, e);
+    const double2 zk = xs[k];
+    const double dx = z.x - zk.x, dy = z.y - zk.y;
+    acc = fma(q[k].x, 0.5 * log(fma(dx, dx, dy * dy)), acc);
   }
   acc = wave_sum(acc);
   if (lane == 0) out[(size_t)r * npts + p] = -acc / (2.0 * kPi);
@@ -1239,20 +1299,20 @@ __global__ __launch_bounds__(64) void k_eval_lap(
 // and omega for body p (out [R][npts][3]), else the velocity (out [R][npts][2]).
 template <int P>
 __global__ __launch_bounds__(64) void k_eval_stk(
-    int M, int nbox, double size, const double2 *__restrict__ pts, double ox, double oy,
-    const int *__restrict__ box_ptr, const int2 *__restrict__ boxes,
-    const int *__restrict__ run_ptr, const int2 *__restrict__ runs,
-    const double2 *__restrict__ center, const double *__restrict__ T_log,
-    const double *__restrict__ T_c, const double2 *__restrict__ xs,
-    const double2 *__restrict__ Q, const double2 *__restrict__ Mexp, int npts, int rigid,
-    const double *__restrict__ xc, const double *__restrict__ yc, double *__restrict__ out) {
+    int M, int nbox, TreeWalk tree, const double2 *__restrict__ pts, double ox, double oy,
+    const double *__restrict__ T_log, const double *__restrict__ T_c,
+    const double2 *__restrict__ xs, const double2 *__restrict__ Q,
+    const double2 *__restrict__ Mexp, int npts, int rigid, const double *__restrict__ xc,
+    const double *__restrict__ yc, double *__restrict__ out) {
+  __shared__ WalkLists w;
   const int p = blockIdx.x, r = blockIdx.y, lane = threadIdx.x;
   const double2 z = make_double2(pts[p].x - ox, pts[p].y - oy);
+  walk_tree(tree, z, w);
   double u1 = 0.0, u2 = 0.0, om = 0.0;  // raw sums: u = (1/4pi) (u1, u2), omega = -(1/4pi) om
-  for (int e = box_ptr[p] + lane; e < box_ptr[p + 1]; e += 64) {
-    const int2 bl = boxes[e];
-    const double h = size / (double)(1 << bl.y);
-    const double2 c = center[bl.x];
+  for (int e = lane; e < w.nbox; e += 64) {
+    const int2 bl = w.box[e];
+    const double h = tree.size / (double)(1 << bl.y);
+    const double2 c = tree.center[bl.x];
     const double2 dz = make_double2(z.x - c.x, z.y - c.y);
     const double2 id = cdiv1(dz);
     const double2 t = make_double2(h * id.x, h * id.y);
@@ -1283,18 +1343,16 @@ __global__ __launch_bounds__(64) void k_eval_stk(
     om += A.y;
   }
   const double2 *f = Q + (size_t)(3 * r) * M;
-  for (int e = run_ptr[p]; e < run_ptr[p + 1]; ++e) {
-    const int2 kr = runs[e];
-    for (int k = kr.x + lane; k < kr.y; k += 64) {
-      const double2 zk = xs[k], fk = f[k];
-      const double dx = z.x - zk.x, dy = z.y - zk.y;
-      const double rr = fma(dx, dx, dy * dy);
-      const double lg = 0.5 * log(rr), inv = 1.0 / rr;
-      const double rt = fma(dx, fk.x, dy * fk.y) * inv;
-      u1 += -lg * fk.x + dx * rt;
-      u2 += -lg * fk.y + dy * rt;
-      om += (dx * fk.y - dy * fk.x) * inv;
-    }
+  for (int e = lane; e < w.nnode; e += 64) {
+    const int k = walk_node(w, e);
+    const double2 zk = xs[k], fk = f[k];
+    const double dx = z.x - zk.x, dy = z.y - zk.y;
+    const double rr = fma(dx, dx, dy * dy);
+    const double lg = 0.5 * log(rr), inv = 1.0 / rr;
+    const double rt = fma(dx, fk.x, dy * fk.y) * inv;
+    u1 += -lg * fk.x + dx * rt;
+    u2 += -lg * fk.y + dy * rt;
+    om += (dx * fk.y - dy * fk.x) * inv;
   }
   u1 = wave_sum(u1);
   u2 = wave_sum(u2);
@@ -1419,7 +1477,7 @@ int build_tree(bie_geom *g, int p, int leaf_cap, FmmTree &t, hipStream_t s) {
     return t.level_off[l] + (int)(it - keys[l].begin());
   };
   std::vector<double2> center(t.nbox);
-  std::vector<int> child(4 * t.nbox, -1), parent(t.nbox, -1), box_level(t.nbox);
+  std::vector<int> child(4 * t.nbox, -1), parent(t.nbox, -1);
   for (int l = 0; l <= L; ++l) {
     const int n = 1 << l;
     const double h = t.size / n;
@@ -1427,7 +1485,6 @@ int build_tree(bie_geom *g, int p, int leaf_cap, FmmTree &t, hipStream_t s) {
       const long long kk = keys[l][b];
       const long long ix = decode((unsigned)kk), iy = decode((unsigned)(kk >> 1));
       const int gb = t.level_off[l] + (int)b;
-      box_level[gb] = l;
       center[gb] = make_double2(-0.5 * t.size + (ix + 0.5) * h, -0.5 * t.size + (iy + 0.5) * h);
       if (l > 0) {
         const int pb = find(l - 1, kk >> 2);
@@ -1438,24 +1495,6 @@ int build_tree(bie_geom *g, int p, int leaf_cap, FmmTree &t, hipStream_t s) {
     }
     (void)n;
   }
-  // host copies for the evaluation at arbitrary points: box levels, centres, children, and the
-  // run of sorted nodes of every box (leaves first, then each parent spans its children)
-  t.h_level = box_level;
-  t.h_center = center;
-  t.h_child = child;
-  t.h_lo.assign(t.nbox, M);
-  t.h_hi.assign(t.nbox, 0);
-  for (int b = 0; b < (int)keys[L].size(); ++b) {
-    t.h_lo[t.level_off[L] + b] = leaf_start[b];
-    t.h_hi[t.level_off[L] + b] = leaf_start[b + 1];
-  }
-  for (int l = L - 1; l >= 0; --l)
-    for (int b = t.level_off[l]; b < t.level_off[l + 1]; ++b)
-      for (int c = 0; c < 4; ++c)
-        if (child[4 * b + c] >= 0) {
-          t.h_lo[b] = std::min(t.h_lo[b], t.h_lo[child[4 * b + c]]);
-          t.h_hi[b] = std::max(t.h_hi[b], t.h_hi[child[4 * b + c]]);
-        }
   // M2L lists (levels >= 2) and near lists (leaves)
   std::vector<int> m2l_ptr(1, 0), m2l_src, m2l_off;
   const int off2 = t.level_off[std::min(2, L)];
@@ -1989,76 +2028,9 @@ int get_tree(bie_geom *g, int p, int leaf, hipStream_t s, FmmTree **out) {
   return BIE_OK;
 }
 
-// Interaction lists of the points pts (absolute coordinates, host) on tree t: a descent from
-// the level-2 boxes; a box at level l >= 2 with |z - c| >= sqrt(2) h_l (twice its half-diagonal:
-// the multipole's terms fall at least as 2^-m) is evaluated by its multipole, a leaf closer
-// than that contributes its nodes directly, any other box is replaced by its children.
-int build_point_lists(const FmmTree &t, const std::vector<double2> &pts, PointLists &pl,
-                      hipStream_t s) {
-  const int n = (int)pts.size();
-  std::vector<int> bptr(1, 0), rptr(1, 0);
-  std::vector<int2> bx, rn;
-  std::vector<int> stack;
-  long long direct = 0;
-  for (int i = 0; i < n; ++i) {
-    const double zx = pts[i].x - t.ox, zy = pts[i].y - t.oy;
-    stack.clear();
-    const int l2 = std::min(2, t.L);
-    for (int b = t.level_off[l2 + 1] - 1; b >= t.level_off[l2]; --b) stack.push_back(b);
-    std::vector<int2> myruns;
-    while (!stack.empty()) {
-      const int b = stack.back();
-      stack.pop_back();
-      const int l = t.h_level[b];
-      const double h = t.size / (double)(1 << l);
-      const double dx = zx - t.h_center[b].x, dy = zy - t.h_center[b].y;
-      if (l >= 2 && dx * dx + dy * dy >= 2.0 * h * h) {
-        bx.push_back(make_int2(b, l));
-      } else if (l == t.L) {
-        myruns.push_back(make_int2(t.h_lo[b], t.h_hi[b]));
-      } else {
-        for (int c = 3; c >= 0; --c)
-          if (t.h_child[4 * b + c] >= 0) stack.push_back(t.h_child[4 * b + c]);
-      }
-    }
-    std::sort(myruns.begin(), myruns.end(), [](int2 a, int2 b) { return a.x < b.x; });
-    for (const int2 &r : myruns) {
-      direct += r.y - r.x;
-      if (!rn.empty() && (int)rn.size() > rptr.back() && rn.back().y == r.x) rn.back().y = r.y;
-      else rn.push_back(r);
-    }
-    bptr.push_back((int)bx.size());
-    rptr.push_back((int)rn.size());
-  }
-  pl.npts = n;
-  pl.nbox_total = (long long)bx.size();
-  pl.direct_pairs = direct;
-  const size_t bytes = (size_t)(2 * (n + 1)) * 4 + (bx.size() + rn.size()) * 8 + 4 * 256;
-  BIE_TRY(pl.buf.reserve(bytes));
-  char *q = pl.buf.as<char>();
-  auto take = [&](size_t nb) {
-    char *r = q;
-    q += (nb + 255) & ~size_t(255);
-    return r;
-  };
-  pl.box_ptr = (int *)take((n + 1) * 4);
-  pl.run_ptr = (int *)take((n + 1) * 4);
-  pl.box = (int2 *)take(std::max<size_t>(bx.size(), 1) * 8);
-  pl.run = (int2 *)take(std::max<size_t>(rn.size(), 1) * 8);
-  BIE_HIP_CHECK(hipMemcpyAsync(pl.box_ptr, bptr.data(), bptr.size() * 4, hipMemcpyHostToDevice, s));
-  BIE_HIP_CHECK(hipMemcpyAsync(pl.run_ptr, rptr.data(), rptr.size() * 4, hipMemcpyHostToDevice, s));
-  if (!bx.empty())
-    BIE_HIP_CHECK(hipMemcpyAsync(pl.box, bx.data(), bx.size() * 8, hipMemcpyHostToDevice, s));
-  if (!rn.empty())
-    BIE_HIP_CHECK(hipMemcpyAsync(pl.run, rn.data(), rn.size() * 8, hipMemcpyHostToDevice, s));
-  BIE_HIP_CHECK(hipStreamSynchronize(s));  // the host vectors go out of scope
-  return BIE_OK;
-}
-
 }  // namespace
 
-// Single-layer potentials of dens at npts points pts (device [npts][2]; the geometry's read-off
-// points when pts == g->pint, whose lists are kept with the tree) by the treecode over the
+// Single-layer potentials of dens at npts points pts (device [npts][2]) by the treecode over the
 // float64 FMM tree of the geometry's order and leaf size. Laplace: res [nrhs][npts]; Stokes:
 // rigid (read-off) res [nrhs][npts][3] = (v, omega), else velocities [nrhs][npts][2].
 int fmm_eval_points(bie_geom *g, int kind, int nrhs, const double *dens, int npts,
@@ -2068,31 +2040,11 @@ int fmm_eval_points(bie_geom *g, int kind, int nrhs, const double *dens, int npt
   FmmTree *tp = nullptr;
   BIE_TRY(get_tree(g, p, leaf, s, &tp));
   FmmTree &t = *tp;
-  PointLists local, *pl = &local;
-  const bool cached = pts == g->pint && npts == g->N;
-  if (cached && t.rd) {
-    pl = t.rd;
-  } else {
-    std::vector<double2> hp(npts);
-    BIE_HIP_CHECK(hipMemcpyAsync(hp.data(), pts, (size_t)npts * 16, hipMemcpyDeviceToHost, s));
-    BIE_HIP_CHECK(hipStreamSynchronize(s));
-    if (cached) {
-      t.rd = new PointLists();
-      pl = t.rd;
-    }
-    const int rc = build_point_lists(t, hp, *pl, s);
-    if (rc != BIE_OK) {
-      if (cached) {
-        t.rd->buf.release();
-        delete t.rd;
-        t.rd = nullptr;
-      }
-      return rc;
-    }
-  }
   const int M = t.M;
   const int Rmax = kind == 0 ? 8 : 4;
   const double ih_leaf = (double)(1 << t.L) / t.size;
+  const TreeWalk walk{t.L, t.level_off[2], t.level_off[3] - t.level_off[2], t.level_off[t.L],
+                      t.size, t.child, t.leaf_start, t.center};
   int rc = BIE_OK;
   for (int r0 = 0; r0 < nrhs && rc == BIE_OK; r0 += Rmax) {
     const int R = std::min(Rmax, nrhs - r0);
@@ -2112,21 +2064,16 @@ int fmm_eval_points(bie_geom *g, int kind, int nrhs, const double *dens, int npt
       constexpr int P = decltype(order)::value;
       upward_pass<P, double>(t, kind, nsets, ih_leaf, Q, Mexp, s);
       if (kind == 0)
-        hipLaunchKernelGGL(k_eval_lap<P>, dim3(npts, R), dim3(64), 0, s, M, t.nbox, t.size,
-                           reinterpret_cast<const double2 *>(pts), t.ox, t.oy, pl->box_ptr, pl->box,
-                           pl->run_ptr, pl->run, t.center, t.T_log, t.xs, Q, Mexp, npts, o);
+        hipLaunchKernelGGL(k_eval_lap<P>, dim3(npts, R), dim3(64), 0, s, M, t.nbox, walk,
+                           reinterpret_cast<const double2 *>(pts), t.ox, t.oy, t.T_log, t.xs, Q,
+                           Mexp, npts, o);
       else
-        hipLaunchKernelGGL(k_eval_stk<P>, dim3(npts, R), dim3(64), 0, s, M, t.nbox, t.size,
-                           reinterpret_cast<const double2 *>(pts), t.ox, t.oy, pl->box_ptr, pl->box,
-                           pl->run_ptr, pl->run, t.center, t.T_log, t.T_c, t.xs, Q, Mexp, npts,
-                           rigid ? 1 : 0, g->xc, g->yc, o);
+        hipLaunchKernelGGL(k_eval_stk<P>, dim3(npts, R), dim3(64), 0, s, M, t.nbox, walk,
+                           reinterpret_cast<const double2 *>(pts), t.ox, t.oy, t.T_log, t.T_c,
+                           t.xs, Q, Mexp, npts, rigid ? 1 : 0, g->xc, g->yc, o);
       BIE_HIP_CHECK(hipGetLastError());
       return BIE_OK;
     });
-  }
-  if (pl == &local) {
-    (void)hipStreamSynchronize(s);  // the lists are freed on return
-    local.buf.release();
   }
   return rc;
 }
@@ -2138,10 +2085,6 @@ void fmm_drop_tree(bie_geom *g, int precision, int order, int leaf) {
   if (it == g->fmm->trees.end() || !it->second) return;
   (void)hipDeviceSynchronize();  // no apply may still use it
   FmmTree *t = it->second;
-  if (t->rd) {
-    t->rd->buf.release();
-    delete t->rd;
-  }
   t->buf.release();
   t->work.release();
   delete t;
