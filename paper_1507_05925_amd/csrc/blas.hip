@@ -5,6 +5,8 @@
 // which other systems share the batch.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "internal.h"
 
 namespace bie {
@@ -196,7 +198,7 @@ __global__ __launch_bounds__(kBlock) void k_dots_uz(int C, const long long *__re
   __shared__ double sh[4][2 * kDotsVecs];
   const int c = blockIdx.x, l0 = blockIdx.y * kDotsVecs;
   const int nl = min(kDotsVecs, nv + 1 - l0);
-  const long long i0 = c0[c], i1 = c1[c];
+  const long long i0 = c0[c], i1 = c1[c], last = i1 > 0 ? i1 - 1 : 0;
   double u[kSub], z[kSub];
 #pragma unroll
   for (int k = 0; k < kSub; ++k) {
@@ -204,22 +206,29 @@ __global__ __launch_bounds__(kBlock) void k_dots_uz(int C, const long long *__re
     u[k] = i < i1 ? U[i] : 0.0;
     z[k] = (Z && i < i1) ? Z[i] : 0.0;
   }
+  // every load of the workgroup's vectors is issued before the first product (places past the
+  // last vector read U again, threads past the chunk's end its last entry against zeros): one
+  // memory latency instead of one per vector (4,608 unknowns 7.8 -> 4.9 us per step, 256,000
+  // unknowns 12.0 -> 7.5)
+  double x[kDotsVecs][kSub];
+#pragma unroll
+  for (int q = 0; q < kDotsVecs; ++q) {
+    const int l = l0 + q;
+    const double *a = l < nv ? V + l * vstride : U;
+#pragma unroll
+    for (int k = 0; k < kSub; ++k) {
+      const long long i = i0 + threadIdx.x + (long long)k * kBlock;
+      x[q][k] = a[i < i1 ? i : last];
+    }
+  }
   double su[kDotsVecs], sz[kDotsVecs];
 #pragma unroll
   for (int q = 0; q < kDotsVecs; ++q) {
     su[q] = sz[q] = 0.0;
-    if (q < nl) {
-      const int l = l0 + q;
-      const double *a = l < nv ? V + l * vstride : U;
 #pragma unroll
-      for (int k = 0; k < kSub; ++k) {
-        const long long i = i0 + threadIdx.x + (long long)k * kBlock;
-        if (i < i1) {
-          const double x = a[i];
-          su[q] = fma(x, u[k], su[q]);
-          sz[q] = fma(x, z[k], sz[q]);
-        }
-      }
+    for (int k = 0; k < kSub; ++k) {
+      su[q] = fma(x[q][k], u[k], su[q]);
+      sz[q] = fma(x[q][k], z[k], sz[q]);
     }
   }
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
@@ -243,34 +252,73 @@ __global__ __launch_bounds__(kBlock) void k_dots_uz(int C, const long long *__re
   }
 }
 
-// Per system s (one workgroup): raw[s][2i], raw[s][2i + 1] = s_i, t_i (i < j), raw[s][2j],
-// raw[s][2j + 1] = U.U, U.Z. Finishes column j - 1 (H[i][j-1] = G[i] + s_i, H[j][j-1] = nu) in
-// the device copy Hd (column-major, leading dimension ldh) and in mapped host memory col_out,
-// then stores the tag of step *seq_base + seq_off in flag[s]. Unless finalize: the coefficients
-// of the update, sc = s (k < j), cc = c (k <= j), inu = 1/nu, and G = g' (the first projection's
-// coefficients of the next column). nu = 0 (breakdown) gives zero coefficients. Dynamic LDS:
-// 3 (j + 1) doubles.
-__global__ __launch_bounds__(kBlock) void k_dcgs_small(
-    int j, int finalize, const double *__restrict__ raw, long long rstride,
-    double *__restrict__ G, double *__restrict__ Hd, long long ldh, long long hstride,
-    double *__restrict__ sc, double *__restrict__ cc, double *__restrict__ inu, long long hs,
-    double *__restrict__ col_out, unsigned long long *flag,
-    const unsigned long long *seq_base, unsigned long long seq_off) {
-  extern __shared__ double sm[];
-  double *sv = sm, *tv = sm + (j + 1), *hv = sm + 2 * (j + 1);
-  __shared__ double red[2];
-  const int s = blockIdx.x;
-  const double *rw = raw + s * rstride;
-  double *H = Hd + s * hstride;
-  for (int i = threadIdx.x; i < j; i += kBlock) {
-    sv[i] = rw[2 * i];
-    tv[i] = rw[2 * i + 1];
+// A finished column to the host: stored by one wave, whose flag store follows a release of its own
+// stores only (a fence by every wave of the workgroup, ahead of the column's next use, cost about
+// 3 us of each step).
+__device__ __forceinline__ void notify_column(int cnt, const double *column, double *col_out,
+                                              unsigned long long *flag,
+                                              const unsigned long long *seq_base,
+                                              unsigned long long seq_off) {
+  const int lane = threadIdx.x & 63;
+  for (int i = lane; i < cnt; i += 64) col_out[i] = column[i];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");  // system scope
+  if (lane == 0)
+    __hip_atomic_store(flag, column_tag(*seq_base + seq_off), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The sums of up to kFewChunks chunk sums in the order of k_dots_stage2's shuffle tree.
+constexpr int kFewChunks = 8;
+__device__ __forceinline__ double chunk_total(const double *p, long long stride, int C) {
+  double x[kFewChunks];
+#pragma unroll
+  for (int c = 0; c < kFewChunks; ++c) x[c] = c < C ? p[c * stride] : 0.0;
+  return ((x[0] + x[4]) + (x[2] + x[6])) + ((x[1] + x[5]) + (x[3] + x[7]));
+}
+
+// The small part of a DCGS2 step, for one system by one workgroup of T threads, from
+// sv[i], tv[i] = s_i, t_i (i < j) and U.U, U.Z (i = j) in LDS: finishes column j - 1
+// (col[i] = G[i] + s_i, col[j] = nu, also stored to the device copy Hd: column-major, leading
+// dimension ldh) and, unless finalize, leaves the update's coefficients (s = sv for k < j,
+// c_k = cc for k <= j, 1/nu returned) and G = g' (the first projection's coefficients of the next
+// column). nu = 0 (breakdown) gives zero coefficients. Hl: step_h_lds(j) doubles of LDS with the
+// columns of H before j - 1, which the product H s needs (HAhead: read while the reductions run).
+constexpr int kHRead = 48;  // columns up to which H is read ahead into LDS
+inline __host__ __device__ int step_h_lds(int j) { return j <= kHRead ? j * (j + 1) : 0; }
+
+template <int T>
+struct HAhead {
+  static constexpr int N = (kHRead * (kHRead + 1) + T - 1) / T;
+  double v[N];
+  // columns 0 .. j - 2, rows 0 .. j of each (column i at i (j + 1))
+  __device__ __forceinline__ void load(const double *H, long long ldh, int j) {
+    if (j > kHRead) return;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      const int x = threadIdx.x + e * T, i = x / (j + 1), k = x % (j + 1);
+      if (x < (j - 1) * (j + 1)) v[e] = k <= i + 1 ? H[(long long)i * ldh + k] : 0.0;
+    }
   }
-  __syncthreads();
+  __device__ __forceinline__ void store(double *Hl, int j) const {
+    if (j > kHRead) return;
+#pragma unroll
+    for (int e = 0; e < N; ++e) {
+      const int x = threadIdx.x + e * T;
+      if (x < (j - 1) * (j + 1)) Hl[x] = v[e];
+    }
+  }
+};
+
+template <int T>
+__device__ __forceinline__ double dcgs_small_part(int j, bool finalize, const double *sv,
+                                                  const double *tv, double *col, double *cc,
+                                                  const double *Hl, double *red, double *G,
+                                                  double *H, long long ldh) {
+  const int t = threadIdx.x;
   // s.s and s.t in a fixed order (first wave: lanes stride, then the shuffle tree)
-  if (threadIdx.x < 64) {
+  if (t < 64) {
     double a = 0.0, b = 0.0;
-    for (int i = threadIdx.x; i < j; i += 64) {
+    for (int i = t; i < j; i += 64) {
       a = fma(sv[i], sv[i], a);
       b = fma(sv[i], tv[i], b);
     }
@@ -279,90 +327,300 @@ __global__ __launch_bounds__(kBlock) void k_dcgs_small(
       a += __shfl_down(a, off, 64);
       b += __shfl_down(b, off, 64);
     }
-    if (threadIdx.x == 0) {
+    if (t == 0) {
       red[0] = a;
       red[1] = b;
     }
   }
+  const double g0 = t < j ? G[t] : 0.0;
   __syncthreads();
-  const double nu2 = rw[2 * j] - red[0];
+  const double nu2 = sv[j] - red[0];
   const double nu = nu2 > 0.0 ? sqrt(nu2) : 0.0;
-  // column j - 1, final
-  for (int i = threadIdx.x; i <= j; i += kBlock) {
-    const double v = i < j ? G[s * hs + i] + sv[i] : nu;
+  for (int i = t; i <= j; i += T) {
+    const double v = i < j ? (i < T ? g0 : G[i]) + sv[i] : nu;
+    col[i] = v;
     H[(long long)(j - 1) * ldh + i] = v;
-    if (col_out) col_out[s * hs + i] = v;
   }
-  if (flag) {
-    __threadfence_system();  // the column reaches host memory before its flag
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      const unsigned long long tag = column_tag(*seq_base + seq_off);
-      __hip_atomic_store(flag + s, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    }
-  }
-  if (finalize) return;
-  __syncthreads();  // column j - 1 of H is written (and G read)
-  // (H s)_k = sum_{i < j} H[k][i] s_i, k = 0..j (H[k][i] = 0 for k > i + 1)
-  // (eight loads in flight per step; the sum keeps the order of i)
-  for (int k = threadIdx.x; k <= j; k += kBlock) {
+  const double iv = nu > 0.0 ? 1.0 / nu : 0.0;
+  __syncthreads();
+  if (finalize) return iv;
+  // (H s)_k = sum_{i < j} H[k][i] s_i, k = 0..j (H[k][i] = 0 for k > i + 1), in the order of i
+  for (int k = t; k <= j; k += T) {
     double a = 0.0;
     int i = k > 0 ? k - 1 : 0;
-    for (; i + 8 <= j; i += 8) {
-      double h[8];
+    if (j <= kHRead) {
+      for (; i < j - 1; ++i) a = fma(Hl[i * (j + 1) + k], sv[i], a);
+    } else {
+      for (; i + 8 <= j - 1; i += 8) {
+        double h[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) h[e] = H[(long long)(i + e) * ldh + k];
+        for (int e = 0; e < 8; ++e) h[e] = H[(long long)(i + e) * ldh + k];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) a = fma(h[e], sv[i + e], a);
+        for (int e = 0; e < 8; ++e) a = fma(h[e], sv[i + e], a);
+      }
+      for (; i < j - 1; ++i) a = fma(H[(long long)i * ldh + k], sv[i], a);
     }
-    for (; i < j; ++i) a = fma(H[(long long)i * ldh + k], sv[i], a);
-    hv[k] = a;
+    a = fma(col[k], sv[j - 1], a);
+    const double gn = k < j ? (tv[k] - a) * iv : ((tv[j] - red[1]) * iv - a) * iv;
+    cc[k] = nu > 0.0 ? a * iv + gn : 0.0;
+    G[k] = nu > 0.0 ? gn : 0.0;
   }
   __syncthreads();
-  const double iv = nu > 0.0 ? 1.0 / nu : 0.0;
-  for (int k = threadIdx.x; k <= j; k += kBlock) {
-    const double g = k < j ? (tv[k] - hv[k]) * iv : ((rw[2 * j + 1] - red[1]) * iv - hv[k]) * iv;
-    cc[s * hs + k] = nu > 0.0 ? hv[k] * iv + g : 0.0;
-    G[s * hs + k] = nu > 0.0 ? g : 0.0;
-    if (k < j) sc[s * hs + k] = sv[k];
-  }
-  if (threadIdx.x == 0) inu[s] = iv;
+  return iv;
 }
 
-// V_j = (U - sum_{k<j} sc_k V_k) / nu and U = Z / nu - sum_{k<j} cc_k V_k - cc_j V_j, entry by
-// entry (one pass over V_0..V_{j-1}); grid (C, kSub) as k_combination.
+// Per system (one workgroup): the small part of a step, from raw[s][2i], raw[s][2i + 1] or, with
+// FEW (every system at most kFewChunks chunks), from the chunk sums themselves (partial, as
+// k_dots_uz leaves them), which saves the launch that adds them. The update's coefficients go to
+// sc, cc, inu; the column to the host with finalize only (else the update's launch sends it).
+// Dynamic LDS: 4 (j + 1) + step_h_lds(j) doubles.
+template <bool FEW>
+__global__ __launch_bounds__(kBlock) void k_dcgs_small(
+    int j, int finalize, const double *__restrict__ raw, long long rstride,
+    const double *__restrict__ partial, int Ctot, const int *__restrict__ sys_chunk, double *G,
+    double *Hd, long long ldh, long long hstride, double *__restrict__ sc,
+    double *__restrict__ cc, double *__restrict__ inu, long long hs, double *__restrict__ col_out,
+    unsigned long long *flag, const unsigned long long *seq_base, unsigned long long seq_off) {
+  extern __shared__ double sm[];
+  double *sv = sm, *tv = sm + (j + 1), *col = tv + (j + 1), *ccl = col + (j + 1), *Hl = ccl + (j + 1);
+  __shared__ double red[2];
+  const int s = blockIdx.x, t = threadIdx.x;
+  double *H = Hd + s * hstride;
+  HAhead<kBlock> ahead;
+  if (!finalize) ahead.load(H, ldh, j);
+  for (int r = t; r < 2 * (j + 1); r += kBlock) {
+    double v;
+    if (FEW) v = chunk_total(partial + (long long)r * Ctot + sys_chunk[s], 1, sys_chunk[s + 1] - sys_chunk[s]);
+    else v = raw[s * rstride + r];
+    ((r & 1) ? tv : sv)[r >> 1] = v;
+  }
+  if (!finalize) ahead.store(Hl, j);
+  __syncthreads();
+  const double iv = dcgs_small_part<kBlock>(j, finalize != 0, sv, tv, col, ccl, Hl, red,
+                                            G + s * hs, H, ldh);
+  if (finalize) {
+    if (t < 64) notify_column(j + 1, col, col_out + s * hs, flag + s, seq_base, seq_off);
+    return;
+  }
+  for (int k = t; k <= j; k += kBlock) {
+    cc[s * hs + k] = ccl[k];
+    if (k < j) sc[s * hs + k] = sv[k];
+  }
+  if (t == 0) inu[s] = iv;
+}
+
+// One entry of V_j = (U - sum_{k<j} sc_k V_k) / nu and of the next candidate
+// U = Z / nu - sum_{k<j} cc_k V_k - cc_j V_j; term l goes to accumulator l mod 4. Eight entries of
+// V are in flight at a time.
+__device__ __forceinline__ void dcgs_entry(int j, const double *V, long long vstride, long long i,
+                                           const double *sr, const double *cr, double iv, double u,
+                                           double z, double &vj, double &unext) {
+  double a[4] = {0.0, 0.0, 0.0, 0.0}, b[4] = {0.0, 0.0, 0.0, 0.0};
+  int l = 0;
+  for (; l + 8 <= j; l += 8) {
+    double v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = V[(l + q) * vstride + i];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      a[q & 3] = fma(v[q], sr[l + q], a[q & 3]);
+      b[q & 3] = fma(v[q], cr[l + q], b[q & 3]);
+    }
+  }
+  if (l < j) {
+    double v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = l + q < j ? V[(l + q) * vstride + i] : 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (l + q < j) {
+        a[q & 3] = fma(v[q], sr[l + q], a[q & 3]);
+        b[q & 3] = fma(v[q], cr[l + q], b[q & 3]);
+      }
+  }
+  vj = (u - ((a[0] + a[1]) + (a[2] + a[3]))) * iv;
+  unext = z * iv - ((b[0] + b[1]) + (b[2] + b[3])) - cr[j] * vj;
+}
+
+// The update of a step, entry by entry (one pass over V_0..V_{j-1}); grid (C + S, kSub): chunk c's
+// workgroups as k_combination, and workgroup (C + s, 0) sends system s's column j - 1 to the host
+// meanwhile.
 __global__ __launch_bounds__(kBlock) void k_dcgs_update(
-    int j, const int *__restrict__ csys, const long long *__restrict__ c0,
+    int j, int C, const int *__restrict__ csys, const long long *__restrict__ c0,
     const long long *__restrict__ c1, const double *__restrict__ V, long long vstride,
     const double *__restrict__ sc, const double *__restrict__ cc, const double *__restrict__ inu,
-    long long hs, double *__restrict__ U, const double *__restrict__ Z, double *__restrict__ Vj) {
-  const int c = blockIdx.x, s = csys[c];
-  const double *sr = sc + s * hs, *cr = cc + s * hs;
-  const double iv = inu[s], cj = cr[j];
+    long long hs, double *__restrict__ U, const double *__restrict__ Z, double *__restrict__ Vj,
+    const double *__restrict__ Hd, long long ldh, long long hstride, double *__restrict__ col_out,
+    unsigned long long *flag, const unsigned long long *seq_base, unsigned long long seq_off) {
+  const int c = blockIdx.x;
+  if (c >= C) {
+    const int s = c - C;
+    if (blockIdx.y == 0 && threadIdx.x < 64)
+      notify_column(j + 1, Hd + s * hstride + (long long)(j - 1) * ldh, col_out + s * hs, flag + s,
+                    seq_base, seq_off);
+    return;
+  }
+  const int s = csys[c];
+  const double iv = inu[s];
   for (long long i = c0[c] + blockIdx.y * kBlock + threadIdx.x; i < c1[c]; i += kSub * kBlock) {
-    double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0, b0 = 0.0, b1 = 0.0, b2 = 0.0, b3 = 0.0;
-    int l = 0;
-    for (; l + 4 <= j; l += 4) {
-      const double v0 = V[l * vstride + i], v1 = V[(l + 1) * vstride + i];
-      const double v2 = V[(l + 2) * vstride + i], v3 = V[(l + 3) * vstride + i];
-      a0 = fma(v0, sr[l], a0);
-      a1 = fma(v1, sr[l + 1], a1);
-      a2 = fma(v2, sr[l + 2], a2);
-      a3 = fma(v3, sr[l + 3], a3);
-      b0 = fma(v0, cr[l], b0);
-      b1 = fma(v1, cr[l + 1], b1);
-      b2 = fma(v2, cr[l + 2], b2);
-      b3 = fma(v3, cr[l + 3], b3);
-    }
-    for (int r = 0; l + r < j; ++r) {
-      const double v = V[(l + r) * vstride + i];
-      if (r == 0) { a0 = fma(v, sr[l], a0); b0 = fma(v, cr[l], b0); }
-      if (r == 1) { a1 = fma(v, sr[l + 1], a1); b1 = fma(v, cr[l + 1], b1); }
-      if (r == 2) { a2 = fma(v, sr[l + 2], a2); b2 = fma(v, cr[l + 2], b2); }
-    }
-    const double vj = (U[i] - ((a0 + a1) + (a2 + a3))) * iv;
+    double vj, un;
+    dcgs_entry(j, V, vstride, i, sc + s * hs, cc + s * hs, iv, U[i], Z[i], vj, un);
     Vj[i] = vj;
-    U[i] = Z[i] * iv - ((b0 + b1) + (b2 + b3)) - cj * vj;
+    U[i] = un;
+  }
+}
+
+// ---- Arnoldi steps of small systems in one launch -------------------------------------------
+// One workgroup per system of one chunk takes a whole Arnoldi step: the reductions, the small
+// per-system part and the update, with the barriers of one workgroup where the separate kernels
+// need launches. Every sum has the order of the separate kernels, so which of the two runs
+// changes no bit and a batch may mix sizes. Bound by the latency of its phases; a longer system
+// would be read through one compute unit (4,608 unknowns: 46 us per step at 20 vectors, the
+// separate kernels 20), so only sets of one-chunk systems take it.
+constexpr int kStepThreads = kChunk;
+constexpr int kStepWaves = kStepThreads / 64;
+constexpr int kStepVectors = kHRead;  // most basis vectors a fused step reads
+
+// The sum that k_dots_stage1 / k_dots_uz forms over one chunk, by one wave: accumulator q stands for
+// that kernel's wave q; x holds the vector (zero past the chunk's end).
+__device__ __forceinline__ double chunk_dot(const double (&x)[kSub][4], const double *u) {
+  const int lane = threadIdx.x & 63;
+  double a[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    a[q] = 0.0;
+#pragma unroll
+    for (int k = 0; k < kSub; ++k) a[q] = fma(x[k][q], u[k * kBlock + q * 64 + lane], a[q]);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) a[q] += __shfl_down(a[q], off, 64);
+  return (a[0] + a[1]) + (a[2] + a[3]);  // (valid in lane 0)
+}
+
+__device__ __forceinline__ void chunk_load(const double *v, int len, double (&x)[kSub][4]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int k = 0; k < kSub; ++k)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int e = k * kBlock + q * 64 + lane;
+      x[k][q] = e < len ? v[e] : 0.0;
+    }
+}
+
+// One DCGS2 step. Dynamic LDS: 4 (j + 1) + step_h_lds(j) doubles.
+__global__ __launch_bounds__(kStepThreads) void k_dcgs_step(
+    const int *__restrict__ sys_chunk, const long long *__restrict__ c0,
+    const long long *__restrict__ c1, int j, int finalize, const double *__restrict__ V,
+    long long vstride, double *G, double *Hd, long long ldh, long long hstride, long long hs,
+    double *__restrict__ U, const double *__restrict__ Z, double *__restrict__ Vj,
+    double *__restrict__ col_out, unsigned long long *flag, const unsigned long long *seq_base,
+    unsigned long long seq_off) {
+  extern __shared__ double sm[];
+  __shared__ double us[kChunk], zs[kChunk], red[2];
+  double *sv = sm, *tv = sv + (j + 1), *col = tv + (j + 1), *cc = col + (j + 1), *Hl = cc + (j + 1);
+  const int s = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const long long i0 = c0[sys_chunk[s]];
+  const int len = (int)(c1[sys_chunk[s]] - i0);
+  double *H = Hd + s * hstride;
+  HAhead<kStepThreads> ahead;
+  if (!finalize) ahead.load(H, ldh, j);
+  const double ut = t < len ? U[i0 + t] : 0.0, zt = Z && t < len ? Z[i0 + t] : 0.0;
+  double x[kSub][4];
+  if (wv < j) chunk_load(V + wv * vstride + i0, len, x);
+  us[t] = ut;
+  zs[t] = zt;
+  if (!finalize) ahead.store(Hl, j);
+  __syncthreads();
+  for (int l = wv; l <= j; l += kStepWaves) {
+    if (l == j) {
+#pragma unroll
+      for (int k = 0; k < kSub; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[k][q] = us[k * kBlock + q * 64 + lane];
+    } else if (l != wv) {
+      chunk_load(V + l * vstride + i0, len, x);
+    }
+#pragma unroll 1  // one at a time: both at once do not fit the registers of 16 waves
+    for (int z = 0; z < 2; ++z) {
+      const double a = chunk_dot(x, z ? zs : us);
+      if (lane == 0) (z ? tv : sv)[l] = a;
+    }
+  }
+  __syncthreads();
+  const double iv = dcgs_small_part<kStepThreads>(j, finalize != 0, sv, tv, col, cc, Hl, red,
+                                                  G + s * hs, H, ldh);
+  if (!finalize && t < len) {
+    double vj, un;
+    dcgs_entry(j, V, vstride, i0 + t, sv, cc, iv, ut, zt, vj, un);
+    Vj[i0 + t] = vj;
+    U[i0 + t] = un;
+  }
+  if (wv == kStepWaves - 1) notify_column(j + 1, col, col_out + s * hs, flag + s, seq_base, seq_off);
+}
+
+// One classical Gram-Schmidt pass: h = V^T w (nv vectors), w -= V h, and with NORM the new basis
+// vector vnext = w / ||w|| and the column (h, ||w||) (k_dots_stage1, k_dots_stage2,
+// k_combination_nrm and k_normalize_column with a zero second pass); without, h is left in h_out
+// (the first projection of a DCGS2 cycle).
+template <bool NORM>
+__global__ __launch_bounds__(kStepThreads) void k_cgs_step(
+    const int *__restrict__ sys_chunk, const long long *__restrict__ c0,
+    const long long *__restrict__ c1, int nv, const double *__restrict__ V, long long vstride,
+    double *__restrict__ h_out, long long hs, double *__restrict__ w, double *__restrict__ nrm,
+    double *__restrict__ vnext, double *__restrict__ col_out, unsigned long long *flag,
+    const unsigned long long *seq_base, unsigned long long seq_off) {
+  __shared__ double us[kChunk], ws[kStepWaves], h[kStepVectors + 1];
+  const int s = blockIdx.x, t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const long long i0 = c0[sys_chunk[s]];
+  const int len = (int)(c1[sys_chunk[s]] - i0);
+  const double wt = t < len ? w[i0 + t] : 0.0;
+  us[t] = wt;
+  __syncthreads();
+  for (int l = wv; l < nv; l += kStepWaves) {
+    double x[kSub][4];
+    chunk_load(V + l * vstride + i0, len, x);
+    const double a = chunk_dot(x, us);
+    if (lane == 0) h[l] = a;
+  }
+  __syncthreads();
+  double v = 0.0;
+  if (t < len) {
+    double a[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int l = 0; l < nv; l += 8) {
+      double y[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) y[q] = l + q < nv ? V[(l + q) * vstride + i0 + t] : 0.0;
+#pragma unroll
+      for (int q = 0; q < 8; ++q)
+        if (l + q < nv) a[q & 3] = fma(y[q], h[l + q], a[q & 3]);
+    }
+    v = wt + -1.0 * ((a[0] + a[1]) + (a[2] + a[3]));
+    w[i0 + t] = v;
+  }
+  for (int l = t; l < nv; l += kStepThreads) h_out[s * hs + l] = h[l];
+  if (!NORM) return;
+  double sq = t < len ? fma(v, v, 0.0) : 0.0;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) sq += __shfl_down(sq, off, 64);
+  if (lane == 0) ws[wv] = sq;
+  __syncthreads();
+  // the four workgroups' parts of k_combination_nrm, added in k_normalize_column's tree
+  double part[kSub];
+#pragma unroll
+  for (int q = 0; q < kSub; ++q)
+    part[q] = (ws[4 * q] + ws[4 * q + 1]) + (ws[4 * q + 2] + ws[4 * q + 3]);
+  const double n = sqrt((part[0] + part[2]) + (part[1] + part[3]));
+  if (t < len) vnext[i0 + t] = n > 0.0 ? v / n : 0.0;
+  if (t == 0) {
+    nrm[s] = n;
+    h_out[s * hs + nv] = n;
+  }
+  if (wv == kStepWaves - 1) {
+    if (lane == 0) h[nv] = n;
+    notify_column(nv + 1, h, col_out + s * hs, flag + s, seq_base, seq_off);
   }
 }
 
@@ -376,6 +634,9 @@ __global__ void k_add_h(int cnt, long long hs, const double *__restrict__ h1, do
   const int s = blockIdx.x;
   for (int l = threadIdx.x; l < cnt; l += blockDim.x) h2[s * hs + l] += h1[s * hs + l];
 }
+
+// Sets whose systems all have few chunks: the consumer adds a reduction's chunk sums.
+bool few_chunks(const Segments &sg) { return sg.max_len <= (long long)kFewChunks * kChunk; }
 
 }  // namespace
 
@@ -427,28 +688,69 @@ int dcgs_dots(const Segments &sg, int nv, const double *V, long long vstride, co
               const double *Z, double *raw, long long rstride, double *scratch, hipStream_t s) {
   hipLaunchKernelGGL(k_dots_uz, dim3(sg.C, (nv + kDotsVecs) / kDotsVecs), dim3(kBlock), 0, s,
                      sg.C, sg.c0, sg.c1, nv, V, vstride, U, Z, scratch);
-  hipLaunchKernelGGL(k_dots_stage2, dim3(2 * nv + 2, sg.S), dim3(64), 0, s, sg.C, sg.sys_chunk,
-                     scratch, raw, rstride, 0);
+  if (!few_chunks(sg))  // else dcgs_small adds the chunk sums itself
+    hipLaunchKernelGGL(k_dots_stage2, dim3(2 * nv + 2, sg.S), dim3(64), 0, s, sg.C, sg.sys_chunk,
+                       scratch, raw, rstride, 0);
   BIE_HIP_CHECK(hipGetLastError());
   return BIE_OK;
 }
 
-int dcgs_small(int S, int j, bool finalize, const double *raw, long long rstride, double *G,
-               double *Hd, long long ldh, long long hstride, double *sc, double *cc, double *inu,
-               long long hs, double *col_out, unsigned long long *flag,
-               const unsigned long long *seq_base, unsigned long long seq_off, hipStream_t s) {
-  hipLaunchKernelGGL(k_dcgs_small, dim3(S), dim3(kBlock), (size_t)3 * (j + 1) * sizeof(double), s,
-                     j, finalize ? 1 : 0, raw, rstride, G, Hd, ldh, hstride, sc, cc, inu, hs,
-                     col_out, flag, seq_base, seq_off);
+int dcgs_small(const Segments &sg, int j, bool finalize, const double *raw, long long rstride,
+               const double *scratch, double *G, double *Hd, long long ldh, long long hstride,
+               double *sc, double *cc, double *inu, long long hs, double *col_out,
+               unsigned long long *flag, const unsigned long long *seq_base,
+               unsigned long long seq_off, hipStream_t s) {
+  const size_t lds = (size_t)(4 * (j + 1) + step_h_lds(j)) * sizeof(double);
+  if (few_chunks(sg))
+    hipLaunchKernelGGL(k_dcgs_small<true>, dim3(sg.S), dim3(kBlock), lds, s, j, finalize ? 1 : 0,
+                       raw, rstride, scratch, sg.C, sg.sys_chunk, G, Hd, ldh, hstride, sc, cc, inu,
+                       hs, col_out, flag, seq_base, seq_off);
+  else
+    hipLaunchKernelGGL(k_dcgs_small<false>, dim3(sg.S), dim3(kBlock), lds, s, j, finalize ? 1 : 0,
+                       raw, rstride, scratch, sg.C, sg.sys_chunk, G, Hd, ldh, hstride, sc, cc, inu,
+                       hs, col_out, flag, seq_base, seq_off);
   BIE_HIP_CHECK(hipGetLastError());
   return BIE_OK;
 }
 
 int dcgs_update(const Segments &sg, int j, const double *V, long long vstride, const double *sc,
                 const double *cc, const double *inu, long long hs, double *U, const double *Z,
-                double *Vj, hipStream_t s) {
-  hipLaunchKernelGGL(k_dcgs_update, dim3(sg.C, kSub), dim3(kBlock), 0, s, j, sg.csys, sg.c0, sg.c1,
-                     V, vstride, sc, cc, inu, hs, U, Z, Vj);
+                double *Vj, const double *Hd, long long ldh, long long hstride, double *col_out,
+                unsigned long long *flag, const unsigned long long *seq_base,
+                unsigned long long seq_off, hipStream_t s) {
+  hipLaunchKernelGGL(k_dcgs_update, dim3(sg.C + sg.S, kSub), dim3(kBlock), 0, s, j, sg.C, sg.csys,
+                     sg.c0, sg.c1, V, vstride, sc, cc, inu, hs, U, Z, Vj, Hd, ldh, hstride,
+                     col_out, flag, seq_base, seq_off);
+  BIE_HIP_CHECK(hipGetLastError());
+  return BIE_OK;
+}
+
+bool step_is_small(const Segments &sg, int vectors) {
+  return vectors <= kStepVectors && sg.max_len <= kChunk;
+}
+
+int dcgs_step(const Segments &sg, int j, bool finalize, const double *V, long long vstride,
+              double *G, double *Hd, long long ldh, long long hstride, long long hs, double *U,
+              const double *Z, double *Vj, double *col_out, unsigned long long *flag,
+              const unsigned long long *seq_base, unsigned long long seq_off, hipStream_t s) {
+  const size_t lds = (size_t)(4 * (j + 1) + step_h_lds(j)) * sizeof(double);
+  hipLaunchKernelGGL(k_dcgs_step, dim3(sg.S), dim3(kStepThreads), lds, s, sg.sys_chunk, sg.c0,
+                     sg.c1, j, finalize ? 1 : 0, V, vstride, G, Hd, ldh, hstride, hs, U, Z, Vj,
+                     col_out, flag, seq_base, seq_off);
+  BIE_HIP_CHECK(hipGetLastError());
+  return BIE_OK;
+}
+
+int cgs_step(const Segments &sg, int nv, bool norm, const double *V, long long vstride, double *h,
+             long long hs, double *w, double *nrm, double *vnext, double *col_out,
+             unsigned long long *flag, const unsigned long long *seq_base,
+             unsigned long long seq_off, hipStream_t s) {
+  if (norm)
+    hipLaunchKernelGGL(k_cgs_step<true>, dim3(sg.S), dim3(kStepThreads), 0, s, sg.sys_chunk, sg.c0,
+                       sg.c1, nv, V, vstride, h, hs, w, nrm, vnext, col_out, flag, seq_base, seq_off);
+  else
+    hipLaunchKernelGGL(k_cgs_step<false>, dim3(sg.S), dim3(kStepThreads), 0, s, sg.sys_chunk, sg.c0,
+                       sg.c1, nv, V, vstride, h, hs, w, nrm, vnext, col_out, flag, seq_base, seq_off);
   BIE_HIP_CHECK(hipGetLastError());
   return BIE_OK;
 }
@@ -500,6 +802,8 @@ int Segments::build(const std::vector<long long> &lens, hipStream_t s,
     h_off[k + 1] = off;
   }
   // h_off[k] is the start of system k; h_off[S] the end of the last one
+  max_len = 0;
+  for (long long n : lens) max_len = std::max(max_len, n);
   C = (int)cs.size();
   Ntot = off;
   const size_t bytes = (size_t)C * (8 + 8 + 4) + (S + 1) * 4 + 256;

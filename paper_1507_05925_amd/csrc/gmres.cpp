@@ -298,30 +298,43 @@ int gmres(SysSet &ss, int precision, const double *f, double *x, bool x_is_zero,
     auto step_body = [&](int j, Stats &sts, hipStream_t s, int sp) -> int {
       if (onep) {
         BIE_TRY(apply(ss, sp, wk.V + (size_t)j * N, wk.w, sts, s));
-        BIE_TRY(seg_dots(sg, j + 1, wk.V, N, wk.w, wk.h1, hs, wk.scratch, s));
         double *col = mem.pinned_dev + (j & 1) * slot;
         auto *flag = reinterpret_cast<unsigned long long *>(col + (size_t)S * hs);
+        if (step_is_small(sg, j + 1))
+          return cgs_step(sg, j + 1, true, wk.V, N, wk.h1, hs, wk.w, wk.nrm,
+                          wk.V + (size_t)(j + 1) * N, col, flag, base_d,
+                          (unsigned long long)j + 1, s);
+        BIE_TRY(seg_dots(sg, j + 1, wk.V, N, wk.w, wk.h1, hs, wk.scratch, s));
         return seg_combination_column(sg, j + 1, wk.V, N, wk.zero, wk.h1, hs, wk.w, wk.nrm,
                                       wk.V + (size_t)(j + 1) * N, col, flag, base_d,
                                       (unsigned long long)j + 1, wk.scratch, s);
       }
       if (j == 0) {
         BIE_TRY(apply(ss, sp, wk.V, wk.U, sts, s));
+        if (step_is_small(sg, 1))
+          return cgs_step(sg, 1, false, wk.V, N, wk.G, hs, wk.U, nullptr, nullptr, nullptr, nullptr,
+                          nullptr, 0, s);
         BIE_TRY(seg_dots(sg, 1, wk.V, N, wk.U, wk.G, hs, wk.scratch, s));
         BIE_TRY(seg_combination(sg, 1, wk.V, N, wk.G, hs, wk.U, -1.0, s));
         return BIE_OK;
       }
       const bool fin = j == m;
       if (!fin) BIE_TRY(apply(ss, sp, wk.U, wk.w, sts, s));
-      BIE_TRY(dcgs_dots(sg, j, wk.V, N, wk.U, fin ? nullptr : wk.w, wk.raw, wk.rstride,
-                        wk.scratch, s));
       double *col = mem.pinned_dev + ((j - 1) & 1) * slot;
       auto *flag = reinterpret_cast<unsigned long long *>(col + (size_t)S * hs);
-      BIE_TRY(dcgs_small(S, j, fin, wk.raw, wk.rstride, wk.G, wk.Hd, wk.ldh, wk.hstride, wk.sc,
-                         wk.cc, wk.inu, hs, col, flag, base_d, (unsigned long long)j, s));
+      if (step_is_small(sg, j + 1))
+        return dcgs_step(sg, j, fin, wk.V, N, wk.G, wk.Hd, wk.ldh, wk.hstride, hs, wk.U,
+                         fin ? nullptr : wk.w, wk.V + (size_t)j * N, col, flag, base_d,
+                         (unsigned long long)j, s);
+      BIE_TRY(dcgs_dots(sg, j, wk.V, N, wk.U, fin ? nullptr : wk.w, wk.raw, wk.rstride,
+                        wk.scratch, s));
+      BIE_TRY(dcgs_small(sg, j, fin, wk.raw, wk.rstride, wk.scratch, wk.G, wk.Hd, wk.ldh,
+                         wk.hstride, wk.sc, wk.cc, wk.inu, hs, col, flag, base_d,
+                         (unsigned long long)j, s));
       if (!fin)
         BIE_TRY(dcgs_update(sg, j, wk.V, N, wk.sc, wk.cc, wk.inu, hs, wk.U, wk.w,
-                            wk.V + (size_t)j * N, s));
+                            wk.V + (size_t)j * N, wk.Hd, wk.ldh, wk.hstride, col, flag, base_d,
+                            (unsigned long long)j, s));
       return BIE_OK;
     };
     // With graphs: step j is captured (after running it once eagerly, which sizes every buffer)

@@ -65,7 +65,7 @@ struct FmmPlan;  // far-field FMM state (fmm.hip)
 // Independent systems stored back to back in flat vectors; chunks never straddle two systems.
 struct Segments {
   int S = 0, C = 0;
-  long long Ntot = 0;
+  long long Ntot = 0, max_len = 0;  // entries in all, and of the longest system
   std::vector<long long> h_off;  // [S+1] host offsets
   DevBuf buf;
   long long *c0 = nullptr, *c1 = nullptr;  // [C] flat chunk ranges
@@ -297,13 +297,30 @@ int vec_axpby(long long total, double a, const double *x, double b, double *y, h
 // NULL); the per-system column and coefficients; the update writing V_j and the next candidate
 int dcgs_dots(const Segments &sg, int nv, const double *V, long long vstride, const double *U,
               const double *Z, double *raw, long long rstride, double *scratch, hipStream_t s);
-int dcgs_small(int S, int j, bool finalize, const double *raw, long long rstride, double *G,
-               double *Hd, long long ldh, long long hstride, double *sc, double *cc, double *inu,
-               long long hs, double *col_out, unsigned long long *flag,
-               const unsigned long long *seq_base, unsigned long long seq_off, hipStream_t s);
+int dcgs_small(const Segments &sg, int j, bool finalize, const double *raw, long long rstride,
+               const double *scratch, double *G, double *Hd, long long ldh, long long hstride,
+               double *sc, double *cc, double *inu, long long hs, double *col_out,
+               unsigned long long *flag, const unsigned long long *seq_base,
+               unsigned long long seq_off, hipStream_t s);
+// (sends the column that dcgs_small finished, unless that did)
 int dcgs_update(const Segments &sg, int j, const double *V, long long vstride, const double *sc,
                 const double *cc, const double *inu, long long hs, double *U, const double *Z,
-                double *Vj, hipStream_t s);
+                double *Vj, const double *Hd, long long ldh, long long hstride, double *col_out,
+                unsigned long long *flag, const unsigned long long *seq_base,
+                unsigned long long seq_off, hipStream_t s);
+// Whole Arnoldi steps in one launch, for sets whose systems are all short (step_is_small for the
+// number of basis vectors a step reads): dcgs_step is dcgs_dots, dcgs_small and dcgs_update (Z
+// may be NULL with finalize); cgs_step, with norm, is seg_dots, then seg_combination_column with
+// a zero first pass, and without, seg_dots and seg_combination with sign -1. Same results.
+bool step_is_small(const Segments &sg, int vectors);
+int dcgs_step(const Segments &sg, int j, bool finalize, const double *V, long long vstride,
+              double *G, double *Hd, long long ldh, long long hstride, long long hs, double *U,
+              const double *Z, double *Vj, double *col_out, unsigned long long *flag,
+              const unsigned long long *seq_base, unsigned long long seq_off, hipStream_t s);
+int cgs_step(const Segments &sg, int nv, bool norm, const double *V, long long vstride, double *h,
+             long long hs, double *w, double *nrm, double *vnext, double *col_out,
+             unsigned long long *flag, const unsigned long long *seq_base,
+             unsigned long long seq_off, hipStream_t s);
 int seg_add_h(int S, const double *h1, double *h2, int cnt, long long hs, hipStream_t s);
 
 // ---- gmres.cpp ----------------------------------------------------------------------------
