@@ -136,7 +136,7 @@ int bie_batch_solve(bie_batch *b, int nitems, const bie_batch_item *items, const
   for (int i = 0; i < nitems; ++i) {
     bie_geom *g = items[i].g;
     mitems[i] = {g, items[i].kind, items[i].nrhs, item_off[i],
-                 method_is_fmm(o.method, g->M), effective_order(o, items[i].kind), g->fmm_leaf};
+                 method_is_fmm(o.method, g->M), effective_order(o, items[i].kind), g->fmm_leaf, true};
     first_sys[i + 1] = first_sys[i] + items[i].nrhs;
   }
   ss.group_ptr = first_sys;  // items: a relaxed mixed solve picks precisions per item
@@ -169,7 +169,7 @@ int bie_batch_solve(bie_batch *b, int nitems, const bie_batch_item *items, const
   }
   SysSet *ssp = &ss;
   MultiPlan **plan = &b->plan;
-  ss.apply = [ssp, plan, mitems, first_sys, Ntot, pc_items, pc_lds, pc_blocks, pc_macs, ptmp,
+  ss.apply = [ssp, plan, mitems, first_sys, pc_items, pc_lds, pc_blocks, pc_macs, ptmp,
               nitems](int precision, const double *in, double *out, hipStream_t st) {
     if (pc_items) {
       BIE_TRY(pc_apply_batch(nitems, pc_items, pc_lds, pc_blocks, pc_macs, in, ptmp, st));
@@ -184,8 +184,8 @@ int bie_batch_solve(bie_batch *b, int nitems, const bie_batch_item *items, const
         act[i] = a;
       }
     if (precision == kPrecPerGroup)
-      return multi_apply(*plan, mitems, act, BIE_FP64, in, out, Ntot, st, &ssp->group_f32);
-    return multi_apply(*plan, mitems, act, precision, in, out, Ntot, st);
+      return multi_apply(*plan, mitems, act, BIE_FP64, in, out, st, &ssp->group_f32);
+    return multi_apply(*plan, mitems, act, precision, in, out, st);
   };
   std::vector<double> rel;
   bie_info inf{};

@@ -27,7 +27,9 @@ template <int KIND, int R>
 __global__ __launch_bounds__(kBlock, sweep_occupancy(PairShape<KIND, R>::V)) void k_pair_sweep(
     int M, int per, PairSources src, double factor, double *__restrict__ partial) {
   __shared__ double buf[kSweepLds<KIND, R>];
-  pair_sweep_tile<KIND, R>(M, per, blockIdx.x, blockIdx.y, src, factor, partial, buf);
+  const int k0 = blockIdx.y * per;
+  pair_sweep_tile<KIND, R>(blockIdx.x * kSweepTile, M, k0, min(k0 + per, M), src, factor,
+                           partial + (size_t)blockIdx.y * R * src.len, buf);
 }
 
 // The rest of a split apply: grid (N bodies x target tiles of kBlock, R). A workgroup forms its

@@ -106,7 +106,9 @@ __global__ __launch_bounds__(kBlock, sweep_occupancy(PairShape<KIND, R>::V)) voi
     moments<KIND == kPairStkDl>(ma, blockIdx.x % ma.N, blockIdx.x / ma.N, buf);
     return;
   }
-  pair_sweep_tile<KIND, R>(M, per, w % tiles, w / tiles, src, factor, partial, buf);
+  const int sp = w / tiles, k0 = sp * per;
+  pair_sweep_tile<KIND, R>((w % tiles) * kSweepTile, M, k0, min(k0 + per, M), src, factor,
+                           partial + (size_t)sp * R * src.len, buf);
 }
 
 // out = alpha (1/2 mu + diagonal limit + sum of the split partials + completion), one lane per

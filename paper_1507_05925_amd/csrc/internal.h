@@ -394,13 +394,17 @@ struct MultiItem {
   long long io;  // start of the item's rhs block in the flat vectors (64-byte aligned)
   bool fmm;      // applied by the single-geometry FMM path
   int fmm_order = 40, fmm_leaf = 64;  // its expansion order and leaf population (FMM items)
+  // whether its BIE_MIXED applies may take the float32 matrix-core sweep, a choice that depends on
+  // nrhs (not for items whose nrhs depends on other callers)
+  bool f32_sweep = false;
 };
 struct MultiPlan;
-// item_f32 (nullptr: every item uses precision): per item, 1 = float32 far field (BIE_MIXED),
-// 0 = float64; at most kMaxPrecGroups items.
+// item_f32 (nullptr: every item uses precision): per item, 1 = BIE_MIXED, 0 = BIE_FP64, at most
+// kMaxPrecGroups items. Direct items without f32_sweep or with few right-hand sides are float64
+// either way.
 int multi_apply(MultiPlan *&plan, const std::vector<MultiItem> &items,
                 const std::vector<char> &active, int precision, const double *in, double *out,
-                long long Ntot, hipStream_t s, const std::vector<char> *item_f32 = nullptr);
+                hipStream_t s, const std::vector<char> *item_f32 = nullptr);
 void multi_destroy(MultiPlan *p);
 inline long long align8(long long v) { return (v + 7) / 8 * 8; }
 

@@ -1,14 +1,19 @@
-// One operator apply for many geometries at once (batched solves and the server): the far-field
-// sweeps, the per-body epilogues and the strength packing of every item run as three launches
-// per kernel class instead of three per geometry. Work is described by task lists built on the
-// host whenever the set of active items changes:
-//   far task      = (item, rhs chunk of R, 256-target tile, source-body split)
-//   epilogue task = (item, body, rhs)
-//   pack task     = (item, rhs)
-// The arithmetic per target is the single-geometry sweep's (kernels.hip): float32 body-relative
-// or float64 coordinates, float64 accumulation per source body, own body skipped, then self
-// block, diagonal limit, identity and completion in float64 with the partials summed in split
-// order. Items above the FMM threshold are applied by the single-geometry path.
+// One operator apply for many geometries at once (batched solves and the server): the pair sweeps
+// and the finishing terms of every item run as one launch per kernel class instead of a few per
+// geometry. Work is described by task lists built on the host whenever the set of active items
+// changes:
+//   sweep task  = (item, first rhs of a group of R, tile of kSweepTile targets, source split)
+//   finish task = (item, body, rhs, group)
+// The sweep is the single-geometry float64 sweep (pairs.h) over all pairs. With BIE_MIXED, items of a
+// batch with kMmRhs or more right-hand sides take their pairs of different bodies in float32 on the
+// matrix cores instead (k_multi_mm: 16 right-hand sides at a time) and the bodies' own blocks in
+// float64; fewer right-hand sides stay in float64, where float32 takes no less time per pair. (The
+// server's items always do: how many right-hand sides its items have depends on the other requests in
+// flight, and a request's arithmetic must not.) Float64 right-hand sides go in groups of up to eight (Laplace) or
+// four (Stokes); splits and summation order depend on the geometry alone, and every group size
+// forms a column's sums in the same order, so a system's result depends neither on the rest of the
+// batch nor on the other right-hand sides of its item. Items above the FMM threshold are applied
+// by the single-geometry path.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -16,18 +21,38 @@
 #include <vector>
 
 #include "internal.h"
+#include "pairs.h"
 
 namespace bie {
 
 struct ItemDesc {
-  int M, N, kind, nrhs, R, nchunk, ntile, nsplit;
-  long long io;    // offset of the item's rhs block in the flat in/out vectors (doubles)
-  long long slot;  // first partial slot of the item
-  const int *body_ptr, *body_of, *split_body;
-  const double *x, *y, *nx, *ny, *w, *kappa, *px, *py, *xc, *yc;
+  int M, N, nrhs, S, per;  // S source splits of per nodes
+  long long io;       // offset of the item's rhs block in the flat in/out vectors (doubles)
+  long long part;     // offset of its partial sums: rhs group r0 at part + r0 S len, [S][R][len]
+  const int *body_ptr;
+  const double *nx, *ny, *w, *kappa, *px, *py;
   const double2 *xy;
+  double scale;       // bie_geom::pair_scale
+  // float32 sweep (mm: the item has it): lists of 16-target tiles (body, first node) and of source
+  // chunks (body, first node, nodes); Smm splits of cper chunks, and one more slot of partial sums
+  // for the bodies' own blocks: group r0 at part + r0 (Smm + 1) len
+  int mm, ntile, nchunk, cper, Smm;
+  const int2 *tile;
+  const int4 *chunk;
   const float2 *xr;
+  const double *xc, *yc;
 };
+
+// Right-hand sides per group of the float32 matrix-core sweep, and the fewest an item (and a group)
+// has for it.
+constexpr int kMmGroup = 16;
+constexpr int kMmRhs = 8;
+constexpr int kMmChunk = 64;                       // sources staged at a time (one body's)
+constexpr int kMmTiles = 2;                        // 16-target tiles per wave
+constexpr int kMmTile = 16 * kMmTiles * 4;         // targets per workgroup, at most
+
+// Right-hand side group sizes of each kind.
+constexpr int kGroups[2][5] = {{8, 4, 3, 2, 1}, {4, 3, 2, 1, 0}};
 
 constexpr int kFmmStreams = 4;
 
@@ -37,11 +62,12 @@ struct MultiPlan {
   // appearance), forked from and joined back to the caller's stream
   hipStream_t pool[kFmmStreams] = {};
   hipEvent_t fork = nullptr, join[kFmmStreams] = {};
-  std::vector<int> split_host;
-  int nfar[2] = {0, 0}, nepi[2] = {0, 0}, npack = 0;
-  int *far_task[2] = {nullptr, nullptr}, *epi_task[2] = {nullptr, nullptr}, *pack_task = nullptr;
+  int nsweep = 0, nfin = 0, nlap = 0;  // tasks; finish tasks of Laplace items (they come first)
+  int nmm[2] = {0, 0};                 // float32 sweep tasks per kind
+  int4 *sweep_task = nullptr, *fin_task = nullptr, *mm_task[2] = {nullptr, nullptr};
+  DevBuf list_buf;  // the items' tile and chunk lists
   ItemDesc *desc = nullptr;
-  long long nslots[2] = {0, 0};
+  long long npart = 0;  // doubles of partial sums
   // the plan is reused while every item matches: geometry id, kind, rhs count, method and
   // offset of its block, and the active flags
   std::vector<unsigned long long> key_gen;
@@ -63,6 +89,7 @@ void multi_destroy(MultiPlan *p) {
   }
   if (p->fork) (void)hipEventDestroy(p->fork);
   p->desc_buf.release();
+  p->list_buf.release();
   p->task_buf.release();
   p->ws.release();
   delete p;
@@ -70,463 +97,420 @@ void multi_destroy(MultiPlan *p) {
 
 namespace {
 
-constexpr int kT = 256;  // targets per far tile (= kBlock)
-constexpr float kFar32 = 1.0e18f;
-constexpr double kFar64 = 1.0e100;
-
-// The descriptor's pointers are generic; a load through a generic pointer may reach per-lane
-// private memory, so the compiler treats its result as divergent even at a uniform address.
-// Casting to the global address space lets wave-uniform reads (source nodes, strengths, body
-// ranges) become scalar loads.
-template <class T>
-using gptr = const T __attribute__((address_space(1))) *;
-template <class T>
-__device__ __forceinline__ gptr<T> G(const T *p) {
-  return (gptr<T>)p;
-}
-
-__device__ __forceinline__ float2 ldf2(const float2 *p, long long i) {
-  const gptr<float> q = G(reinterpret_cast<const float *>(__builtin_assume_aligned(p, 8)));
-  return make_float2(q[2 * i], q[2 * i + 1]);
-}
-__device__ __forceinline__ double2 ldd2(const double2 *p, long long i) {
-  const gptr<double> q = G(reinterpret_cast<const double *>(__builtin_assume_aligned(p, 16)));
-  return make_double2(q[2 * i], q[2 * i + 1]);
-}
-
-__device__ inline double rcp64(double a) {
-  const double y = __builtin_amdgcn_rcp(a);
-  const double e = fma(-a, y, 1.0);
-  return fma(y, e, y);
-}
-
-__device__ inline double block_sum(double v, double *sh) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 0) sh[wid] = v;
-  __syncthreads();
-  const double t = (sh[0] + sh[1]) + (sh[2] + sh[3]);
-  __syncthreads();
-  return t;
-}
-
-// task encoding: 4 ints per far task (item, chunk, tile, split); 3 per epilogue (item, body, rhs);
-// 2 per pack task (item, rhs)
-
-// Far-field precision of an item: MODE 0 float64, 1 float32, 2 bit `it` of the mask (per-item
-// precisions of a relaxed mixed batch; the branch is uniform over the workgroup).
+// The items that take the float32 sweep in an apply: those whose bit is set, where they have it.
 struct ItemMask {
   unsigned long long w[kMaxPrecGroups / 64];
 };
-__device__ __forceinline__ bool item_f32(int mode, const ItemMask &m, int it) {
-  return mode == 1 || (mode == 2 && ((m.w[it >> 6] >> (it & 63)) & 1ull));
+__device__ __forceinline__ bool in_mask(const ItemMask &m, int it) {
+  return (m.w[it >> 6] >> (it & 63)) & 1ull;
 }
 
-__global__ __launch_bounds__(kBlock) void k_multi_pack(const int *__restrict__ tasks,
-                                                      const ItemDesc *__restrict__ D,
-                                                      const double *__restrict__ mu,
-                                                      double *__restrict__ s64,
-                                                      float *__restrict__ s32) {
-  const int it = tasks[2 * blockIdx.x], r = tasks[2 * blockIdx.x + 1];
-  const ItemDesc &d = D[it];
-  const int comps = d.kind == 0 ? 1 : 2;
-  const long long len = (long long)d.M * comps;
-  const long long base = d.io + r * len;
-  for (long long t = threadIdx.x; t < len; t += kBlock) {
-    const double v = G(d.w)[t / comps] * mu[base + t];
-    s64[base + t] = v;
-    if (s32) s32[base + t] = (float)v;
+// Float64 sweep task: all sources of split sp, or (own) body sp's block of its own targets, which
+// goes with the float32 sweep of the others. z: first target.
+template <int KIND, int R>
+__device__ __forceinline__ void sweep_task(const int4 &t, const ItemDesc &d, bool own,
+                                           const double *__restrict__ mu,
+                                           double *__restrict__ partial, double *buf) {
+  const long long len = (long long)d.M * PairShape<KIND, R>::COMPS;
+  const PairSources src{d.xy, d.nx, d.ny, d.w, mu + d.io + t.y * len, len, d.scale};
+  const int sp = t.w & 0xfffff;
+  int i1, k0, k1;
+  long long at;
+  if (own) {  // slot Smm of the rhs group of 16 that t.y lies in
+    const int r0 = t.y / kMmGroup * kMmGroup, G = min(kMmGroup, d.nrhs - r0);
+    k0 = gload(d.body_ptr, sp);
+    i1 = k1 = gload(d.body_ptr, sp + 1);
+    at = (long long)r0 * (d.Smm + 1) * len + ((long long)d.Smm * G + (t.y - r0)) * len;
+  } else {
+    k0 = sp * d.per;
+    k1 = min(k0 + d.per, d.M);
+    i1 = d.M;
+    at = ((long long)t.y * d.S + (long long)sp * R) * len;
+  }
+  pair_sweep_tile<KIND, R>(t.z, i1, k0, k1, src, (KIND == kPairStk ? -1.0 : -0.5) / kPi,
+                           partial + d.part + at, buf);
+}
+
+// One launch for every kind and group size: task (item, first rhs, first target, split or body |
+// (16 kind + R) << 20 | own << 26).
+// Separate launches let the smaller groups keep more waves in flight but ran one after another:
+// the remainders of six geometries' P and M took seven launches of about 8 us beside 100 us of
+// full groups.
+__global__ __launch_bounds__(kBlock, 2) void k_multi_sweep(const int4 *__restrict__ tasks,
+                                                           const ItemDesc *__restrict__ D,
+                                                           const double *__restrict__ mu,
+                                                           const ItemMask mm,
+                                                           double *__restrict__ partial) {
+  __shared__ double buf[kSweepLds<kPairStk, 4> > kSweepLds<kPairLapN, 8> ? kSweepLds<kPairStk, 4>
+                                                                         : kSweepLds<kPairLapN, 8>];
+  const int4 t = tasks[blockIdx.x];
+  const ItemDesc &d = D[t.x];
+  const bool own = t.w >> 26;
+  if (own != (d.mm && in_mask(mm, t.x))) return;  // (whole workgroup)
+  switch ((t.w >> 20) & 0x3f) {
+    case 8: sweep_task<kPairLapN, 8>(t, d, own, mu, partial, buf); break;
+    case 4: sweep_task<kPairLapN, 4>(t, d, own, mu, partial, buf); break;
+    case 3: sweep_task<kPairLapN, 3>(t, d, own, mu, partial, buf); break;
+    case 2: sweep_task<kPairLapN, 2>(t, d, own, mu, partial, buf); break;
+    case 1: sweep_task<kPairLapN, 1>(t, d, own, mu, partial, buf); break;
+    case 16 + 4: sweep_task<kPairStk, 4>(t, d, own, mu, partial, buf); break;
+    case 16 + 3: sweep_task<kPairStk, 3>(t, d, own, mu, partial, buf); break;
+    case 16 + 2: sweep_task<kPairStk, 2>(t, d, own, mu, partial, buf); break;
+    default: sweep_task<kPairStk, 1>(t, d, own, mu, partial, buf); break;
   }
 }
 
-template <int R, int MODE>
-__global__ __launch_bounds__(kBlock) void k_multi_far_lap(const int *__restrict__ tasks,
-                                                         const ItemDesc *__restrict__ D,
-                                                         const double *__restrict__ s64,
-                                                         const float *__restrict__ s32,
-                                                         double *__restrict__ partial,
-                                                         const ItemMask f32mask) {
-  const int *tk = tasks + 4 * blockIdx.x;
-  const int it = tk[0], ch = tk[1], tile = tk[2], sp = tk[3];
-  const bool F32 = item_f32(MODE, f32mask, it);
-  const ItemDesc &d = D[it];
-  const int M = d.M;
-  const int i = tile * kT + threadIdx.x;
-  const bool valid = i < M;
-  const int ii = valid ? i : M - 1;
-  const int bi = G(d.body_of)[ii];
-  const int r0 = ch * R;  // rhs r0..r0+R-1; those past nrhs read padding or the next item and
-                          // only fill partial entries that the epilogue never reads
-  const long long sb = d.io + (long long)r0 * M;
-  double Gx[R], Gy[R];
+// Float32 pairs of different bodies on the matrix cores: for 16 targets and four sources a lane forms
+// one kernel value (target lane % 16, source lane / 16), the A operand of a 16 x 16 x 4 product
+// whose B operand holds the sources' strengths of 16 right-hand sides. A Laplace value is one
+// operand, a Stokes pair's symmetric 2 x 2 block three, used in four products. A workgroup takes up
+// to eight 16-target tiles (two per wave, each of one body) against one split's source chunks
+// (at most 64 nodes of one body): coordinates relative to the source body's centroid in float32, a
+// chunk's products added into float64 (the float32 scheme of the single-geometry sweep, which
+// adds once per body). Bound by the vector work per value and the products, which do not overlap:
+// per 64 pairs and 16 right-hand sides about 75 (Laplace) and 200 (Stokes) cycles, where the vector
+// sweep took 34 (Stokes) cycles per right-hand side. P and M of 32 geometries of 8 to 128 bodies:
+// 5.4 -> 4.0 s with the block preconditioner, 19.6 -> 13.3 s without (in float64 throughout: 5.6
+// and 23.9 s).
+typedef float mm_f4 __attribute__((ext_vector_type(4)));
+
+template <bool STK>
+__global__ __launch_bounds__(kBlock) void k_multi_mm(const int4 *__restrict__ tasks,
+                                                     const ItemDesc *__restrict__ D,
+                                                     const double *__restrict__ mu,
+                                                     const ItemMask mm,
+                                                     double *__restrict__ partial) {
+  constexpr int C = STK ? 2 : 1;
+  constexpr int ROW = kMmGroup * C + 2;  // floats per staged source (padded: writes spread over banks)
+  __shared__ float2 xs[kMmChunk];
+  __shared__ float ss[kMmChunk * ROW];
+  const int4 t = tasks[blockIdx.x];  // item, first rhs, first tile, split
+  if (!in_mask(mm, t.x)) return;     // (whole workgroup)
+  const ItemDesc &d = D[t.x];
+  const int r0 = t.y, G = min(kMmGroup, d.nrhs - r0);
+  const long long len = (long long)d.M * C;
+  const int lane = threadIdx.x & 63, j = lane & 15, q = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // this wave's tiles: body (wave-uniform; -1: none) and this lane's target
+  int body[kMmTiles], first[kMmTiles];
+  double cx[kMmTiles], cy[kMmTiles];
+  float2 pr[kMmTiles];
+  float nx[kMmTiles], ny[kMmTiles], tx[kMmTiles], ty[kMmTiles];
+  double acc[kMmTiles][C][4];
 #pragma unroll
-  for (int r = 0; r < R; ++r) Gx[r] = Gy[r] = 0.0;
-  const int c0 = G(d.split_body)[sp], c1 = G(d.split_body)[sp + 1];
-  const double cxi = G(d.xc)[bi], cyi = G(d.yc)[bi];
-  const float2 pr = ldf2(d.xr, ii);
-  const double2 p64 = ldd2(d.xy, ii);
+  for (int u = 0; u < kMmTiles; ++u) {
+    const int ti = t.z + wv * kMmTiles + u;
+    body[u] = -1;
+    first[u] = 0;
+    if (ti < d.ntile) {
+      body[u] = __builtin_amdgcn_readfirstlane(gload(reinterpret_cast<const int *>(d.tile), 2 * ti));
+      first[u] = __builtin_amdgcn_readfirstlane(gload(reinterpret_cast<const int *>(d.tile), 2 * ti + 1));
+      const int i = min(first[u] + j, gload(d.body_ptr, body[u] + 1) - 1);
+      cx[u] = gload(d.xc, body[u]);
+      cy[u] = gload(d.yc, body[u]);
+      const float *p = reinterpret_cast<const float *>(d.xr);
+      pr[u] = make_float2(gload(p, 2LL * i), gload(p, 2LL * i + 1));
+      nx[u] = (float)gload(d.nx, i);
+      ny[u] = (float)gload(d.ny, i);
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[u][c][e] = 0.0;
+  }
+  const int c0 = t.w * d.cper, c1 = min(c0 + d.cper, d.nchunk);
+  // staging: thread (row r, kk) takes nodes kk, kk + 16, ... of the chunk for right-hand side r
+  const int sr = threadIdx.x >> 4, kk = threadIdx.x & 15;
+  const double *m = mu + d.io + (long long)(r0 + min(sr, G - 1)) * len;
+  double mv[4][C], wt[4];
+  float2 xv;
+  int4 ch = d.chunk[c0];
+  auto fetch = [&](const int4 &h) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int k = h.y + min(kk + 16 * e, h.z - 1);
+      wt[e] = gload(d.w, k);
+#pragma unroll
+      for (int c = 0; c < C; ++c) mv[e][c] = m[(long long)C * k + c];
+    }
+    if (threadIdx.x < kMmChunk) {
+      const float *p = reinterpret_cast<const float *>(d.xr);
+      const long long k = h.y + min((int)threadIdx.x, h.z - 1);
+      xv = make_float2(gload(p, 2 * k), gload(p, 2 * k + 1));
+    }
+  };
+  fetch(ch);
+  int frame = -1;  // the body whose centroid tx, ty are relative to
   for (int c = c0; c < c1; ++c) {
-    const bool self = (c == bi);
-    if (__all(self)) continue;
-    const int k0 = G(d.body_ptr)[c], k1 = G(d.body_ptr)[c + 1];
-    if (F32) {
-      float tx = (float)((cxi - G(d.xc)[c]) + (double)pr.x);
-      float ty = (float)((cyi - G(d.yc)[c]) + (double)pr.y);
-      tx = self ? kFar32 : tx;
-      ty = self ? kFar32 : ty;
-      float gx[R], gy[R];
+    const int cb = __builtin_amdgcn_readfirstlane(ch.x), n = __builtin_amdgcn_readfirstlane(ch.z);
+    // nodes past the chunk's end: no strength, far away
 #pragma unroll
-      for (int r = 0; r < R; ++r) gx[r] = gy[r] = 0.0f;
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int a = 0; a < C; ++a)
+        ss[(kk + 16 * e) * ROW + C * sr + a] = kk + 16 * e < n && sr < G ? (float)(wt[e] * mv[e][a]) : 0.0f;
+    if (threadIdx.x < kMmChunk)
+      xs[threadIdx.x] = (int)threadIdx.x < n ? xv : make_float2(1.0e18f, 1.0e18f);
+    __syncthreads();
+    if (c + 1 < c1) {
+      ch = d.chunk[c + 1];
+      fetch(ch);
+    }
+    if (frame != cb) {
+      frame = cb;
+      const double sx = gload(d.xc, cb), sy = gload(d.yc, cb);
+#pragma unroll
+      for (int u = 0; u < kMmTiles; ++u) {
+        tx[u] = (float)((cx[u] - sx) + (double)pr[u].x);
+        ty[u] = (float)((cy[u] - sy) + (double)pr[u].y);
+      }
+    }
+    mm_f4 y[kMmTiles][C];
+#pragma unroll
+    for (int u = 0; u < kMmTiles; ++u)
+#pragma unroll
+      for (int a = 0; a < C; ++a) y[u][a] = mm_f4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int kb = 0; kb < n; kb += 4) {
+      const int k = kb + q;
+      const float2 p = xs[k];
+      float b[C];
+#pragma unroll
+      for (int a = 0; a < C; ++a) b[a] = ss[k * ROW + C * j + a];
+#pragma unroll
+      for (int u = 0; u < kMmTiles; ++u) {
+        if (body[u] == cb || body[u] < 0) continue;  // (wave-uniform)
+        const float dx = tx[u] - p.x, dy = ty[u] - p.y;
+        const float inv = __builtin_amdgcn_rcpf(fmaf(dx, dx, dy * dy));
+        const float a = fmaf(dx, nx[u], dy * ny[u]) * inv;
+        if constexpr (STK) {
+          const float g = a * inv, gx = g * dx, gy = g * dy;
+          const float xx = gx * dx, xy = gx * dy, yy = gy * dy;
+          y[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xx, b[0], y[u][0], 0, 0, 0);
+          y[u][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(xy, b[0], y[u][1], 0, 0, 0);
+          y[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xy, b[C - 1], y[u][0], 0, 0, 0);
+          y[u][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(yy, b[C - 1], y[u][1], 0, 0, 0);
+        } else {
+          y[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b[0], y[u][0], 0, 0, 0);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kMmTiles; ++u)
+#pragma unroll
+      for (int a = 0; a < C; ++a)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[u][a][e] += (double)y[u][a][e];
+    __syncthreads();  // the chunk is no longer read
+  }
+  // accumulator layout: lane (j, q) holds targets 4 q + e of right-hand side j
+  if (j >= G) return;
+  double *o = partial + d.part + (long long)r0 * (d.Smm + 1) * len + ((long long)t.w * G + j) * len;
+  const double f = (STK ? -1.0 : -0.5) / kPi;
+#pragma unroll
+  for (int u = 0; u < kMmTiles; ++u) {
+    if (body[u] < 0) continue;
+    const int b1 = gload(d.body_ptr, body[u] + 1);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int i = first[u] + 4 * q + e;
+      if (i >= b1) continue;
+#pragma unroll
+      for (int a = 0; a < C; ++a) o[(long long)C * i + a] = f * acc[u][a][e];
+    }
+  }
+}
+
+// Identity, diagonal limit, completion and the splits' sums (in order) of one body and right-hand
+// side by one wave: task (item, body, rhs r, first rhs of its group | group size << 24).
+template <bool STK>
+__device__ __forceinline__ void finish_task(const int4 &t, const ItemDesc &d,
+                                            bool mm, const double *__restrict__ mu,
+                                            const double *__restrict__ partial,
+                                            double *__restrict__ out) {
+  const int lane = threadIdx.x & 63;
+  constexpr int C = STK ? 2 : 1;
+  const long long len = (long long)d.M * C;
+  const int r0 = mm ? t.z / kMmGroup * kMmGroup : t.w & 0xffffff;
+  const int R = mm ? min(kMmGroup, d.nrhs - r0) : t.w >> 24, S = mm ? d.Smm + 1 : d.S;
+  const int k0 = gload(d.body_ptr, t.y), k1 = gload(d.body_ptr, t.y + 1);
+  const double *m = mu + d.io + t.z * len;
+  const double *part = partial + d.part + r0 * S * len + (t.z - r0) * len;
+  double *o = out + d.io + t.z * len;
+  double s[3] = {0.0, 0.0, 0.0};
+  for (int k = k0 + lane; k < k1; k += 64) {
+    const double w = gload(d.w, k);
+    if (STK) {
+      const double s1 = w * m[2 * k], s2 = w * m[2 * k + 1];
+      s[0] += s1;
+      s[1] += s2;
+      s[2] += gload(d.px, k) * s1 + gload(d.py, k) * s2;
+    } else {
+      s[0] += w * m[k];
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < (STK ? 3 : 1); ++c)
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) s[c] += __shfl_xor(s[c], off, 64);
+  for (int i = k0 + lane; i < k1; i += 64) {
+    double far[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) far[c] = 0.0;
 #pragma unroll 4
-      for (int k = k0; k < k1; ++k) {
-        const float2 q = ldf2(d.xr, k);
-        const float dx = tx - q.x, dy = ty - q.y;
-        const float inv = __builtin_amdgcn_rcpf(fmaf(dx, dx, dy * dy));
+    for (int sp = 0; sp < S; ++sp)
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const float sv = s32[sb + (long long)r * M + k];
-          const float t = sv * inv;
-          gx[r] = fmaf(dx, t, gx[r]);
-          gy[r] = fmaf(dy, t, gy[r]);
-        }
-      }
-      if (!self) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          Gx[r] += (double)gx[r];
-          Gy[r] += (double)gy[r];
-        }
-      }
+      for (int c = 0; c < C; ++c) far[c] += part[(long long)sp * R * len + (long long)C * i + c];
+    const double wi = gload(d.w, i), kap = gload(d.kappa, i);
+    if constexpr (STK) {
+      const double m1 = m[2 * i], m2 = m[2 * i + 1];
+      const double t1 = -gload(d.ny, i), t2 = gload(d.nx, i);  // unit tangent
+      const double dg = -kap / (2.0 * kPi) * (t1 * (wi * m1) + t2 * (wi * m2));
+      o[2 * i] = 0.5 * m1 + dg * t1 + s[0] + gload(d.px, i) * s[2] + far[0];
+      o[2 * i + 1] = 0.5 * m2 + dg * t2 + s[1] + gload(d.py, i) * s[2] + far[1];
     } else {
-      const double tx = self ? kFar64 : p64.x, ty = self ? kFar64 : p64.y;
-      double gx[R], gy[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) gx[r] = gy[r] = 0.0;
-#pragma unroll 2
-      for (int k = k0; k < k1; ++k) {
-        const double2 q = ldd2(d.xy, k);
-        const double dx = tx - q.x, dy = ty - q.y;
-        const double inv = rcp64(fma(dx, dx, dy * dy));
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const double sv = s64[sb + (long long)r * M + k];
-          const double t = sv * inv;
-          gx[r] = fma(dx, t, gx[r]);
-          gy[r] = fma(dy, t, gy[r]);
-        }
-      }
-      if (!self) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          Gx[r] += gx[r];
-          Gy[r] += gy[r];
-        }
-      }
+      const double mi = m[i];
+      o[i] = 0.5 * mi - wi * mi * kap / (4.0 * kPi) + s[0] + far[0];
     }
-  }
-  const long long slot = d.slot + ((long long)ch * d.ntile + tile) * d.nsplit + sp;
-  double *o = partial + slot * (R * kT);
-  const double a = G(d.nx)[ii], b = G(d.ny)[ii];
-#pragma unroll
-  for (int r = 0; r < R; ++r) o[r * kT + threadIdx.x] = -(a * Gx[r] + b * Gy[r]) / (2.0 * kPi);
-}
-
-template <int R, int MODE>
-__global__ __launch_bounds__(kBlock) void k_multi_far_stk(const int *__restrict__ tasks,
-                                                         const ItemDesc *__restrict__ D,
-                                                         const double *__restrict__ s64,
-                                                         const float *__restrict__ s32,
-                                                         double *__restrict__ partial,
-                                                         const ItemMask f32mask) {
-  const int *tk = tasks + 4 * blockIdx.x;
-  const int it = tk[0], ch = tk[1], tile = tk[2], sp = tk[3];
-  const bool F32 = item_f32(MODE, f32mask, it);
-  const ItemDesc &d = D[it];
-  const int M = d.M;
-  const int i = tile * kT + threadIdx.x;
-  const bool valid = i < M;
-  const int ii = valid ? i : M - 1;
-  const int bi = G(d.body_of)[ii];
-  const int r0 = ch * R;
-  const long long sb = d.io + (long long)r0 * 2 * M;
-  double Gx[R], Gy[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) Gx[r] = Gy[r] = 0.0;
-  const int c0 = G(d.split_body)[sp], c1 = G(d.split_body)[sp + 1];
-  const double cxi = G(d.xc)[bi], cyi = G(d.yc)[bi];
-  const float2 pr = ldf2(d.xr, ii);
-  const double2 p64 = ldd2(d.xy, ii);
-  const double nxi = G(d.nx)[ii], nyi = G(d.ny)[ii];
-  for (int c = c0; c < c1; ++c) {
-    const bool self = (c == bi);
-    if (__all(self)) continue;
-    const int k0 = G(d.body_ptr)[c], k1 = G(d.body_ptr)[c + 1];
-    if (F32) {
-      float tx = (float)((cxi - G(d.xc)[c]) + (double)pr.x);
-      float ty = (float)((cyi - G(d.yc)[c]) + (double)pr.y);
-      tx = self ? kFar32 : tx;
-      ty = self ? kFar32 : ty;
-      const float fnx = (float)nxi, fny = (float)nyi;
-      float gx[R], gy[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) gx[r] = gy[r] = 0.0f;
-#pragma unroll 2
-      for (int k = k0; k < k1; ++k) {
-        const float2 q = ldf2(d.xr, k);
-        const float dx = tx - q.x, dy = ty - q.y;
-        const float inv = __builtin_amdgcn_rcpf(fmaf(dx, dx, dy * dy));
-        const float a = fmaf(dx, fnx, dy * fny) * (inv * inv);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const float2 sv = ldf2(reinterpret_cast<const float2 *>(s32 + sb + (long long)r * 2 * M), k);
-          const float cc = fmaf(dx, sv.x, dy * sv.y) * a;
-          gx[r] = fmaf(cc, dx, gx[r]);
-          gy[r] = fmaf(cc, dy, gy[r]);
-        }
-      }
-      if (!self) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          Gx[r] += (double)gx[r];
-          Gy[r] += (double)gy[r];
-        }
-      }
-    } else {
-      const double tx = self ? kFar64 : p64.x, ty = self ? kFar64 : p64.y;
-      double gx[R], gy[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) gx[r] = gy[r] = 0.0;
-#pragma unroll 2
-      for (int k = k0; k < k1; ++k) {
-        const double2 q = ldd2(d.xy, k);
-        const double dx = tx - q.x, dy = ty - q.y;
-        const double inv = rcp64(fma(dx, dx, dy * dy));
-        const double a = fma(dx, nxi, dy * nyi) * (inv * inv);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          const double2 sv = ldd2(reinterpret_cast<const double2 *>(s64 + sb + (long long)r * 2 * M), k);
-          const double cc = fma(dx, sv.x, dy * sv.y) * a;
-          gx[r] = fma(cc, dx, gx[r]);
-          gy[r] = fma(cc, dy, gy[r]);
-        }
-      }
-      if (!self) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-          Gx[r] += gx[r];
-          Gy[r] += gy[r];
-        }
-      }
-    }
-  }
-  const long long slot = d.slot + ((long long)ch * d.ntile + tile) * d.nsplit + sp;
-  double *o = partial + slot * (R * kT * 2);
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    o[(r * kT + threadIdx.x) * 2] = -Gx[r] / kPi;
-    o[(r * kT + threadIdx.x) * 2 + 1] = -Gy[r] / kPi;
   }
 }
 
-// Epilogue: self block, diagonal, identity, completion, far partials (in split order).
-template <int R>
-__global__ __launch_bounds__(kBlock) void k_multi_epi_lap(const int *__restrict__ tasks,
+__global__ __launch_bounds__(kBlock) void k_multi_finish(int ntask, int nlap,
+                                                         const int4 *__restrict__ tasks,
                                                          const ItemDesc *__restrict__ D,
                                                          const double *__restrict__ mu,
-                                                         const double *__restrict__ s64,
+                                                         const ItemMask mm,
                                                          const double *__restrict__ partial,
                                                          double *__restrict__ out) {
-  __shared__ double sh[4];
-  const int it = tasks[3 * blockIdx.x], b = tasks[3 * blockIdx.x + 1], r = tasks[3 * blockIdx.x + 2];
-  const ItemDesc &d = D[it];
-  const int M = d.M;
-  const int k0 = G(d.body_ptr)[b], k1 = G(d.body_ptr)[b + 1];
-  const double *s = s64 + d.io + (long long)r * M;
-  const double *m = mu + d.io + (long long)r * M;
-  double part = 0.0;
-  for (int k = k0 + threadIdx.x; k < k1; k += kBlock) part += s[k];
-  const double charge = block_sum(part, sh);
-  const int ch = r / R, j = r % R;
-  for (int base = k0; base < k1; base += kBlock) {
-    const int i = base + threadIdx.x;
-    const bool valid = i < k1;
-    const int ii = valid ? i : k0;
-    const double xi = G(d.x)[ii], yi = G(d.y)[ii], a = G(d.nx)[ii], bb = G(d.ny)[ii];
-    double gx = 0.0, gy = 0.0;
-    for (int k = k0; k < k1; ++k) {
-      const double dx = xi - G(d.x)[k], dy = yi - G(d.y)[k];
-      const bool same = (k == ii);
-      const double inv = rcp64(same ? 1.0 : fma(dx, dx, dy * dy));
-      const double t = same ? 0.0 : s[k] * inv;
-      gx = fma(dx, t, gx);
-      gy = fma(dy, t, gy);
-    }
-    double v = 0.5 * m[ii] - (a * gx + bb * gy) / (2.0 * kPi) - s[ii] * G(d.kappa)[ii] / (4.0 * kPi) + charge;
-    const int tile = ii / kT;
-    for (int sp = 0; sp < d.nsplit; ++sp) {
-      const long long slot = d.slot + ((long long)ch * d.ntile + tile) * d.nsplit + sp;
-      v += partial[slot * (R * kT) + j * kT + (ii - tile * kT)];
-    }
-    if (valid) out[d.io + (long long)r * M + i] = v;
-  }
+  const int ti = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (ti >= ntask) return;
+  const int4 t = tasks[ti];
+  const ItemDesc &d = D[t.x];
+  const bool f32 = d.mm && in_mask(mm, t.x);
+  if (ti < nlap) finish_task<false>(t, d, f32, mu, partial, out);
+  else finish_task<true>(t, d, f32, mu, partial, out);
 }
 
-template <int R>
-__global__ __launch_bounds__(kBlock) void k_multi_epi_stk(const int *__restrict__ tasks,
-                                                         const ItemDesc *__restrict__ D,
-                                                         const double *__restrict__ mu,
-                                                         const double *__restrict__ s64,
-                                                         const double *__restrict__ partial,
-                                                         double *__restrict__ out) {
-  __shared__ double sh[4];
-  const int it = tasks[3 * blockIdx.x], b = tasks[3 * blockIdx.x + 1], r = tasks[3 * blockIdx.x + 2];
-  const ItemDesc &d = D[it];
-  const int M = d.M;
-  const int k0 = G(d.body_ptr)[b], k1 = G(d.body_ptr)[b + 1];
-  const double *s = s64 + d.io + (long long)r * 2 * M;
-  const double *m = mu + d.io + (long long)r * 2 * M;
-  double f1 = 0.0, f2 = 0.0, tq = 0.0;
-  for (int k = k0 + threadIdx.x; k < k1; k += kBlock) {
-    f1 += s[2 * k];
-    f2 += s[2 * k + 1];
-    tq += G(d.px)[k] * s[2 * k] + G(d.py)[k] * s[2 * k + 1];
-  }
-  const double F1 = block_sum(f1, sh), F2 = block_sum(f2, sh), TQ = block_sum(tq, sh);
-  const int ch = r / R, j = r % R;
-  for (int base = k0; base < k1; base += kBlock) {
-    const int i = base + threadIdx.x;
-    const bool valid = i < k1;
-    const int ii = valid ? i : k0;
-    const double xi = G(d.x)[ii], yi = G(d.y)[ii], a = G(d.nx)[ii], bb = G(d.ny)[ii];
-    double gx = 0.0, gy = 0.0;
-    for (int k = k0; k < k1; ++k) {
-      const double dx = xi - G(d.x)[k], dy = yi - G(d.y)[k];
-      const bool same = (k == ii);
-      const double inv = rcp64(same ? 1.0 : fma(dx, dx, dy * dy));
-      const double rn = fma(dx, a, dy * bb);
-      const double cc = same ? 0.0 : fma(dx, s[2 * k], dy * s[2 * k + 1]) * rn * (inv * inv);
-      gx = fma(cc, dx, gx);
-      gy = fma(cc, dy, gy);
-    }
-    const double t1 = -bb, t2 = a;
-    const double ts = t1 * s[2 * ii] + t2 * s[2 * ii + 1];
-    const double dg = -G(d.kappa)[ii] / (2.0 * kPi);
-    double v1 = 0.5 * m[2 * ii] - gx / kPi + dg * t1 * ts + F1 + G(d.px)[ii] * TQ;
-    double v2 = 0.5 * m[2 * ii + 1] - gy / kPi + dg * t2 * ts + F2 + G(d.py)[ii] * TQ;
-    const int tile = ii / kT;
-    for (int sp = 0; sp < d.nsplit; ++sp) {
-      const long long slot = d.slot + ((long long)ch * d.ntile + tile) * d.nsplit + sp;
-      const double *o = partial + slot * (R * kT * 2) + (j * kT + (ii - tile * kT)) * 2;
-      v1 += o[0];
-      v2 += o[1];
-    }
-    if (valid) {
-      out[d.io + (long long)r * 2 * M + 2 * i] = v1;
-      out[d.io + (long long)r * 2 * M + 2 * i + 1] = v2;
-    }
-  }
+// Source splits of an item: from the geometry alone, about 256 workgroups per rhs group with at
+// least kBlock sources each (a batch has several groups and items to fill the compute units).
+int item_splits(int M) {
+  const int tiles = (M + kSweepTile - 1) / kSweepTile;
+  return std::max(1, std::min(256 / tiles, M / kBlock));
 }
 
-constexpr int kRLap = 8, kRStk = 4;
-
-// Source-body split ranges with about equal node counts.
-void split_bodies(const bie_geom *g, int S, std::vector<int> &out) {
-  out.clear();
-  out.push_back(0);
-  for (int s = 1; s < S; ++s) {
-    const long long cut = (long long)g->M * s / S;
-    int b = out.back();
-    while (b < g->N && g->h_body_ptr[b + 1] <= cut) ++b;
-    if (b > out.back() && b < g->N) out.push_back(b);
-  }
-  out.push_back(g->N);
+// The next right-hand side group of kind's items when `left` remain.
+int next_group(int kind, int left) {
+  int c = 0;
+  while (kGroups[kind][c] > left) ++c;
+  return kGroups[kind][c];
 }
 
 int build_plan(MultiPlan &P, const std::vector<MultiItem> &items, const std::vector<char> &active,
                hipStream_t s) {
   const int n = (int)items.size();
   std::vector<ItemDesc> desc(n);
-  std::vector<int> far[2], epi[2], pack, splits;
-  long long slots[2] = {0, 0};
-  std::vector<std::vector<int>> item_splits(n);
+  std::vector<int4> sweep[2], own[2], fin[2], mm[2], chunks;
+  std::vector<int2> tiles16;
+  std::vector<size_t> tile_at(n, 0), chunk_at(n, 0);
+  long long part = 0;
   for (int i = 0; i < n; ++i) {
     const MultiItem &m = items[i];
     bie_geom *g = m.g;
     ItemDesc &d = desc[i];
+    const int want = item_splits(g->M);
+    d = ItemDesc{};
     d.M = g->M;
     d.N = g->N;
-    d.kind = m.kind;
     d.nrhs = m.nrhs;
-    d.R = m.kind == 0 ? kRLap : kRStk;
-    d.nchunk = (m.nrhs + d.R - 1) / d.R;
-    d.ntile = (g->M + kT - 1) / kT;
+    d.per = (g->M + want - 1) / want;
+    d.S = (g->M + d.per - 1) / d.per;  // no split is empty
     d.io = m.io;
     d.body_ptr = g->body_ptr;
-    d.body_of = g->body_of;
-    d.x = g->x; d.y = g->y; d.nx = g->nx; d.ny = g->ny; d.w = g->w; d.kappa = g->kappa;
-    d.px = g->px; d.py = g->py; d.xc = g->xc; d.yc = g->yc; d.xy = g->xy; d.xr = g->xr;
-    // source splits from the geometry alone (about 4k workgroups for one rhs chunk, at most 16
-    // splits, which bounds the partial sums of items with many rhs), so a system's summation
-    // order depends neither on the rest of the batch nor on how many rhs share its item
-    const long long base = d.ntile;
-    const long long want = std::min<long long>(16, (4096 + base - 1) / base);
-    split_bodies(g, (int)std::min<long long>(want, std::min(g->N, 64)), item_splits[i]);
-    d.nsplit = (int)item_splits[i].size() - 1;
-    d.slot = slots[m.kind];
+    d.nx = g->nx; d.ny = g->ny; d.w = g->w; d.kappa = g->kappa;
+    d.px = g->px; d.py = g->py; d.xy = g->xy;
+    d.xr = g->xr; d.xc = g->xc; d.yc = g->yc;
+    d.scale = g->pair_scale;
+    d.part = part;
     if (!active[i] || m.fmm) continue;
-    slots[m.kind] += (long long)d.nchunk * d.ntile * d.nsplit;
-    for (int c = 0; c < d.nchunk; ++c)
-      for (int t = 0; t < d.ntile; ++t)
-        for (int sp = 0; sp < d.nsplit; ++sp) {
-          far[m.kind].push_back(i);
-          far[m.kind].push_back(c);
-          far[m.kind].push_back(t);
-          far[m.kind].push_back(sp);
-        }
-    for (int b = 0; b < g->N; ++b)
-      for (int r = 0; r < m.nrhs; ++r) {
-        epi[m.kind].push_back(i);
-        epi[m.kind].push_back(b);
-        epi[m.kind].push_back(r);
+    const long long len = g->M * (m.kind == 0 ? 1LL : 2LL);
+    d.mm = m.f32_sweep && m.nrhs >= kMmRhs && n <= kMaxPrecGroups;
+    if (d.mm) {
+      tile_at[i] = tiles16.size();
+      chunk_at[i] = chunks.size();
+      for (int b = 0; b < g->N; ++b) {
+        const int b0 = g->h_body_ptr[b], b1 = g->h_body_ptr[b + 1];
+        for (int k = b0; k < b1; k += 16) tiles16.push_back(make_int2(b, k));
+        for (int k = b0; k < b1; k += kMmChunk)
+          chunks.push_back(make_int4(b, k, std::min(kMmChunk, b1 - k), 0));
       }
-    for (int r = 0; r < m.nrhs; ++r) {
-      pack.push_back(i);
-      pack.push_back(r);
+      d.ntile = (int)(tiles16.size() - tile_at[i]);
+      d.nchunk = (int)(chunks.size() - chunk_at[i]);
+      const int wgs = (d.ntile + kMmTile / 16 - 1) / (kMmTile / 16);
+      const int smm = std::max(1, std::min(256 / wgs, d.nchunk / 4));
+      d.cper = (d.nchunk + smm - 1) / smm;
+      d.Smm = (d.nchunk + d.cper - 1) / d.cper;
+      for (int r0 = 0; r0 < m.nrhs; r0 += kMmGroup)
+        for (int sp = 0; sp < d.Smm; ++sp)
+          for (int t = 0; t < d.ntile; t += kMmTile / 16) mm[m.kind].push_back(make_int4(i, r0, t, sp));
+      // the bodies' own blocks in float64, in groups that stay within the groups of 16
+      for (int r0 = 0; r0 < m.nrhs;) {
+        const int left = std::min(m.nrhs, r0 / kMmGroup * kMmGroup + kMmGroup) - r0;
+        const int R = next_group(m.kind, left);
+        for (int b = 0; b < g->N; ++b)
+          for (int k = g->h_body_ptr[b]; k < g->h_body_ptr[b + 1]; k += kSweepTile)
+            own[m.kind].push_back(make_int4(i, r0, k, b | (16 * m.kind + R) << 20 | 1 << 26));
+        r0 += R;
+      }
+    }
+    part += m.nrhs * len * std::max(d.S, d.mm ? d.Smm + 1 : 0);
+    for (int r0 = 0; r0 < m.nrhs;) {
+      const int R = next_group(m.kind, m.nrhs - r0);
+      for (int sp = 0; sp < d.S; ++sp)
+        for (int k = 0; k < g->M; k += kSweepTile)
+          sweep[m.kind].push_back(make_int4(i, r0, k, sp | (16 * m.kind + R) << 20));
+      for (int b = 0; b < g->N; ++b)
+        for (int r = r0; r < r0 + R; ++r) fin[m.kind].push_back(make_int4(i, b, r, r0 | R << 24));
+      r0 += R;
     }
   }
-  // split arrays live in the task buffer; patch pointers after upload
-  std::vector<int> split_off(n + 1, 0);
-  for (int i = 0; i < n; ++i) split_off[i + 1] = split_off[i] + (int)item_splits[i].size();
-  const size_t nint = far[0].size() + far[1].size() + epi[0].size() + epi[1].size() + pack.size() +
-                      split_off[n] + 64;
-  BIE_TRY(P.task_buf.reserve(nint * 4 + 1024));
-  BIE_TRY(P.desc_buf.reserve(n * sizeof(ItemDesc) + 256));
-  int *q = P.task_buf.as<int>();
-  auto put = [&](const std::vector<int> &v) -> int * {
-    int *dst = q;
-    if (!v.empty())
-      (void)hipMemcpyAsync(dst, v.data(), v.size() * 4, hipMemcpyHostToDevice, s);
-    q += v.size();
-    return dst;
+  // the longest tasks (Stokes) first, so that the short ones fill the last round
+  std::vector<int4> all(sweep[1]);
+  auto append = [&](const std::vector<int4> &v) {
+    all.insert(all.end(), v.begin(), v.end());
+    return (int)v.size();
   };
-  P.far_task[0] = put(far[0]);
-  P.far_task[1] = put(far[1]);
-  P.epi_task[0] = put(epi[0]);
-  P.epi_task[1] = put(epi[1]);
-  P.pack_task = put(pack);
-  for (int i = 0; i < n; ++i) desc[i].split_body = put(item_splits[i]);
+  append(sweep[0]);
+  append(own[1]);
+  append(own[0]);
+  P.nsweep = (int)all.size();
+  P.nlap = append(fin[0]);
+  P.nfin = P.nlap + append(fin[1]);
+  for (int k = 0; k < 2; ++k) P.nmm[k] = append(mm[k]);
+  BIE_TRY(P.task_buf.reserve(all.size() * sizeof(int4) + 256));
+  BIE_TRY(P.desc_buf.reserve(n * sizeof(ItemDesc) + 256));
+  BIE_TRY(P.list_buf.reserve(chunks.size() * sizeof(int4) + tiles16.size() * sizeof(int2) + 256));
+  P.sweep_task = P.task_buf.as<int4>();
+  P.fin_task = P.sweep_task + P.nsweep;
+  P.mm_task[0] = P.fin_task + P.nfin;
+  P.mm_task[1] = P.mm_task[0] + P.nmm[0];
+  if (!all.empty())
+    BIE_HIP_CHECK(hipMemcpyAsync(P.sweep_task, all.data(), all.size() * sizeof(int4),
+                                 hipMemcpyHostToDevice, s));
+  int4 *dch = P.list_buf.as<int4>();
+  int2 *dti = reinterpret_cast<int2 *>(dch + chunks.size());
+  if (!chunks.empty()) {
+    BIE_HIP_CHECK(hipMemcpyAsync(dch, chunks.data(), chunks.size() * sizeof(int4),
+                                 hipMemcpyHostToDevice, s));
+    BIE_HIP_CHECK(hipMemcpyAsync(dti, tiles16.data(), tiles16.size() * sizeof(int2),
+                                 hipMemcpyHostToDevice, s));
+  }
+  for (int i = 0; i < n; ++i) {
+    desc[i].chunk = dch + chunk_at[i];
+    desc[i].tile = dti + tile_at[i];
+  }
   P.desc = P.desc_buf.as<ItemDesc>();
   BIE_HIP_CHECK(hipMemcpyAsync(P.desc, desc.data(), n * sizeof(ItemDesc), hipMemcpyHostToDevice, s));
   BIE_HIP_CHECK(hipStreamSynchronize(s));  // host vectors go out of scope
-  P.nfar[0] = (int)far[0].size() / 4;
-  P.nfar[1] = (int)far[1].size() / 4;
-  P.nepi[0] = (int)epi[0].size() / 3;
-  P.nepi[1] = (int)epi[1].size() / 3;
-  P.npack = (int)pack.size() / 2;
-  P.nslots[0] = slots[0];
-  P.nslots[1] = slots[1];
+  P.npart = part;
   return BIE_OK;
 }
 
@@ -535,7 +519,7 @@ int build_plan(MultiPlan &P, const std::vector<MultiItem> &items, const std::vec
 // out = (1/2 I + K + L) in for every active item (rhs blocks at items[i].io in flat vectors);
 // inactive items get out = 0.
 int multi_apply(MultiPlan *&P, const std::vector<MultiItem> &items, const std::vector<char> &active,
-                int precision, const double *in, double *out, long long Ntot, hipStream_t s,
+                int precision, const double *in, double *out, hipStream_t s,
                 const std::vector<char> *item_f32) {
   if (!P) P = new MultiPlan();
   const int n = (int)items.size();
@@ -543,19 +527,7 @@ int multi_apply(MultiPlan *&P, const std::vector<MultiItem> &items, const std::v
     set_error("multi_apply: per-item precisions need one flag per item and at most 1024 items");
     return BIE_EINVAL;
   }
-  // far-field mode: 0 float64, 1 float32, 2 per item (mask)
-  ItemMask mask{};
-  int mode = precision == BIE_MIXED ? 1 : 0;
-  if (item_f32) {
-    int nf = 0;
-    for (int i = 0; i < n; ++i)
-      if ((*item_f32)[i]) {
-        mask.w[i >> 6] |= 1ull << (i & 63);
-        ++nf;
-      }
-    mode = nf == 0 ? 0 : nf == n ? 1 : 2;
-  }
-  auto f32_of = [&](int i) { return mode == 2 ? (*item_f32)[i] != 0 : mode == 1; };
+  auto f32_of = [&](int i) { return item_f32 ? (*item_f32)[i] != 0 : precision == BIE_MIXED; };
   bool same = P->valid && (int)P->key_gen.size() == n && P->key_active == active;
   for (int i = 0; same && i < n; ++i)
     same = P->key_gen[i] == items[i].g->gen && P->key_kind[i] == items[i].kind &&
@@ -579,62 +551,40 @@ int multi_apply(MultiPlan *&P, const std::vector<MultiItem> &items, const std::v
     P->key_active = active;
     P->valid = true;
   }
-  const bool f32 = mode != 0;  // some item needs the float32 strengths
-  // workspace: s64 [Np], s32 [Np], partial (Laplace slots, then Stokes slots); Np pads Ntot by
-  // R rhs of the longest item so that a far task's last rhs chunk can read past its item
-  long long maxlen = 0;
-  for (const auto &it : items) maxlen = std::max<long long>(maxlen, (long long)it.g->M * 2);
-  const long long Np = align8(Ntot + (long long)kRLap * maxlen);
-  const size_t plap = (size_t)P->nslots[0] * kRLap * kT, pstk = (size_t)P->nslots[1] * kRStk * kT * 2;
-  const bool grow = P->ws.bytes < (size_t)Np * 12 + (plap + pstk) * 8 + 512;
-  BIE_TRY(P->ws.reserve((size_t)Np * 12 + (plap + pstk) * 8 + 512));
-  double *s64 = P->ws.as<double>();
-  float *s32 = reinterpret_cast<float *>(s64 + Np);
-  if (grow) BIE_HIP_CHECK(hipMemsetAsync(P->ws.ptr, 0, P->ws.bytes, s));  // padding stays finite
-  double *part = reinterpret_cast<double *>(
-      (reinterpret_cast<uintptr_t>(s32 + Np) + 63) & ~uintptr_t(63));
-  double *part_lap = part, *part_stk = part + plap;
+  BIE_TRY(P->ws.reserve((size_t)P->npart * sizeof(double)));
+  double *part = P->ws.as<double>();
   // inactive items (and FMM items, filled below) start from zero
   for (int i = 0; i < n; ++i)
     if (!active[i]) {
       const long long len = (long long)items[i].nrhs * items[i].g->M * (items[i].kind == 0 ? 1 : 2);
       BIE_HIP_CHECK(hipMemsetAsync(out + items[i].io, 0, len * sizeof(double), s));
     }
-  if (P->npack > 0)
-    hipLaunchKernelGGL(k_multi_pack, dim3(P->npack), dim3(kBlock), 0, s, P->pack_task, P->desc, in,
-                       s64, f32 ? s32 : nullptr);
-  if (P->nfar[0] > 0) {
-    ProfScope prof(f32 ? BIE_K_FAR_LAPLACE_F32 : BIE_K_FAR_LAPLACE_F64, s, 0);
-    if (mode == 2)
-      hipLaunchKernelGGL((k_multi_far_lap<kRLap, 2>), dim3(P->nfar[0]), dim3(kBlock), 0, s,
-                         P->far_task[0], P->desc, s64, s32, part_lap, mask);
-    else if (mode == 1)
-      hipLaunchKernelGGL((k_multi_far_lap<kRLap, 1>), dim3(P->nfar[0]), dim3(kBlock), 0, s,
-                         P->far_task[0], P->desc, s64, s32, part_lap, mask);
-    else
-      hipLaunchKernelGGL((k_multi_far_lap<kRLap, 0>), dim3(P->nfar[0]), dim3(kBlock), 0, s,
-                         P->far_task[0], P->desc, s64, s32, part_lap, mask);
-  }
-  if (P->nfar[1] > 0) {
-    ProfScope prof(f32 ? BIE_K_FAR_STOKES_F32 : BIE_K_FAR_STOKES_F64, s, 0);
-    if (mode == 2)
-      hipLaunchKernelGGL((k_multi_far_stk<kRStk, 2>), dim3(P->nfar[1]), dim3(kBlock), 0, s,
-                         P->far_task[1], P->desc, s64, s32, part_stk, mask);
-    else if (mode == 1)
-      hipLaunchKernelGGL((k_multi_far_stk<kRStk, 1>), dim3(P->nfar[1]), dim3(kBlock), 0, s,
-                         P->far_task[1], P->desc, s64, s32, part_stk, mask);
-    else
-      hipLaunchKernelGGL((k_multi_far_stk<kRStk, 0>), dim3(P->nfar[1]), dim3(kBlock), 0, s,
-                         P->far_task[1], P->desc, s64, s32, part_stk, mask);
-  }
-  {
+  if (P->nsweep > 0) {
+    ItemMask mm{};
+    bool any = false;
+    for (int i = 0; i < n && n <= kMaxPrecGroups; ++i)
+      if (f32_of(i)) {
+        mm.w[i >> 6] |= 1ull << (i & 63);
+        any = true;
+      }
+    for (int k = 1; any && k >= 0; --k) {
+      if (P->nmm[k] == 0) continue;
+      ProfScope prof(k ? BIE_K_FAR_STOKES_F32 : BIE_K_FAR_LAPLACE_F32, s, 0);
+      if (k)
+        hipLaunchKernelGGL(k_multi_mm<true>, dim3(P->nmm[k]), dim3(kBlock), 0, s, P->mm_task[k],
+                           P->desc, in, mm, part);
+      else
+        hipLaunchKernelGGL(k_multi_mm<false>, dim3(P->nmm[k]), dim3(kBlock), 0, s, P->mm_task[k],
+                           P->desc, in, mm, part);
+    }
+    {
+      ProfScope prof(P->nlap < P->nfin ? BIE_K_FAR_STOKES_F64 : BIE_K_FAR_LAPLACE_F64, s, 0);
+      hipLaunchKernelGGL(k_multi_sweep, dim3(P->nsweep), dim3(kBlock), 0, s, P->sweep_task, P->desc,
+                         in, mm, part);
+    }
     ProfScope prof(BIE_K_EPILOGUE, s, 0);
-    if (P->nepi[0] > 0)
-      hipLaunchKernelGGL(k_multi_epi_lap<kRLap>, dim3(P->nepi[0]), dim3(kBlock), 0, s,
-                         P->epi_task[0], P->desc, in, s64, part_lap, out);
-    if (P->nepi[1] > 0)
-      hipLaunchKernelGGL(k_multi_epi_stk<kRStk>, dim3(P->nepi[1]), dim3(kBlock), 0, s,
-                         P->epi_task[1], P->desc, in, s64, part_stk, out);
+    hipLaunchKernelGGL(k_multi_finish, dim3((P->nfin + 3) / 4), dim3(kBlock), 0, s, P->nfin,
+                       P->nlap, P->fin_task, P->desc, in, mm, part, out);
   }
   BIE_HIP_CHECK(hipGetLastError());
   // FMM items: independent geometries overlap on the stream pool; items of one geometry share

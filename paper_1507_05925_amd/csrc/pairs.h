@@ -12,8 +12,21 @@ namespace bie {
 //   kPairLap    (r . n_target) s / |r|^2                      kPairLapDl  (r . n_source) s / |r|^2
 //   kPairStk    (r . n_target)(r . s) r / |r|^4               kPairStkDl  (r . n_source)(r . s) r / |r|^4
 // kPairLap with one right-hand side accumulates s r / |r|^2 (two values) and takes the normal
-// component at the end, one multiply-add less per pair.
-enum PairKind { kPairLap = 0, kPairStk = 1, kPairLapDl = 2, kPairStkDl = 3 };
+// component at the end, one multiply-add less per pair; kPairLapN is kPairLap without that
+// exception, for callers whose sums must not depend on how many right-hand sides go together.
+enum PairKind { kPairLap = 0, kPairStk = 1, kPairLapDl = 2, kPairStkDl = 3, kPairLapN = 4 };
+
+// Loads through the global address space: a pointer that was itself loaded from memory (an item
+// descriptor's) is generic to the compiler, and generic loads also wait for LDS.
+template <class T>
+__device__ __forceinline__ T gload(const T *p, long long i) {
+  return ((const T __attribute__((address_space(1))) *)p)[i];
+}
+typedef double pair_d2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ double2 gload2(const double2 *p, long long i) {
+  const pair_d2 v = ((const pair_d2 __attribute__((address_space(1))) *)p)[i];
+  return make_double2(v.x, v.y);
+}
 
 template <int KIND, int R>
 struct PairShape {
@@ -106,17 +119,17 @@ struct PairRaw {
   double2 z;
   double w, nx, ny, mu[S::COMPS * R];
   __device__ __forceinline__ void load(const PairSources &a, int kk) {
-    z = a.xy[kk];
-    w = a.w[kk];
+    z = gload2(a.xy, kk);
+    w = gload(a.w, kk);
     if (S::DL) {
-      nx = a.nx[kk];
-      ny = a.ny[kk];
+      nx = gload(a.nx, kk);
+      ny = gload(a.ny, kk);
     }
 #pragma unroll
     for (int r = 0; r < R; ++r)
 #pragma unroll
       for (int c = 0; c < S::COMPS; ++c)
-        mu[r * S::COMPS + c] = a.mu[(size_t)r * a.len + (size_t)S::COMPS * kk + c];
+        mu[r * S::COMPS + c] = gload(a.mu, (long long)r * a.len + (long long)S::COMPS * kk + c);
   }
   __device__ __forceinline__ void store(double scale, bool valid, double *buf, int stride, int t) const {
     const double away = valid ? 0.0 : 16.0;  // the geometry's scaled diameter lies in [1, 2)
@@ -132,7 +145,7 @@ struct PairRaw {
   }
 };
 
-// Split sweep over the sources [sp per, (sp + 1) per) for one tile of targets.
+// Pair sweep of one tile of targets over a range of sources.
 constexpr int kSweepT = 2;                // targets per lane
 constexpr int kSweepTile = 64 * kSweepT;  // targets per workgroup
 constexpr int kStage = kBlock;            // sources staged at a time: one per thread
@@ -146,27 +159,27 @@ constexpr int kSweepLds = PairShape<KIND, R>::ARR * kStage > 4 * kSweepTile * Pa
                               ? PairShape<KIND, R>::ARR * kStage
                               : 4 * kSweepTile * PairShape<KIND, R>::V;
 
-// A workgroup of kBlock threads; buf: kSweepLds doubles of LDS. Wave w takes the quads w, w + 4, ...
+// Targets i0 .. min(i0 + kSweepTile, i1) - 1, sources k0 .. k1 - 1 (k1 > k0); raw sums to
+// out[r][target comp] (of len entries each). A workgroup of kBlock threads; buf: kSweepLds doubles
+// of LDS. Wave w takes the quads w, w + 4, ...
 // of each staged block; the four waves' sums are added in wave order through LDS. Blocks that
 // hold one of the tile's own nodes (a uniform test) mask the pair of a node with itself.
 template <int KIND, int R>
-__device__ __forceinline__ void pair_sweep_tile(int M, int per, int tile, int sp,
+__device__ __forceinline__ void pair_sweep_tile(int i0, int i1, int k0, int k1,
                                                 const PairSources &src, double factor,
-                                                double *__restrict__ partial, double *buf) {
+                                                double *__restrict__ out, double *buf) {
   using P = PairShape<KIND, R>;
-  const int i0 = tile * kSweepTile;
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int k0 = sp * per, k1 = min(k0 + per, M);
   double tx[kSweepT], ty[kSweepT], nx[kSweepT], ny[kSweepT], acc[kSweepT][P::V];
 #pragma unroll
   for (int u = 0; u < kSweepT; ++u) {
-    const int i = min(i0 + lane + 64 * u, M - 1);
-    const double2 z = src.xy[i];
+    const int i = min(i0 + lane + 64 * u, i1 - 1);
+    const double2 z = gload2(src.xy, i);
     tx[u] = z.x * src.scale;
     ty[u] = z.y * src.scale;
-    nx[u] = P::DL ? 0.0 : src.nx[i];
-    ny[u] = P::DL ? 0.0 : src.ny[i];
+    nx[u] = P::DL ? 0.0 : gload(src.nx, i);
+    ny[u] = P::DL ? 0.0 : gload(src.ny, i);
 #pragma unroll
     for (int v = 0; v < P::V; ++v) acc[u][v] = 0.0;
   }
@@ -201,18 +214,18 @@ __device__ __forceinline__ void pair_sweep_tile(int M, int per, int tile, int sp
   constexpr int kOut = KIND == kPairLap ? R : P::V;  // values per target after the normal component
   for (int e = t; e < kSweepTile * kOut; e += kBlock) {
     const int j = e % kSweepTile, v = e / kSweepTile, i = i0 + j;
-    if (i >= M) continue;
+    if (i >= i1) continue;
     auto sum = [&](int c) {
       const double *b = buf + c * kSweepTile + j;
       constexpr int w = P::V * kSweepTile;
       return (b[0] + b[w]) + (b[2 * w] + b[3 * w]);
     };
     if constexpr (KIND == kPairLap && R == 1) {
-      partial[(size_t)sp * M + i] = f * (src.nx[i] * sum(0) + src.ny[i] * sum(1));
+      out[i] = f * (src.nx[i] * sum(0) + src.ny[i] * sum(1));
     } else if constexpr (P::STK) {
-      partial[((size_t)sp * R + v / 2) * 2 * M + 2 * i + (v & 1)] = f * sum(v);
+      out[(v / 2) * src.len + 2 * i + (v & 1)] = f * sum(v);
     } else {
-      partial[((size_t)sp * R + v) * M + i] = f * sum(v);
+      out[v * src.len + i] = f * sum(v);
     }
   }
 }

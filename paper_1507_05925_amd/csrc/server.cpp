@@ -250,8 +250,8 @@ int bie_server::cycle() {
   MultiPlan **planp = &plan;
   {
     const std::vector<MultiItem> mi = L1.items;
-    ss.apply = [mi, planp, N](int precision, const double *in, double *out, hipStream_t st) {
-      return multi_apply(*planp, mi, std::vector<char>(mi.size(), 1), precision, in, out, N, st);
+    ss.apply = [mi, planp](int precision, const double *in, double *out, hipStream_t st) {
+      return multi_apply(*planp, mi, std::vector<char>(mi.size(), 1), precision, in, out, st);
     };
   }
   // ---- true residual with the float64 operator; retire converged requests -------------------
@@ -358,9 +358,8 @@ int bie_server::cycle() {
     std::vector<int> first(mi.size() + 1, 0);
     for (size_t q = 0; q <= mi.size(); ++q) first[q] = sys0[L2.first[q]];
     SysSet *ssp = &ss;
-    const long long N2 = L2.total;
     double *pu = R;
-    ss.apply = [mi, planp, N2, first, ssp, pc_items, pc_n, pc_lds, pc_blocks, pc_macs, pu](
+    ss.apply = [mi, planp, first, ssp, pc_items, pc_n, pc_lds, pc_blocks, pc_macs, pu](
                    int precision, const double *in, double *out, hipStream_t st) {
       if (pc_items) {
         BIE_TRY(pc_apply_batch(pc_n, pc_items, pc_lds, pc_blocks, pc_macs, in, pu, st));
@@ -373,7 +372,7 @@ int bie_server::cycle() {
           for (int q = first[i]; q < first[i + 1]; ++q) a |= ssp->active[q];
           act[i] = a;
         }
-      return multi_apply(*planp, mi, act, precision, in, out, N2, st);
+      return multi_apply(*planp, mi, act, precision, in, out, st);
     };
   }
   int iters = 0, applies = 0;
