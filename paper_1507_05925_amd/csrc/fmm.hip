@@ -31,6 +31,7 @@
 #include <vector>
 
 #include "internal.h"
+#include "pairs.h"
 
 namespace bie {
 
@@ -125,21 +126,13 @@ __device__ inline V cfma(V a, V b, V c) {  // a*b + c
   return r;
 }
 
-__device__ inline double rcp64(double a) {
-  const double y = __builtin_amdgcn_rcp(a);
-  const double e = fma(-a, y, 1.0);
-  return fma(y, e, y);
-}
-
 // Source strengths s = w mu (written to s64 in node order, as the epilogue reads them) and, in
 // sorted order, the charges: Laplace set r is (s, 0) (in float when Qf is given); Stokes sets 3r,
-// 3r+1, 3r+2 are rho, conj(rho), rho conj(z). Also the near-field source records
-// S4[r][j] = (x, y, s, 0), resp. (x, y, rho), always in float64.
+// 3r+1, 3r+2 are rho, conj(rho), rho conj(z). The near field reads its strengths from sets r, 3r.
 __global__ void k_gather(int M, int R, int kind, const int *__restrict__ perm,
                          const double2 *__restrict__ xs, const double *__restrict__ wq,
                          const double *__restrict__ mu, double *__restrict__ s64,
-                         double2 *__restrict__ Q, float2 *__restrict__ Qf,
-                         double4 *__restrict__ S4) {
+                         double2 *__restrict__ Q, float2 *__restrict__ Qf) {
   const int j = blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= M) return;
   const int k = perm[j];
@@ -153,7 +146,6 @@ __global__ void k_gather(int M, int R, int kind, const int *__restrict__ perm,
         Qf[(size_t)r * M + j] = make_float2((float)v, 0.0f);
       else
         Q[(size_t)r * M + j] = make_double2(v, 0.0);
-      S4[(size_t)r * M + j] = make_double4(z.x, z.y, v, 0.0);
     } else {
       const double2 rho = make_double2(wk * mu[(size_t)r * 2 * M + 2 * k],
                                        wk * mu[(size_t)r * 2 * M + 2 * k + 1]);
@@ -162,7 +154,6 @@ __global__ void k_gather(int M, int R, int kind, const int *__restrict__ perm,
       Q[(size_t)(3 * r) * M + j] = rho;
       Q[(size_t)(3 * r + 1) * M + j] = make_double2(rho.x, -rho.y);
       Q[(size_t)(3 * r + 2) * M + j] = cmul(rho, make_double2(z.x, -z.y));
-      S4[(size_t)r * M + j] = make_double4(z.x, z.y, rho.x, rho.y);
     }
   }
 }
@@ -664,107 +655,166 @@ __device__ inline V eval_value(const V *b, V w) {
 }
 
 // Near field. The neighbour leaves of a leaf (itself included) form a few runs of consecutive
-// sorted nodes, whose source records (x, y, s, 0) or (x, y, rho) are the same for all targets of
-// the leaf. A workgroup of four waves takes a chunk of up to 64 targets of one leaf: wave w holds
-// targets 16 w .. 16 w + 15 of the chunk (lane % 16), and lane group g = lane / 16 takes the
-// records g, g + 4, g + 8, ... of the staged records, so a leaf of n targets keeps ceil(n / 16)
-// waves busy with 16 lanes per target row instead of one wave with n of 64 lanes. The four
-// groups' sums are added at the end in a fixed order.
+// sorted nodes, whose coordinates and strengths are the same for all targets of the leaf. A
+// workgroup of four waves takes a chunk of up to 64 targets of one leaf and R right-hand sides:
+// wave w holds targets 16 w .. 16 w + 15 of the chunk (lane % 16), and lane group g = lane / 16
+// takes the quads g, g + 4, ... of the staged sources, so a leaf of n targets keeps ceil(n / 16)
+// waves busy with 16 lanes per target row instead of one wave with n of 64 lanes. The four groups'
+// sums are added at the end in a fixed order.
 //
-// No pair is masked. The pair of a target with itself has r = 0 exactly (its record holds the
-// same coordinates): |r|^2 is raised to kSelfFloor, far below the square of any distance between
-// two nodes, so the factor stays finite and the pair adds r times it, i.e. zero. Staged segments
-// are padded to a multiple of 32 records with zero-weight records far away, which add zero too.
-constexpr double kSelfFloor = 1e-100;
-constexpr double kNearPad = 1e50;  // coordinates of a padding record
+// What bounds it: the vector rate (it shares the float64 pipeline with the M2L's products) and the
+// LDS return path, 128 B per clock and compute unit. So the staged values are separate arrays
+// (24 B per Laplace source and lane; records of 32 B, a quarter of them padding, needed 64 LDS
+// clocks per 64-lane step of all four SIMDs, as long as the step's arithmetic), four pairs share a
+// reciprocal (rcp4 of pairs.h), and right-hand sides share their pairs' geometry. No pair is
+// masked: the pair of a target with itself has r = 0 exactly, and |r|^2 carries an offset far below
+// the square of any distance between two nodes (near_floor, added in the multiply-add that forms
+// |r|^2), so the pair adds r times a finite factor, i.e. zero.
+// In float64 pairs are as in pairs.h; in float32 (the near field of the mixed-precision applies)
+// coordinates are relative to the chunk's first target (one float64 difference, rounded once),
+// pair terms and the sums of eight sources are float32, and those are added into float64: the
+// float32 rounding of r stays at eps32 times the neighbourhood's size rather than the geometry's.
+// Lengths are scaled by the geometry's diameter (bie_geom::pair_scale). Sources that pad a staged
+// block have no strength and lie well outside the geometry.
+constexpr double kNearPad = 16.0;
+template <class T>
+constexpr T near_floor = std::is_same<T, double>::value ? (T)1e-60 : (T)1e-30;
+template <class T, int R>
+constexpr int near_occupancy = R > 1 ? 3 : std::is_same<T, double>::value ? 5 : 6;
 
-// One step over the eight records rec (this lane's group). The reciprocals of |r|^2 are formed
-// two at a time from one reciprocal of their product, 1/a = b / (ab) and 1/b = a / (ab): the
-// quarter-rate reciprocal is issued once per two pairs. |r|^2 lies in [kSelfFloor, about
-// 2 kNearPad^2], so ab stays within the float64 range.
-template <bool STOKES>
-__device__ __forceinline__ void near_step(const double4 *rec, double2 z, double2 nv, double &gx,
-                                          double &gy) {
-#pragma unroll
-  for (int u = 0; u < 8; u += 2) {
-    const double dx0 = z.x - rec[u].x, dy0 = z.y - rec[u].y;
-    const double dx1 = z.x - rec[u + 1].x, dy1 = z.y - rec[u + 1].y;
-    const double a = fmax(fma(dx0, dx0, dy0 * dy0), kSelfFloor);
-    const double b = fmax(fma(dx1, dx1, dy1 * dy1), kSelfFloor);
-    const double y = rcp64(a * b);
-    const double inv0 = b * y, inv1 = a * y;
-    double t0, t1;
-    if (STOKES) {
-      const double rn0 = fma(dx0, nv.x, dy0 * nv.y), rn1 = fma(dx1, nv.x, dy1 * nv.y);
-      t0 = fma(dx0, rec[u].z, dy0 * rec[u].w) * rn0 * (inv0 * inv0);
-      t1 = fma(dx1, rec[u + 1].z, dy1 * rec[u + 1].w) * rn1 * (inv1 * inv1);
-    } else {
-      t0 = rec[u].z * inv0;
-      t1 = rec[u + 1].z * inv1;
-    }
-    gx = fma(dx0, t0, gx);
-    gy = fma(dy0, t0, gy);
-    gx = fma(dx1, t1, gx);
-    gy = fma(dy1, t1, gy);
-  }
-}
+template <bool STK, int R>
+struct NearShape {
+  static constexpr int C = STK ? 2 : 1;
+  static constexpr int V = STK ? 2 * R : (R == 1 ? 2 : R);  // sums per target
+  static constexpr int ARR = 2 + C * R;                      // staged arrays
+};
 
-// Sum over the staged records at LDS positions [0, n) (n a multiple of 32): this lane's group
-// reads positions g, g + 4, ... by LDS broadcast (four addresses per read, one per group), eight
-// per step.
-template <bool STOKES>
-__device__ __forceinline__ void near_seg(const double4 *buf, int n, int g, double2 z, double2 nv,
-                                         double &gx, double &gy) {
-  for (int k = 0; k < n; k += 32) {
-    double4 rec[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) rec[u] = buf[k + 4 * u + g];
-    near_step<STOKES>(rec, z, nv, gx, gy);
-  }
-}
-
-// LDS records per workgroup (a multiple of 32). A leaf whose runs hold at most this many records
+// LDS sources per workgroup (a multiple of 32). A leaf whose runs hold at most this many sources
 // (after padding) has them all staged at once, back to back: one load latency and one barrier.
 // Larger neighbourhoods are read run by run in blocks of this size.
 constexpr int kNearCap = 512;
 
-// Copies n records src[0 .. n) to buf[at ..], then zero-weight padding up to a multiple of 32
-// records; returns the padded count.
-__device__ __forceinline__ int near_stage(const double4 *__restrict__ src, int n, double4 *buf,
-                                          int at) {
-  const int np = (n + 31) & ~31;
-  for (int t = threadIdx.x; t < np; t += blockDim.x)
-    buf[at + t] = t < n ? src[t] : make_double4(kNearPad, kNearPad, 0.0, 0.0);
-  return np;
+// Adds the quad of staged sources at position k to one target's sums.
+template <class T, bool STK, int R>
+__device__ __forceinline__ void near_quad(const T *buf, int k, T zx, T zy, T nx, T ny,
+                                          T (&acc)[NearShape<STK, R>::V]) {
+  T dx[4], dy[4], rr[4], inv[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    dx[u] = zx - buf[k + u];
+    dy[u] = zy - buf[kNearCap + k + u];
+    rr[u] = fma(dx[u], dx[u], fma(dy[u], dy[u], near_floor<T>));
+  }
+  if constexpr (std::is_same<T, double>::value) {
+    rcp4(rr, inv);
+  } else {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) inv[u] = __builtin_amdgcn_rcpf(rr[u]);
+  }
+  const T *st = buf + 2 * kNearCap + k;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if constexpr (!STK && R == 1) {
+      const T t = st[u] * inv[u];
+      acc[0] = fma(dx[u], t, acc[0]);
+      acc[1] = fma(dy[u], t, acc[1]);
+    } else {
+      const T a = fma(dx[u], nx, dy[u] * ny) * inv[u];
+      if constexpr (STK) {
+        const T b = a * inv[u];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const T c = fma(dx[u], st[2 * r * kNearCap + u], dy[u] * st[(2 * r + 1) * kNearCap + u]) * b;
+          acc[2 * r] = fma(c, dx[u], acc[2 * r]);
+          acc[2 * r + 1] = fma(c, dy[u], acc[2 * r + 1]);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r] = fma(a, st[r * kNearCap + u], acc[r]);
+      }
+    }
+  }
 }
 
-// Near field: grid (target chunks, R), 256 threads. Laplace writes -(1/2pi) n.(sum over the
+// Sum over the staged sources [0, n) (n a multiple of 32), eight of this lane's per step.
+template <class T, bool STK, int R>
+__device__ __forceinline__ void near_block(const T *buf, int n, int g, T zx, T zy, T nx, T ny,
+                                           double (&acc)[NearShape<STK, R>::V]) {
+  constexpr int V = NearShape<STK, R>::V;
+  for (int k = 0; k < n; k += 32) {
+    T sum[V];
+    if constexpr (std::is_same<T, double>::value) {
+#pragma unroll
+      for (int v = 0; v < V; ++v) sum[v] = acc[v];
+    } else {
+#pragma unroll
+      for (int v = 0; v < V; ++v) sum[v] = (T)0;
+    }
+    near_quad<T, STK, R>(buf, k + 4 * g, zx, zy, nx, ny, sum);
+    near_quad<T, STK, R>(buf, k + 16 + 4 * g, zx, zy, nx, ny, sum);
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      if constexpr (std::is_same<T, double>::value) acc[v] = sum[v];
+      else acc[v] += (double)sum[v];
+    }
+  }
+}
+
+// Grid (target chunks, right-hand sides / R), 256 threads. Laplace writes -(1/2pi) n.(sum over the
 // neighbour leaves, k != i, of s_k r/|r|^2); Stokes writes -(1/pi) sum over the neighbour leaves,
 // k != i, of (r.n)(r.rho_k) r/|r|^4 (two components per node). Waves without targets (busy false,
-// uniform over the wave) take part in the copies and barriers only. At least five waves per
-// SIMD (at most 102 VGPRs instead of 104): the kernel shares the compute units with the
-// expansion chain, and its smaller register footprint leaves room for the chain's waves.
-// Chunks are taken in XCD-contiguous order (xcd_item): neighbouring leaves, which stage mostly
-// the same source records, then run on one XCD and share its L2.
-template <bool STOKES>
-__global__ __launch_bounds__(256, 5) void k_near(
-    int M, const int *__restrict__ leaf_start, const double2 *__restrict__ xs,
+// uniform over the wave) take part in the copies and barriers only. For one right-hand side at
+// least five (float32: six) waves per SIMD: the kernel shares the compute units with the expansion
+// chain, and its smaller register footprint leaves room for the chain's waves. Chunks are taken
+// in XCD-contiguous order (xcd_item): neighbouring leaves, which stage mostly the same sources,
+// then run on one XCD and share its L2. q: the charge sets, set r (Laplace) or 3 r (Stokes).
+template <class T, bool STK, int R, class QT>
+__global__ __launch_bounds__(256, (near_occupancy<T, R>)) void k_near(
+    int M, double scale, const int *__restrict__ leaf_start, const double2 *__restrict__ xs,
     const double2 *__restrict__ nrm, const int *__restrict__ perm,
     const int *__restrict__ run_ptr, const int2 *__restrict__ run,
     const int *__restrict__ chunk_leaf, const int *__restrict__ chunk_start,
-    const double4 *__restrict__ S4, double *__restrict__ out) {
+    const QT *__restrict__ q, double *__restrict__ out) {
+  using N = NearShape<STK, R>;
+  constexpr bool F32 = std::is_same<T, float>::value;
   const int cb = xcd_item(blockIdx.x, gridDim.x);
-  const int leaf = chunk_leaf[cb], r = blockIdx.y;
+  const int leaf = chunk_leaf[cb], r0 = blockIdx.y * R;
   const int j1 = leaf_start[leaf + 1];
   const int lane = threadIdx.x & 63, g = lane >> 4;
   const int t0 = chunk_start[cb] + 16 * (threadIdx.x >> 6);  // the wave's first target
   const int j = t0 + (lane & 15);
   const bool valid = j < j1, busy = t0 < j1;
-  const int jj = valid ? j : t0;
-  const double2 z = xs[min(jj, M - 1)], nv = nrm[min(jj, M - 1)];
-  const double4 *src = S4 + (size_t)r * M;
-  __shared__ double4 buf[kNearCap];
-  double gx = 0.0, gy = 0.0;
+  const int jj = valid ? j : chunk_start[cb];
+  const double2 o = F32 ? xs[chunk_start[cb]] : make_double2(0.0, 0.0);
+  const double2 z = xs[jj], nv = nrm[jj];
+  const T zx = (T)((z.x - o.x) * scale), zy = (T)((z.y - o.y) * scale);
+  const T nx = (T)nv.x, ny = (T)nv.y;
+  __shared__ T buf[N::ARR * kNearCap];
+  double acc[N::V];
+#pragma unroll
+  for (int v = 0; v < N::V; ++v) acc[v] = 0.0;
+  // stages sources j .. j + n - 1 at positions at .. at + n - 1
+  auto stage = [&](int from, int n, int at) {
+    for (int t = threadIdx.x; t < n; t += 256) {
+      const double2 c = xs[from + t];
+      buf[at + t] = (T)((c.x - o.x) * scale);
+      buf[kNearCap + at + t] = (T)((c.y - o.y) * scale);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const QT s = q[(size_t)(r0 + r) * (STK ? 3 : 1) * M + from + t];
+        buf[(2 + N::C * r) * kNearCap + at + t] = (T)s.x;
+        if (STK) buf[(3 + N::C * r) * kNearCap + at + t] = (T)s.y;
+      }
+    }
+  };
+  auto pad = [&](int from, int to) {
+    for (int t = from + threadIdx.x; t < to; t += 256) {
+      buf[t] = (T)kNearPad;
+      buf[kNearCap + t] = (T)kNearPad;
+#pragma unroll
+      for (int e = 2; e < N::ARR; ++e) buf[e * kNearCap + t] = (T)0;
+    }
+  };
   const int e0 = run_ptr[leaf], e1 = run_ptr[leaf + 1];
   int total = 0;
   for (int e = e0; e < e1; ++e) total += run[e].y - run[e].x;
@@ -773,160 +823,43 @@ __global__ __launch_bounds__(256, 5) void k_near(
     int at = 0;
     for (int e = e0; e < e1; ++e) {
       const int2 kr = run[e];
-      const int n = kr.y - kr.x;
-      for (int t = threadIdx.x; t < n; t += blockDim.x) buf[at + t] = src[kr.x + t];
-      at += n;
+      stage(kr.x, kr.y - kr.x, at);
+      at += kr.y - kr.x;
     }
-    for (int t = total + threadIdx.x; t < padded; t += blockDim.x)
-      buf[t] = make_double4(kNearPad, kNearPad, 0.0, 0.0);
+    pad(total, padded);
     __syncthreads();
-    if (busy) near_seg<STOKES>(buf, padded, g, z, nv, gx, gy);
+    if (busy) near_block<T, STK, R>(buf, padded, g, zx, zy, nx, ny, acc);
   } else {
     for (int e = e0; e < e1; ++e) {
       const int2 kr = run[e];
       for (int base = kr.x; base < kr.y; base += kNearCap) {
         __syncthreads();  // the previous block is no longer read
-        const int n = near_stage(src + base, min(kNearCap, kr.y - base), buf, 0);
+        const int n = min(kNearCap, kr.y - base), np = (n + 31) & ~31;
+        stage(base, n, 0);
+        pad(n, np);
         __syncthreads();
-        if (busy) near_seg<STOKES>(buf, n, g, z, nv, gx, gy);
+        if (busy) near_block<T, STK, R>(buf, np, g, zx, zy, nx, ny, acc);
       }
     }
   }
-  gx += __shfl_xor(gx, 16, 64);
-  gy += __shfl_xor(gy, 16, 64);
-  gx += __shfl_xor(gx, 32, 64);
-  gy += __shfl_xor(gy, 32, 64);
+#pragma unroll
+  for (int v = 0; v < N::V; ++v) {
+    acc[v] += __shfl_xor(acc[v], 16, 64);
+    acc[v] += __shfl_xor(acc[v], 32, 64);
+  }
   if (!valid || g != 0) return;
   const int i = perm[j];
-  if (STOKES) {
-    out[(size_t)r * 2 * M + 2 * i] = -gx / kPi;
-    out[(size_t)r * 2 * M + 2 * i + 1] = -gy / kPi;
-  } else {
-    out[(size_t)r * M + i] = -(nv.x * gx + nv.y * gy) / (2.0 * kPi);
-  }
-}
-
-// Float32 near field of the mixed-precision applies: k_near's neighbour lists,
-// chunks and summation pattern, with the staged records converted to float32 coordinates
-// relative to the chunk's first target (one float64 difference, rounded once, so a target and its
-// own record still give r = 0 exactly) and float32 pair terms; each lane adds its eight-record
-// partial sums into float64 accumulators. Coordinates relative to a point of the leaf keep the
-// float32 rounding of r at eps32 times the neighbourhood size rather than the geometry's.
-constexpr float kSelfFloor32 = 1e-20f;  // |r|^2 floor (self pair): s / floor stays finite
-constexpr float kNearPad32 = 1e18f;     // padding record coordinates: |r|^2 stays finite
-
-// Stokes (STOKES): records (x, y, rho_x, rho_y) and the term (r.n)(r.rho) r/|r|^4, formed as
-// (((r.rho)(r.n)) / |r|^2) / |r|^2 so that the self pair, whose r.rho is 0, gives 0 and not 0
-// times an overflowed square of the floored reciprocal.
-template <bool STOKES>
-__device__ __forceinline__ void near_seg32(const float4 *buf, int n, int g, float2 z, float2 nv,
-                                           double &gx, double &gy) {
-  for (int k = 0; k < n; k += 32) {
-    float4 rec[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) rec[u] = buf[k + 4 * u + g];
-    float sx = 0.0f, sy = 0.0f;
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const float dx = z.x - rec[u].x, dy = z.y - rec[u].y;
-      const float inv = __builtin_amdgcn_rcpf(fmaxf(fmaf(dx, dx, dy * dy), kSelfFloor32));
-      float t;
-      if (STOKES) {
-        const float rn = fmaf(dx, nv.x, dy * nv.y);
-        t = ((fmaf(dx, rec[u].z, dy * rec[u].w) * rn) * inv) * inv;
-      } else {
-        t = rec[u].z * inv;
-      }
-      sx = fmaf(dx, t, sx);
-      sy = fmaf(dy, t, sy);
+  for (int r = 0; r < R; ++r) {
+    if constexpr (STK) {
+      double *u = out + (size_t)(r0 + r) * 2 * M + 2 * (size_t)i;
+      u[0] = -(scale / kPi) * acc[2 * r];
+      u[1] = -(scale / kPi) * acc[2 * r + 1];
+    } else if constexpr (R == 1) {
+      out[(size_t)r0 * M + i] = -(scale / (2.0 * kPi)) * (nv.x * acc[0] + nv.y * acc[1]);
+    } else {
+      out[(size_t)(r0 + r) * M + i] = -(scale / (2.0 * kPi)) * acc[r];
     }
-    gx += (double)sx;
-    gy += (double)sy;
-  }
-}
-
-// Stages n records src[0 .. n) at buf[at ..] relative to o, then padding up to a multiple of 32
-// (the fourth component: rho_y for Stokes, 0 for Laplace).
-template <bool STOKES>
-__device__ __forceinline__ int near_stage32(const double4 *__restrict__ src, int n, float4 *buf,
-                                            int at, double2 o) {
-  const int np = (n + 31) & ~31;
-  for (int t = threadIdx.x; t < np; t += blockDim.x) {
-    float4 v = make_float4(kNearPad32, kNearPad32, 0.0f, 0.0f);
-    if (t < n) {
-      const double4 r = src[t];
-      v = make_float4((float)(r.x - o.x), (float)(r.y - o.y), (float)r.z,
-                      STOKES ? (float)r.w : 0.0f);
-    }
-    buf[at + t] = v;
-  }
-  return np;
-}
-
-template <bool STOKES>
-__global__ __launch_bounds__(256, 6) void k_near_f32(
-    int M, const int *__restrict__ leaf_start, const double2 *__restrict__ xs,
-    const double2 *__restrict__ nrm, const int *__restrict__ perm,
-    const int *__restrict__ run_ptr, const int2 *__restrict__ run,
-    const int *__restrict__ chunk_leaf, const int *__restrict__ chunk_start,
-    const double4 *__restrict__ S4, double *__restrict__ out) {
-  const int cb = xcd_item(blockIdx.x, gridDim.x);
-  const int leaf = chunk_leaf[cb], r = blockIdx.y;
-  const int j1 = leaf_start[leaf + 1];
-  const int lane = threadIdx.x & 63, g = lane >> 4;
-  const int t0 = chunk_start[cb] + 16 * (threadIdx.x >> 6);  // the wave's first target
-  const int j = t0 + (lane & 15);
-  const bool valid = j < j1, busy = t0 < j1;
-  const int jj = valid ? j : t0;
-  const double2 o = xs[chunk_start[cb]];  // origin of the chunk's float32 coordinates
-  const double2 zd = xs[min(jj, M - 1)], nv = nrm[min(jj, M - 1)];
-  const float2 z = make_float2((float)(zd.x - o.x), (float)(zd.y - o.y));
-  const float2 nvf = make_float2((float)nv.x, (float)nv.y);
-  const double4 *src = S4 + (size_t)r * M;
-  __shared__ float4 buf[kNearCap];
-  double gx = 0.0, gy = 0.0;
-  const int e0 = run_ptr[leaf], e1 = run_ptr[leaf + 1];
-  int total = 0;
-  for (int e = e0; e < e1; ++e) total += run[e].y - run[e].x;
-  if (((total + 31) & ~31) <= kNearCap) {  // the runs back to back, one padding at the end
-    int at = 0;
-    for (int e = e0; e < e1; ++e) {
-      const int2 kr = run[e];
-      const int n = kr.y - kr.x;
-      for (int t = threadIdx.x; t < n; t += blockDim.x) {
-        const double4 v = src[kr.x + t];
-        buf[at + t] = make_float4((float)(v.x - o.x), (float)(v.y - o.y), (float)v.z,
-                                  STOKES ? (float)v.w : 0.0f);
-      }
-      at += n;
-    }
-    const int padded = (total + 31) & ~31;
-    for (int t = total + threadIdx.x; t < padded; t += blockDim.x)
-      buf[t] = make_float4(kNearPad32, kNearPad32, 0.0f, 0.0f);
-    __syncthreads();
-    if (busy) near_seg32<STOKES>(buf, padded, g, z, nvf, gx, gy);
-  } else {
-    for (int e = e0; e < e1; ++e) {
-      const int2 kr = run[e];
-      for (int base = kr.x; base < kr.y; base += kNearCap) {
-        __syncthreads();  // the previous block is no longer read
-        const int n = near_stage32<STOKES>(src + base, min(kNearCap, kr.y - base), buf, 0, o);
-        __syncthreads();
-        if (busy) near_seg32<STOKES>(buf, n, g, z, nvf, gx, gy);
-      }
-    }
-  }
-  gx += __shfl_xor(gx, 16, 64);
-  gy += __shfl_xor(gy, 16, 64);
-  gx += __shfl_xor(gx, 32, 64);
-  gy += __shfl_xor(gy, 32, 64);
-  if (!valid || g != 0) return;
-  const int i = perm[j];
-  if (STOKES) {
-    out[(size_t)r * 2 * M + 2 * i] = -gx / kPi;
-    out[(size_t)r * 2 * M + 2 * i + 1] = -gy / kPi;
-  } else {
-    out[(size_t)r * M + i] = -(nv.x * gx + nv.y * gy) / (2.0 * kPi);
   }
 }
 
@@ -1938,6 +1871,23 @@ void upward_pass(const FmmTree &t, int kind, int nsets, double ih_leaf, const cx
   m2m_passes<P, T>(t, nsets, Mexp, s);
 }
 
+template <class T, bool STK, int R, class QT>
+void launch_near_group(const FmmTree &t, int groups, double scale, const QT *q, double *out,
+                       hipStream_t s) {
+  hipLaunchKernelGGL((k_near<T, STK, R, QT>), dim3(t.nchunk, groups), dim3(256), 0, s, t.M, scale,
+                     t.leaf_start, t.xs, t.nrm, t.perm, t.run_ptr, t.run, t.chunk_leaf,
+                     t.chunk_start, q, out);
+}
+
+// The near field of R right-hand sides, four (Laplace) or two (Stokes) at a time where there are as
+// many: more would need more LDS and registers than the expansion chain leaves.
+template <class T, bool STK, class QT>
+void near_pass(const FmmTree &t, int R, double scale, const QT *q, double *out, hipStream_t s) {
+  if (!STK && R % 4 == 0) launch_near_group<T, STK, STK ? 2 : 4>(t, R / 4, scale, q, out, s);
+  else if (R % 2 == 0) launch_near_group<T, STK, 2>(t, R / 2, scale, q, out, s);
+  else launch_near_group<T, STK, 1>(t, R, scale, q, out, s);
+}
+
 constexpr int kNearAtF32 = 0;
 
 template <int P, class T, class Near>
@@ -2109,8 +2059,7 @@ long long fmm_state_bytes(const bie_geom *g, int kind, int precision, int order,
       }
     }
     if (tree == 0) tree = 96LL * g->M + 1024LL * nbox + 16LL * 8 * p * p;
-    total += tree + (long long)R * g->M * 32 +
-             (long long)((size_t)nsets * g->M + 2 * (size_t)nsets * nbox * p) * (long long)csz +
+    total += tree + (long long)((size_t)nsets * g->M + 2 * (size_t)nsets * nbox * p) * (long long)csz +
              (kind == 0 ? (long long)R * g->N * 8 + 64 : 0) + 512;
   }
   return total;
@@ -2131,15 +2080,13 @@ int fmm_far_field(bie_geom *g, int kind, int precision, int R, const double *mu,
   // apply is float32)
   const bool f32 = precision == BIE_MIXED && kind == 0;
   const size_t csz = f32 ? sizeof(float2) : sizeof(double2);
-  // work: near-field source records S4 [R][M] (32 B), charges Q [nsets][M], multipoles and
-  // locals [nsets][nbox][p]
+  // work: charges Q [nsets][M], multipoles and locals [nsets][nbox][p]
   // (and, when the evaluation finishes the apply, the body charges [R][N])
   const bool fuse = finish && kind == 0;
-  const size_t need = (size_t)R * M * 32 + ((size_t)nsets * M + 2 * (size_t)nsets * t.nbox * p) * csz +
+  const size_t need = ((size_t)nsets * M + 2 * (size_t)nsets * t.nbox * p) * csz +
                       (fuse ? (size_t)R * g->N * 8 + 64 : 0) + 512;
   BIE_TRY(t.work.reserve(need));
-  double4 *S4 = t.work.as<double4>();
-  char *wq = reinterpret_cast<char *>(S4 + (size_t)R * M);
+  char *wq = t.work.as<char>();
   char *wm = wq + (size_t)nsets * M * csz;
   char *wl = wm + (size_t)nsets * t.nbox * p * csz;
   double *charge = reinterpret_cast<double *>(
@@ -2162,8 +2109,8 @@ int fmm_far_field(bie_geom *g, int kind, int precision, int R, const double *mu,
   hipLaunchKernelGGL(k_gather, dim3((M + 255) / 256), dim3(256), 0, s, M, R, kind, t.perm, t.xs, g->w,
                      mu, s64,
                      f32 ? nullptr : reinterpret_cast<double2 *>(wq),
-                     f32 ? reinterpret_cast<float2 *>(wq) : nullptr, S4);
-  // the near field needs only the source records: it runs on the side stream while the
+                     f32 ? reinterpret_cast<float2 *>(wq) : nullptr);
+  // the near field needs only the charges: it runs on the side stream while the
   // expansions are built, and writes `partial`; the L2P kernels add the far part after the join
   BIE_HIP_CHECK(hipEventRecord(plan.fork, s));
   auto launch_near = [&]() -> int {
@@ -2177,21 +2124,17 @@ int fmm_far_field(bie_geom *g, int kind, int precision, int R, const double *mu,
       ProfScope pe(near32 ? BIE_K_FMM_NEAR_F32 : BIE_K_FMM_EVAL, plan.side,
                    (t.near_pairs - M) * R);
       if (kind == 0 && near32)
-        hipLaunchKernelGGL(k_near_f32<false>, dim3(t.nchunk, R), dim3(256), 0, plan.side, M,
-                           t.leaf_start, t.xs, t.nrm, t.perm, t.run_ptr, t.run, t.chunk_leaf,
-                           t.chunk_start, S4, partial);
+        near_pass<float, false>(t, R, g->pair_scale, reinterpret_cast<const float2 *>(wq), partial,
+                                plan.side);
       else if (near32)
-        hipLaunchKernelGGL(k_near_f32<true>, dim3(t.nchunk, R), dim3(256), 0, plan.side, M,
-                           t.leaf_start, t.xs, t.nrm, t.perm, t.run_ptr, t.run, t.chunk_leaf,
-                           t.chunk_start, S4, partial);
+        near_pass<float, true>(t, R, g->pair_scale, reinterpret_cast<const double2 *>(wq), partial,
+                               plan.side);
       else if (kind == 0)
-        hipLaunchKernelGGL(k_near<false>, dim3(t.nchunk, R), dim3(256), 0, plan.side, M,
-                           t.leaf_start, t.xs, t.nrm, t.perm, t.run_ptr, t.run, t.chunk_leaf,
-                           t.chunk_start, S4, partial);
+        near_pass<double, false>(t, R, g->pair_scale, reinterpret_cast<const double2 *>(wq), partial,
+                                 plan.side);
       else
-        hipLaunchKernelGGL(k_near<true>, dim3(t.nchunk, R), dim3(256), 0, plan.side, M,
-                           t.leaf_start, t.xs, t.nrm, t.perm, t.run_ptr, t.run, t.chunk_leaf,
-                           t.chunk_start, S4, partial);
+        near_pass<double, true>(t, R, g->pair_scale, reinterpret_cast<const double2 *>(wq), partial,
+                                plan.side);
       BIE_HIP_CHECK(hipGetLastError());
     }
     BIE_HIP_CHECK(hipEventRecord(plan.join, plan.side));
