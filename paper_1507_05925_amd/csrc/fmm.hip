@@ -669,23 +669,32 @@ __device__ inline V eval_value(const V *b, V w) {
 // reciprocal (rcp4 of pairs.h), and right-hand sides share their pairs' geometry. No pair is
 // masked: the pair of a target with itself has r = 0 exactly, and |r|^2 carries an offset far below
 // the square of any distance between two nodes (near_floor, added in the multiply-add that forms
-// |r|^2), so the pair adds r times a finite factor, i.e. zero.
+// |r|^2), so the pair adds r times a finite factor, i.e. zero (near_quad keeps it finite).
 // In float64 pairs are as in pairs.h; in float32 (the near field of the mixed-precision applies)
 // coordinates are relative to the chunk's first target (one float64 difference, rounded once),
 // pair terms and the sums of eight sources are float32, and those are added into float64: the
 // float32 rounding of r stays at eps32 times the neighbourhood's size rather than the geometry's.
 // Lengths are scaled by the geometry's diameter (bie_geom::pair_scale). Sources that pad a staged
 // block have no strength and lie well outside the geometry.
+//
+// Measured beside the expansion chain, against records of 32 B (float32: 16 B), a masked
+// self pair, a reciprocal per two pairs and one right-hand side per workgroup: 256,000 Laplace nodes
+// 53 -> 48 us in float64, 31 -> 27.5 us in float32; four right-hand sides of 38,400 nodes
+// 60 -> 33 us; two right-hand sides of 57,600 Stokes nodes 82 -> 70 us. A persistent grid
+// of 256 to 1280 workgroups was no faster for any of them (a whole apply 70 to 157 us against
+// 57 to 114 us): the hardware's own dispatch balances leaves of unequal size better.
 constexpr double kNearPad = 16.0;
 template <class T>
 constexpr T near_floor = std::is_same<T, double>::value ? (T)1e-60 : (T)1e-30;
 template <class T, int R>
 constexpr int near_occupancy = R > 1 ? 3 : std::is_same<T, double>::value ? 5 : 6;
 
-template <bool STK, int R>
+template <class T, bool STK, int R>
 struct NearShape {
   static constexpr int C = STK ? 2 : 1;
-  static constexpr int V = STK ? 2 * R : (R == 1 ? 2 : R);  // sums per target
+  // g.x and g.y instead of n.g: one product fewer per pair, float64 only (see near_quad)
+  static constexpr bool G = std::is_same<T, double>::value && !STK && R == 1;
+  static constexpr int V = STK ? 2 * R : G ? 2 : R;  // sums per target
   static constexpr int ARR = 2 + C * R;                      // staged arrays
 };
 
@@ -694,10 +703,13 @@ struct NearShape {
 // Larger neighbourhoods are read run by run in blocks of this size.
 constexpr int kNearCap = 512;
 
-// Adds the quad of staged sources at position k to one target's sums.
+// Adds the quad of staged sources at position k to one target's sums. The reciprocal of a target's
+// pair with itself is 1 / near_floor: in float32 it multiplies r.n (zero) before any strength,
+// whose product with 1e30 would overflow from 3e8 on and make that pair infinity times zero. In
+// float64 the product with 1e60 has room for strengths up to 1e248.
 template <class T, bool STK, int R>
 __device__ __forceinline__ void near_quad(const T *buf, int k, T zx, T zy, T nx, T ny,
-                                          T (&acc)[NearShape<STK, R>::V]) {
+                                          T (&acc)[NearShape<T, STK, R>::V]) {
   T dx[4], dy[4], rr[4], inv[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
@@ -714,7 +726,7 @@ __device__ __forceinline__ void near_quad(const T *buf, int k, T zx, T zy, T nx,
   const T *st = buf + 2 * kNearCap + k;
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    if constexpr (!STK && R == 1) {
+    if constexpr (NearShape<T, STK, R>::G) {
       const T t = st[u] * inv[u];
       acc[0] = fma(dx[u], t, acc[0]);
       acc[1] = fma(dy[u], t, acc[1]);
@@ -739,8 +751,8 @@ __device__ __forceinline__ void near_quad(const T *buf, int k, T zx, T zy, T nx,
 // Sum over the staged sources [0, n) (n a multiple of 32), eight of this lane's per step.
 template <class T, bool STK, int R>
 __device__ __forceinline__ void near_block(const T *buf, int n, int g, T zx, T zy, T nx, T ny,
-                                           double (&acc)[NearShape<STK, R>::V]) {
-  constexpr int V = NearShape<STK, R>::V;
+                                           double (&acc)[NearShape<T, STK, R>::V]) {
+  constexpr int V = NearShape<T, STK, R>::V;
   for (int k = 0; k < n; k += 32) {
     T sum[V];
     if constexpr (std::is_same<T, double>::value) {
@@ -775,7 +787,7 @@ __global__ __launch_bounds__(256, (near_occupancy<T, R>)) void k_near(
     const int *__restrict__ run_ptr, const int2 *__restrict__ run,
     const int *__restrict__ chunk_leaf, const int *__restrict__ chunk_start,
     const QT *__restrict__ q, double *__restrict__ out) {
-  using N = NearShape<STK, R>;
+  using N = NearShape<T, STK, R>;
   constexpr bool F32 = std::is_same<T, float>::value;
   const int cb = xcd_item(blockIdx.x, gridDim.x);
   const int leaf = chunk_leaf[cb], r0 = blockIdx.y * R;
@@ -855,7 +867,7 @@ __global__ __launch_bounds__(256, (near_occupancy<T, R>)) void k_near(
       double *u = out + (size_t)(r0 + r) * 2 * M + 2 * (size_t)i;
       u[0] = -(scale / kPi) * acc[2 * r];
       u[1] = -(scale / kPi) * acc[2 * r + 1];
-    } else if constexpr (R == 1) {
+    } else if constexpr (N::G) {
       out[(size_t)r0 * M + i] = -(scale / (2.0 * kPi)) * (nv.x * acc[0] + nv.y * acc[1]);
     } else {
       out[(size_t)(r0 + r) * M + i] = -(scale / (2.0 * kPi)) * acc[r];
