@@ -124,8 +124,8 @@ __global__ __launch_bounds__(kBlock) void k_combination_nrm(
 // base is read when the kernel runs, so a captured graph of the step stays valid across
 // cycles). What bounds it is that store's latency: one wave of a workgroup of its own releases
 // its own stores, where a fence by all four waves of the system's first chunk also waited for
-// that chunk of v (34 steps of up to 8,192 unknowns in
-// several systems: 11.5 -> 5.4 us each).
+// that chunk of v (requests on 12 bodies of 96 nodes,
+// 1,152 or 2,304 unknowns per system: 11.5 -> 5.4 us per step).
 __global__ __launch_bounds__(kBlock) void k_normalize_column(
     int cnt, int C, const int *__restrict__ csys, const int *__restrict__ sys_chunk,
     const long long *__restrict__ c0, const long long *__restrict__ c1,
