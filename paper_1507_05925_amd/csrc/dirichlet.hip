@@ -111,9 +111,20 @@ __global__ __launch_bounds__(kBlock, sweep_occupancy(PairShape<KIND, R>::V)) voi
                            partial + (size_t)sp * R * src.len, buf);
 }
 
-// out = alpha (1/2 mu + diagonal limit + sum of the split partials + completion), one lane per
-// node, grid.y = density. The completion loops over all bodies (wave-uniform).
-constexpr int kEpi = 64;  // one wave per workgroup: the paper's geometries have few nodes
+// out = alpha (1/2 mu + diagonal limit + sum of the split partials + completion), grid.y = density.
+// What bounds it is latency: geometries of this path have few nodes, and a node's splits and bodies
+// (a logarithm, for Stokes also a division, each) are two serial chains. So kEpiLanes lanes share a
+// node: lane g takes the splits and the bodies g, g + kEpiLanes, ... and three shuffle steps add
+// the lanes in a fixed order (splash geometry, 3 Stokes densities: one lane per node 7.3 us,
+// eight 4.2 us).
+constexpr int kEpi = 64;  // one wave per workgroup
+constexpr int kEpiLanes = 8;
+
+__device__ __forceinline__ double epi_sum(double v) {
+#pragma unroll
+  for (int off = 1; off < kEpiLanes; off <<= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
 
 template <bool STOKES>
 __global__ __launch_bounds__(kEpi) void k_dl_epilogue(
@@ -122,55 +133,59 @@ __global__ __launch_bounds__(kEpi) void k_dl_epilogue(
     const double *__restrict__ pint, const double *__restrict__ scale, const double *__restrict__ mu,
     long long len, const double *__restrict__ partial, const double *__restrict__ mom,
     int with_C, double alpha, double *__restrict__ out) {
-  const int i = blockIdx.x * kEpi + threadIdx.x;
+  const int t = blockIdx.x * (kEpi / kEpiLanes) + threadIdx.x / kEpiLanes;
+  const int g = threadIdx.x % kEpiLanes;
+  const int i = min(t, M - 1);  // lanes past the end take part in the shuffles
   const int r = blockIdx.y;
-  if (i >= M) return;
   const double2 p = xy[i];
-  const double logR = log(scale[0]);
   const double *m = mu + (size_t)r * len;
   if (!STOKES) {
-    double c = 0.0, tot = 0.0;
+    const double mi = m[i], kw = kappa[i] * w[i];
+    double far = 0.0, c = 0.0, tot = 0.0;
+    for (int sp = g; sp < S; sp += kEpiLanes) far += partial[((size_t)sp * R + r) * len + i];
     if (with_C) {
       const double *A = mom + (size_t)r * N;
-      for (int b = 0; b < N; ++b) {
+      for (int b = g; b < N; b += kEpiLanes) {
         const double dx = p.x - pint[2 * b], dy = p.y - pint[2 * b + 1];
         c = fma(A[b], log(fma(dx, dx, dy * dy)), c);
         tot += A[b];
       }
+      c = -(0.5 * c - log(scale[0]) * tot) / (2.0 * kPi);
     }
-    const double comp = -(0.5 * c - logR * tot) / (2.0 * kPi);
-    double far = 0.0;
-    for (int sp = 0; sp < S; ++sp) far += partial[((size_t)sp * R + r) * len + i];
-    const double mi = m[i];
-    const double dg = -kappa[i] * w[i] / (4.0 * kPi) * mi;
-    out[(size_t)r * len + i] = alpha * (0.5 * mi + dg + far + comp);
+    far = epi_sum(far + c);
+    if (g == 0 && t < M)
+      out[(size_t)r * len + i] = alpha * (0.5 * mi - kw / (4.0 * kPi) * mi + far);
   } else {
-    double u1 = 0.0, u2 = 0.0;
-    if (with_C) {
-      const double *A = mom + (size_t)r * N * 3;
-      for (int b = 0; b < N; ++b) {
-        const double dx = p.x - pint[2 * b], dy = p.y - pint[2 * b + 1];
-        const double dd = fma(dx, dx, dy * dy);
-        const double inv = 1.0 / dd;
-        const double lg = 0.5 * log(dd) - logR;
-        const double a1 = A[3 * b], a2 = A[3 * b + 1], t = A[3 * b + 2];
-        const double da = fma(dx, a1, dy * a2) * inv;
-        u1 += -lg * a1 + dx * da - t * dy * inv;
-        u2 += -lg * a2 + dy * da + t * dx * inv;
-      }
-    }
-    double f1 = 0.0, f2 = 0.0;
-    for (int sp = 0; sp < S; ++sp) {
+    const double m1 = m[2 * i], m2 = m[2 * i + 1], kw = kappa[i] * w[i];
+    const double tx = -ny[i], ty = nx[i];  // unit tangent (n = (tau_2, -tau_1))
+    double f1 = 0.0, f2 = 0.0, u1 = 0.0, u2 = 0.0;
+    for (int sp = g; sp < S; sp += kEpiLanes) {
       const double *o = partial + ((size_t)sp * R + r) * len;
       f1 += o[2 * i];
       f2 += o[2 * i + 1];
     }
-    const double m1 = m[2 * i], m2 = m[2 * i + 1];
-    const double tx = -ny[i], ty = nx[i];  // unit tangent (n = (tau_2, -tau_1))
-    const double d = -kappa[i] * w[i] / (2.0 * kPi) * fma(tx, m1, ty * m2);
-    double *o = out + (size_t)r * len;
-    o[2 * i] = alpha * (0.5 * m1 + d * tx + f1 + u1 / (4.0 * kPi));
-    o[2 * i + 1] = alpha * (0.5 * m2 + d * ty + f2 + u2 / (4.0 * kPi));
+    if (with_C) {
+      const double logR = log(scale[0]);
+      const double *A = mom + (size_t)r * N * 3;
+      for (int b = g; b < N; b += kEpiLanes) {
+        const double dx = p.x - pint[2 * b], dy = p.y - pint[2 * b + 1];
+        const double dd = fma(dx, dx, dy * dy);
+        const double inv = 1.0 / dd;
+        const double lg = 0.5 * log(dd) - logR;
+        const double a1 = A[3 * b], a2 = A[3 * b + 1], q = A[3 * b + 2];
+        const double da = fma(dx, a1, dy * a2) * inv;
+        u1 += -lg * a1 + dx * da - q * dy * inv;
+        u2 += -lg * a2 + dy * da + q * dx * inv;
+      }
+    }
+    f1 = epi_sum(f1 + u1 / (4.0 * kPi));
+    f2 = epi_sum(f2 + u2 / (4.0 * kPi));
+    const double d = -kw / (2.0 * kPi) * fma(tx, m1, ty * m2);
+    if (g == 0 && t < M) {
+      double *o = out + (size_t)r * len;
+      o[2 * i] = alpha * (0.5 * m1 + d * tx + f1);
+      o[2 * i + 1] = alpha * (0.5 * m2 + d * ty + f2);
+    }
   }
 }
 
@@ -357,7 +372,7 @@ int dl_apply(bie_geom *g, int stokes, int with_C, double alpha, int nrhs, const 
     const int R = chunk(nrhs - r0), S = pair_splits(g->M, pair_values(kind, R));
     const size_t off = (size_t)r0 * len;
     double *mo = mom + (size_t)r0 * g->N * C;
-    const unsigned nt = (unsigned)((g->M + kEpi - 1) / kEpi);
+    const unsigned nt = (unsigned)((g->M + kEpi / kEpiLanes - 1) / (kEpi / kEpiLanes));
     if (stokes) {
       sweep_chunk<kPairStkDl>(g, S, R, with_C != 0, mu + off, len, mo, partial, st);
       hipLaunchKernelGGL(k_dl_epilogue<true>, dim3(nt, R), dim3(kEpi), 0, st, g->M, g->N,
