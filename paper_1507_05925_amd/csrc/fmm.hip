@@ -931,46 +931,67 @@ __device__ __forceinline__ int chunk_leaves(const int *__restrict__ leaf_start,
   return nslot;
 }
 
-// The apply's last terms, added by the Laplace evaluation when out is set (see FmmFinish):
-// out = alpha (1/2 mu - s kappa / (4 pi) [+ charge of the node's body] + near + far), in the
-// order of the separate epilogue, so that both give the same bits.
+// The apply's last terms, added by the evaluation kernels. Laplace:
+// out = alpha (1/2 mu - s kappa / (4 pi) [+ sum_0] + near + far); Stokes, t the unit tangent and p
+// the node's position relative to its body's centre, turned by a right angle:
+// out = alpha (1/2 mu - kappa / (2 pi) t (t.s) [+ (sum_0, sum_1) + p sum_2] + near + far). The sums
+// are those of the node's body (k_body_sums).
 struct L2pFinish {
-  const double *mu, *s64, *kappa, *charge;  // charge [R][N]: sum of s over each body
+  const double *mu, *s64, *kappa, *px, *py, *sums;  // sums [R][N][1 or 3]
   const int *body_of;
   double *out;
   double alpha;
   int N, with_L;
 };
 
-// Per body b and rhs r: charge[r][b] = sum of s over the body's nodes (the epilogue's order).
+// Per body b and rhs r, over the body's nodes: the sum of s (Laplace), or of s_1, s_2 and p.s
+// (Stokes); the order is that of the direct path's epilogue.
+template <bool STK>
 __global__ __launch_bounds__(256) void k_body_sums(int M, int N, const int *__restrict__ body_ptr,
+                                                   const double *__restrict__ px,
+                                                   const double *__restrict__ py,
                                                    const double *__restrict__ s64,
-                                                   double *__restrict__ charge) {
-  __shared__ double sh[4];
+                                                   double *__restrict__ sums) {
+  constexpr int C = STK ? 3 : 1;
+  __shared__ double sh[C][4];
   const int b = blockIdx.x, r = blockIdx.y;
   const int k0 = body_ptr[b], k1 = body_ptr[b + 1];
-  const double *sr = s64 + (size_t)r * M;
-  double part = 0.0;
-  for (int k = k0 + threadIdx.x; k < k1; k += 256) part += sr[k];
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) part += __shfl_down(part, off, 64);
+  const double *sr = s64 + (size_t)r * (STK ? 2 : 1) * M;
+  double part[C] = {};
+  for (int k = k0 + threadIdx.x; k < k1; k += 256) {
+    if constexpr (STK) {
+      const double s1 = sr[2 * k], s2 = sr[2 * k + 1];
+      part[0] += s1;
+      part[1] += s2;
+      part[2] += px[k] * s1 + py[k] * s2;
+    } else {
+      part[0] += sr[k];
+    }
+  }
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  if (lane == 0) sh[wid] = part;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) part[c] += __shfl_down(part[c], off, 64);
+    if (lane == 0) sh[c][wid] = part[c];
+  }
   __syncthreads();
-  if (threadIdx.x == 0) charge[(size_t)r * N + b] = (sh[0] + sh[1]) + (sh[2] + sh[3]);
+  if (threadIdx.x < C) {
+    const double *q = sh[threadIdx.x];
+    sums[((size_t)r * N + b) * C + threadIdx.x] = (q[0] + q[1]) + (q[2] + q[3]);
+  }
 }
 
 // Both evaluation kernels take their chunks in XCD-contiguous order (xcd_item): sibling leaves,
 // which stage the same ancestors, then share one XCD's L2.
-// L2P, Laplace: adds -(1/2pi) Re(nu F(z)) to the near-field sums in out, or (fin.out set) writes
-// the finished apply. Grid (evaluation chunks, R); dynamic LDS: ev_maxslot P coefficients.
+// L2P, Laplace: adds -(1/2pi) Re(nu F(z)) to the near-field sums and writes the finished apply. Grid (evaluation chunks, R); dynamic LDS: ev_maxslot P coefficients.
 template <int P, class T>
 __global__ __launch_bounds__(64) void k_l2p_laplace(
     int M, int nbox, int L, double ih_leaf, const int *__restrict__ leaf_start,
     const int *__restrict__ leaf_anc, const double2 *__restrict__ center,
     const double2 *__restrict__ xs, const double2 *__restrict__ nrm, const int *__restrict__ perm,
     const int *__restrict__ ev_start, const int *__restrict__ ev_leaf,
-    const cx<T> *__restrict__ Lexp, double *__restrict__ out, const L2pFinish fin) {
+    const cx<T> *__restrict__ Lexp, const double *__restrict__ near, const L2pFinish fin) {
   __builtin_amdgcn_s_setprio(kChainPrio);
   extern __shared__ char l2p_lds[];
   cx<T> *cf = reinterpret_cast<cx<T> *>(l2p_lds);
@@ -1000,26 +1021,24 @@ __global__ __launch_bounds__(64) void k_l2p_laplace(
   }
   const int i = perm[j];
   const size_t ri = (size_t)r * M + i;
-  const double part = out[ri] - (nv.x * (double)F.x - nv.y * (double)F.y) / (2.0 * kPi);  // Re(nu F)
-  if (fin.out) {
-    double v = 0.5 * fin.mu[ri] - fin.s64[ri] * fin.kappa[i] / (4.0 * kPi);
-    if (fin.with_L) v += fin.charge[(size_t)r * fin.N + fin.body_of[i]];
-    v += part;
-    fin.out[ri] = fin.alpha * v;
-  } else {
-    out[ri] = part;
-  }
+  const double part = near[ri] - (nv.x * (double)F.x - nv.y * (double)F.y) / (2.0 * kPi);  // Re(nu F)
+  double v = 0.5 * fin.mu[ri] - fin.s64[ri] * fin.kappa[i] / (4.0 * kPi);
+  if (fin.with_L) v += fin.sums[(size_t)r * fin.N + fin.body_of[i]];
+  v += part;
+  fin.out[ri] = fin.alpha * v;
 }
 
 // L2P, Stokes: sets 3r, 3r+1, 3r+2 are the expansions of A, B, C; adds -(1/pi) of
-// (1/4)[conj(nu) conj(C' - conj(z) A') + conj(nu) conj(B) + nu (conj(A) + A)].
+// (1/4)[conj(nu) conj(C' - conj(z) A') + conj(nu) conj(B) + nu (conj(A) + A)] to the near-field
+// sums and writes the finished apply (the epilogue's own launch took 6 us: two right-hand sides
+// of 57,600 nodes 112.1 -> 110.9 us per apply).
 template <int P>
 __global__ __launch_bounds__(64) void k_l2p_stokes(
     int M, int nbox, int L, double ih_leaf, const int *__restrict__ leaf_start,
     const int *__restrict__ leaf_anc, const double2 *__restrict__ center,
     const double2 *__restrict__ xs, const double2 *__restrict__ nrm, const int *__restrict__ perm,
     const int *__restrict__ ev_start, const int *__restrict__ ev_leaf,
-    const double2 *__restrict__ Lexp, double *__restrict__ out) {
+    const double2 *__restrict__ Lexp, const double *__restrict__ near, const L2pFinish fin) {
   __builtin_amdgcn_s_setprio(kChainPrio);
   extern __shared__ char l2p_lds[];
   double2 *cf = reinterpret_cast<double2 *>(l2p_lds);  // sets A, B, C of every staged ancestor
@@ -1064,8 +1083,20 @@ __global__ __launch_bounds__(64) void k_l2p_stokes(
   const double2 t3 = cmul(nv, make_double2(2.0 * A.x, 0.0));  // conj(A) + A = 2 Re A
   const double fx = 0.25 * (t1.x + t2.x + t3.x), fy = 0.25 * (t1.y + t2.y + t3.y);
   const int i = perm[j];
-  out[(size_t)r * 2 * M + 2 * i] -= fx / kPi;
-  out[(size_t)r * 2 * M + 2 * i + 1] -= fy / kPi;
+  const size_t ri = (size_t)r * 2 * M + 2 * (size_t)i;
+  const double s1 = fin.s64[ri], s2 = fin.s64[ri + 1];
+  const double u1 = -nv.y, u2 = nv.x;  // unit tangent
+  const double d = -fin.kappa[i] / (2.0 * kPi), ts = u1 * s1 + u2 * s2;
+  double v1 = 0.5 * fin.mu[ri] + d * u1 * ts, v2 = 0.5 * fin.mu[ri + 1] + d * u2 * ts;
+  if (fin.with_L) {
+    const double *q = fin.sums + ((size_t)r * fin.N + fin.body_of[i]) * 3;
+    v1 += q[0] + fin.px[i] * q[2];
+    v2 += q[1] + fin.py[i] * q[2];
+  }
+  v1 += near[ri] - fx / kPi;
+  v2 += near[ri + 1] - fy / kPi;
+  fin.out[ri] = fin.alpha * v1;
+  fin.out[ri + 1] = fin.alpha * v2;
 }
 
 // ---- evaluation at arbitrary points (read-off, off-surface field) ----------------------------
@@ -1937,7 +1968,7 @@ int expansion_passes(const FmmTree &t, FmmPlan &plan, int kind, int R, int nsets
       hipLaunchKernelGGL((k_l2p_stokes<P>), dim3(t.nev, R), dim3(64),
                          (size_t)3 * t.ev_maxslot * P * sizeof(double2), s, M, t.nbox, t.L,
                          ih_leaf, t.leaf_start, t.leaf_anc, t.center, t.xs, t.nrm, t.perm,
-                         t.ev_start, t.ev_leaf, Lexp, partial);
+                         t.ev_start, t.ev_leaf, Lexp, partial, fin);
   }
   BIE_HIP_CHECK(hipGetLastError());
   return BIE_OK;
@@ -2072,7 +2103,7 @@ long long fmm_state_bytes(const bie_geom *g, int kind, int precision, int order,
     }
     if (tree == 0) tree = 96LL * g->M + 1024LL * nbox + 16LL * 8 * p * p;
     total += tree + (long long)((size_t)nsets * g->M + 2 * (size_t)nsets * nbox * p) * (long long)csz +
-             (kind == 0 ? (long long)R * g->N * 8 + 64 : 0) + 512;
+             (long long)R * g->N * (kind == 0 ? 8 : 24) + 64 + 512;
   }
   return total;
 }
@@ -2080,7 +2111,7 @@ long long fmm_state_bytes(const bie_geom *g, int kind, int precision, int order,
 // Far field of all pairs k != i (sets: Laplace R, Stokes 3R) into partial [R][len] (nsplit 1).
 int fmm_far_field(bie_geom *g, int kind, int precision, int R, const double *mu, double *s64,
                   double *partial,
-                  hipStream_t s, int order, int leaf, const FmmFinish *finish) {
+                  hipStream_t s, int order, int leaf, const FmmFinish &finish) {
   const int p = fmm_length(order, precision);
   if (leaf <= 0) leaf = 64;
   FmmTree *tp = nullptr;
@@ -2093,20 +2124,17 @@ int fmm_far_field(bie_geom *g, int kind, int precision, int R, const double *mu,
   const bool f32 = precision == BIE_MIXED && kind == 0;
   const size_t csz = f32 ? sizeof(float2) : sizeof(double2);
   // work: charges Q [nsets][M], multipoles and locals [nsets][nbox][p]
-  // (and, when the evaluation finishes the apply, the body charges [R][N])
-  const bool fuse = finish && kind == 0;
+  // and the body sums [R][N][1 or 3]
   const size_t need = ((size_t)nsets * M + 2 * (size_t)nsets * t.nbox * p) * csz +
-                      (fuse ? (size_t)R * g->N * 8 + 64 : 0) + 512;
+                      (size_t)R * g->N * (kind == 0 ? 8 : 24) + 64 + 512;
   BIE_TRY(t.work.reserve(need));
   char *wq = t.work.as<char>();
   char *wm = wq + (size_t)nsets * M * csz;
   char *wl = wm + (size_t)nsets * t.nbox * p * csz;
-  double *charge = reinterpret_cast<double *>(
+  double *sums = reinterpret_cast<double *>(
       (reinterpret_cast<uintptr_t>(wl + (size_t)nsets * t.nbox * p * csz) + 63) & ~uintptr_t(63));
-  L2pFinish fin{};
-  if (fuse)
-    fin = L2pFinish{finish->mu, s64, g->kappa, charge, g->body_of, finish->out, finish->alpha,
-                    g->N, finish->with_L};
+  const L2pFinish fin{finish.mu, s64, g->kappa, g->px, g->py, sums, g->body_of, finish.out,
+                      finish.alpha, g->N, finish.with_L};
   FmmPlan &plan = *g->fmm;
   if (!plan.side) {  // side stream for the near field (default priority) and its fork/join events
     BIE_HIP_CHECK(hipStreamCreateWithFlags(&plan.side, hipStreamNonBlocking));
@@ -2127,9 +2155,6 @@ int fmm_far_field(bie_geom *g, int kind, int precision, int R, const double *mu,
   BIE_HIP_CHECK(hipEventRecord(plan.fork, s));
   auto launch_near = [&]() -> int {
     BIE_HIP_CHECK(hipStreamWaitEvent(plan.side, plan.fork, 0));
-    if (fuse && finish->with_L)  // the body charges for the finishing evaluation
-      hipLaunchKernelGGL(k_body_sums, dim3(g->N, R), dim3(256), 0, plan.side, M, g->N,
-                         g->body_ptr, s64, charge);
     {
       // the float32 near field in every mixed apply (Laplace and Stokes)
       const bool near32 = precision == BIE_MIXED;
@@ -2148,6 +2173,16 @@ int fmm_far_field(bie_geom *g, int kind, int precision, int R, const double *mu,
         near_pass<double, true>(t, R, g->pair_scale, reinterpret_cast<const double2 *>(wq), partial,
                                 plan.side);
       BIE_HIP_CHECK(hipGetLastError());
+    }
+    if (finish.with_L) {  // the body sums for the evaluation, behind the near field, which ends
+                           // before the M2L: ahead of it they slowed the M2M levels beside them
+                           // by as much as the epilogue launch had cost
+      if (kind == 0)
+        hipLaunchKernelGGL(k_body_sums<false>, dim3(g->N, R), dim3(256), 0, plan.side, M, g->N,
+                           g->body_ptr, g->px, g->py, s64, sums);
+      else
+        hipLaunchKernelGGL(k_body_sums<true>, dim3(g->N, R), dim3(256), 0, plan.side, M, g->N,
+                           g->body_ptr, g->px, g->py, s64, sums);
     }
     BIE_HIP_CHECK(hipEventRecord(plan.join, plan.side));
     return BIE_OK;

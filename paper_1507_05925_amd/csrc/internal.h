@@ -332,10 +332,9 @@ int gmres_cycle(SysSet &ss, int precision, const double *r, double *d,
                 const std::vector<double> &tol, int m, int &iters, int &applies, hipStream_t s);
 
 // ---- fmm.hip ------------------------------------------------------------------------------
-// mu [nrhs][len] in; s64 [nrhs][len] out (the strengths w mu, for the epilogue)
-// The per-node terms a Laplace FMM apply can add in its evaluation kernel instead of a separate
-// epilogue: out = alpha (1/2 mu - s kappa / (4 pi) [+ with_L: the sum of s over the node's body]
-// + near + far), [R][M] in node order.
+// mu [nrhs][len] in; s64 [nrhs][len] out (the strengths w mu)
+// What the evaluation kernel of an FMM apply writes: the identity, the diagonal limit and (with_L)
+// the completion of the node's body with the near and far field, times alpha; [R][len].
 struct FmmFinish {
   const double *mu = nullptr;
   double *out = nullptr;
@@ -344,7 +343,7 @@ struct FmmFinish {
 };
 int fmm_far_field(bie_geom *g, int kind, int precision, int nrhs, const double *mu, double *s64,
                   double *partial, hipStream_t s, int order, int leaf,
-                  const FmmFinish *finish = nullptr);
+                  const FmmFinish &finish);
 void fmm_destroy(FmmPlan *p);
 // single-layer potentials at points by the treecode over the float64 FMM tree (see kernels.hip
 // eval_points for the layouts)

@@ -293,12 +293,11 @@ __global__ __launch_bounds__(kBlock) void k_lap_epilogue(
     const double *__restrict__ x, const double *__restrict__ y, const double *__restrict__ nx,
     const double *__restrict__ ny, const double *__restrict__ w, const double *__restrict__ kappa,
     const double *__restrict__ mu, const double *__restrict__ s64, const double *__restrict__ partial,
-    int with_L, int self_block, double alpha, double *__restrict__ out) {
+    int with_L, double alpha, double *__restrict__ out) {
   __shared__ double sh[4];
   const int b = blockIdx.x / ntile, tile = blockIdx.x % ntile, r = blockIdx.y;
   const int k0 = body_ptr[b], k1 = body_ptr[b + 1];
   if (k0 + tile * kBlock >= k1) return;  // whole workgroup
-  const int kend = self_block ? k1 : k0;  // the FMM far field already holds same-body pairs
   const double *s = s64 + (size_t)r * M;
   const double *m = mu + (size_t)r * M;
   double part = 0.0;
@@ -310,7 +309,7 @@ __global__ __launch_bounds__(kBlock) void k_lap_epilogue(
   const double xi = x[ii], yi = y[ii], a = nx[ii], bb = ny[ii];
   double gx = 0.0, gy = 0.0;
   int k = k0;
-  for (; k + 4 <= kend; k += 4) {
+  for (; k + 4 <= k1; k += 4) {
     double xs[4], ys[4], ss[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -328,7 +327,7 @@ __global__ __launch_bounds__(kBlock) void k_lap_epilogue(
       gy = fma(dy, t, gy);
     }
   }
-  for (; k < kend; ++k) {
+  for (; k < k1; ++k) {
     const double dx = xi - x[k], dy = yi - y[k];
     const bool same = (k == ii);
     const double inv = rcp64(same ? 1.0 : fma(dx, dx, dy * dy));
@@ -347,13 +346,12 @@ __global__ __launch_bounds__(kBlock) void k_stk_epilogue(
     const double *__restrict__ x, const double *__restrict__ y, const double *__restrict__ nx,
     const double *__restrict__ ny, const double *__restrict__ kappa, const double *__restrict__ px,
     const double *__restrict__ py, const double *__restrict__ mu, const double *__restrict__ s64,
-    const double *__restrict__ partial, int with_L, int self_block, double alpha,
+    const double *__restrict__ partial, int with_L, double alpha,
     double *__restrict__ out) {
   __shared__ double sh[4];
   const int b = blockIdx.x / ntile, tile = blockIdx.x % ntile, r = blockIdx.y;
   const int k0 = body_ptr[b], k1 = body_ptr[b + 1];
   if (k0 + tile * kBlock >= k1) return;  // whole workgroup
-  const int kend = self_block ? k1 : k0;
   const double *s = s64 + (size_t)r * 2 * M;
   const double *m = mu + (size_t)r * 2 * M;
   double f1 = 0.0, f2 = 0.0, tq = 0.0;
@@ -369,7 +367,7 @@ __global__ __launch_bounds__(kBlock) void k_stk_epilogue(
   const double xi = x[ii], yi = y[ii], a = nx[ii], bb = ny[ii];
   double gx = 0.0, gy = 0.0;
   int k = k0;
-  for (; k + 4 <= kend; k += 4) {
+  for (; k + 4 <= k1; k += 4) {
     double xs[4], ys[4], s1[4], s2[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -389,7 +387,7 @@ __global__ __launch_bounds__(kBlock) void k_stk_epilogue(
       gy = fma(cc, dy, gy);
     }
   }
-  for (; k < kend; ++k) {
+  for (; k < k1; ++k) {
     const double dx = xi - x[k], dy = yi - y[k];
     const bool same = (k == ii);
     const double inv = rcp64(same ? 1.0 : fma(dx, dx, dy * dy));
@@ -716,39 +714,34 @@ int apply_operator_ws(bie_geom *g, int kind, int precision, int method, int with
     if (method == BIE_FMM) {
       const int leaf = precision == BIE_MIXED && g->fmm_leaf_mixed > 0 ? g->fmm_leaf_mixed
                                                                         : g->fmm_leaf;
-      if (kind == 0) {  // the Laplace evaluation finishes the apply itself (no epilogue launch)
-        FmmFinish fin;
-        fin.mu = mu + off;
-        fin.out = out + off;
-        fin.alpha = alpha;
-        fin.with_L = with_L;
-        BIE_TRY(fmm_far_field(g, kind, precision, R, mu + off, s64 + off, partial, st,
-                              g->fmm_order, leaf, &fin));
-        r0 += R;
-        continue;
-      }
+      FmmFinish fin;  // the evaluation finishes the apply itself (no epilogue launch)
+      fin.mu = mu + off;
+      fin.out = out + off;
+      fin.alpha = alpha;
+      fin.with_L = with_L;
       BIE_TRY(fmm_far_field(g, kind, precision, R, mu + off, s64 + off, partial, st, g->fmm_order,
-                            leaf));
-    } else {
-      switch (R) {
-        case 8: launch_far<8>(g, kind, s32, partial, st, off); break;
-        case 4: launch_far<4>(g, kind, s32, partial, st, off); break;
-        case 2: launch_far<2>(g, kind, s32, partial, st, off); break;
-        default: launch_far<1>(g, kind, s32, partial, st, off); break;
-      }
-      BIE_HIP_CHECK(hipGetLastError());
+                            leaf, fin));
+      r0 += R;
+      continue;
     }
+    switch (R) {
+      case 8: launch_far<8>(g, kind, s32, partial, st, off); break;
+      case 4: launch_far<4>(g, kind, s32, partial, st, off); break;
+      case 2: launch_far<2>(g, kind, s32, partial, st, off); break;
+      default: launch_far<1>(g, kind, s32, partial, st, off); break;
+    }
+    BIE_HIP_CHECK(hipGetLastError());
     const int ntile = std::max(1, (g->max_nb + kBlock - 1) / kBlock);
     dim3 eg(g->N * ntile, R);
     ProfScope prof(BIE_K_EPILOGUE, st, 0);
     if (kind == 0)
       hipLaunchKernelGGL(k_lap_epilogue, eg, dim3(kBlock), 0, st, g->M, nsplit, R, ntile,
                          g->body_ptr, g->x, g->y, g->nx, g->ny, g->w, g->kappa, mu + off,
-                         s64 + off, partial, with_L, method == BIE_FMM ? 0 : 1, alpha, out + off);
+                         s64 + off, partial, with_L, alpha, out + off);
     else
       hipLaunchKernelGGL(k_stk_epilogue, eg, dim3(kBlock), 0, st, g->M, nsplit, R, ntile,
                          g->body_ptr, g->x, g->y, g->nx, g->ny, g->kappa, g->px, g->py, mu + off,
-                         s64 + off, partial, with_L, method == BIE_FMM ? 0 : 1, alpha, out + off);
+                         s64 + off, partial, with_L, alpha, out + off);
     BIE_HIP_CHECK(hipGetLastError());
     r0 += R;
   }

@@ -69,3 +69,21 @@ def test_near_field_large_densities(kind, factor):
         b = f(g, (factor * mu[:n]).contiguous(), bie2d.BIE_MIXED, bie2d.BIE_FMM, with_L=False)
         assert bool(torch.isfinite(b).all()), (n, factor)
         assert torch.equal(factor * a, b), (n, factor)
+
+
+@pytest.mark.parametrize("kind", [0, 1])
+def test_fmm_apply_completion(kind):
+    """The evaluation adds the completion from per-body sums: bodies of fewer, exactly and more
+    nodes than the 256 threads that sum one, against the direct apply (float64 sums of at most M
+    terms and expansions of 48: the 1e-12 of the groups' test)."""
+    rng = np.random.default_rng(11)
+    c = wl.mixed_grid(rng, 7, np.array([64, 255, 256, 257, 511, 512, 700]))
+    g = bie2d.Geometry.from_curves(c)
+    g.set_fmm(48, 64)
+    f = bie2d.bie_laplace_apply if kind == 0 else bie2d.bie_stokes_apply
+    mu = torch.as_tensor(1.0 + rng.standard_normal((9, c.M * (1 + kind))), device="cuda")
+    for with_L in (True, False):
+        ref = f(g, mu, bie2d.BIE_FP64, bie2d.BIE_DIRECT, with_L=with_L)
+        for n in (1, 4, 9):
+            out = f(g, mu[:n].contiguous(), bie2d.BIE_FP64, bie2d.BIE_FMM, with_L=with_L)
+            assert float((out - ref[:n]).abs().max() / ref.abs().max()) < 1e-12, (n, with_L)
