@@ -157,6 +157,12 @@ __global__ __launch_bounds__(BJ) void k_pc_check(int kind, const int *__restrict
 // interpolation linear, (E y)_i = (1 - t) y_{i / s} + t y_{i / s + 1} with t = (i mod s) / s;
 // then y = B^-1 w (the sum over k cut into `parts` ranges whose partial sums are added in range
 // order) and out = 2 v + E (y - 2 w); with s = 1, out = B^-1 v.
+// Bound by the latency of the inverse's columns: eight are in flight at a time, where a load and its
+// product per step took 10.9 us for 200 bodies of 512 nodes (Stokes; now 6.9), 8.6 us for 1000 of
+// 256 (Laplace; 6.7) and 24.5 us for 6,144 (body, right-hand side) pairs of a batch (14.5). All of
+// a thread's columns ahead of the staging (up to 64) took 56 us there: registers and masked loads.
+// Four right-hand sides per workgroup, which read the inverse once, took 13.4 us there and the
+// call within its noise: not kept.
 template <int NT>
 __device__ void pc_body(int kind, int M, int b, int r, const int *__restrict__ body_ptr,
                         const int *__restrict__ ncoarse, const float *__restrict__ inv, int BJ,
@@ -194,7 +200,15 @@ __device__ void pc_body(int kind, int M, int b, int r, const int *__restrict__ b
     const int o = t % U, p = t / U;
     const int k0 = p * U / parts, k1 = (p + 1) * U / parts;
     const float *ib = inv + (size_t)b * BJ * BJ + o;
-    for (int k = k0; k < k1; ++k) acc = fma((double)ib[(size_t)k * BJ], wv[k], acc);
+    int k = k0;
+    for (; k + 8 <= k1; k += 8) {
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = ib[(size_t)(k + e) * BJ];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc = fma((double)x[e], wv[k + e], acc);
+    }
+    for (; k < k1; ++k) acc = fma((double)ib[(size_t)k * BJ], wv[k], acc);
   }
   part[t] = acc;
   __syncthreads();
@@ -339,8 +353,8 @@ int pc_apply(bie_geom *g, int kind, int nrhs, const double *in, double *out, hip
   // units: multiply-adds (restriction, coarse product and interpolation) per right-hand side
   ProfScope prof(BIE_K_PRECOND, s, pc.macs * nrhs);
   // few bodies: 1024 threads per body shorten each one's sums; many: 512 threads, more
-  // workgroups per compute unit (1000 starfish: 10.4 us per apply against 11.8 with 256 and
-  // 14.3 with 1024)
+  // workgroups per compute unit (1000 starfish, with one column in flight: 10.4 us per apply
+  // against 11.8 with 256 and 14.3 with 1024)
   if (g->N < 512)
     hipLaunchKernelGGL(k_pc_apply<1024>, dim3(g->N, nrhs), dim3(1024), pc.lds, s, kind, g->M,
                        pc.BJ, g->body_ptr, pc.ncoarse, pc.inv.as<float>(), in, out);
