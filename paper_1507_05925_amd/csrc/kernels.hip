@@ -512,6 +512,7 @@ __global__ void k_potential_fin(int N, int nrhs, int S, const double *__restrict
   const long long i = (long long)blockIdx.x * kBlock + threadIdx.x;
   if (i >= (long long)N * nrhs) return;
   double v = 0.0;
+#pragma unroll 8
   for (int sp = 0; sp < S; ++sp) v += part[(size_t)sp * N * nrhs + i];
   phi[i] = -v / (4.0 * kPi);
 }
@@ -575,6 +576,7 @@ __global__ void k_rigid_fin(int N, int nrhs, int S, const double *__restrict__ p
   if (i >= (long long)N * nrhs) return;
   const int j = (int)(i % N);
   double U1 = 0.0, U2 = 0.0, OM = 0.0;
+#pragma unroll 8
   for (int sp = 0; sp < S; ++sp) {
     const double *o = part + ((size_t)sp * N * nrhs + i) * 3;
     U1 += o[0];
@@ -789,6 +791,7 @@ __global__ void k_velocity_fin(int N, int nrhs, int S, const double *__restrict_
   const long long i = (long long)blockIdx.x * kBlock + threadIdx.x;
   if (i >= (long long)N * nrhs) return;
   double U1 = 0.0, U2 = 0.0;
+#pragma unroll 8
   for (int sp = 0; sp < S; ++sp) {
     const double *o = part + ((size_t)sp * N * nrhs + i) * 3;
     U1 += o[0];
@@ -803,10 +806,15 @@ int eval_points(bie_geom *g, int kind, int nrhs, const double *dens, int npts, c
   if (nrhs <= 0 || npts <= 0) return BIE_OK;
   if (method == BIE_AUTO) method = method_is_fmm(method, g->M) ? BIE_FMM : BIE_DIRECT;
   if (method == BIE_FMM) return fmm_eval_points(g, kind, nrhs, dens, npts, pts, rigid, res, st);
-  // source splits: about 2048 workgroups in all, at most 32 splits, at least 2048 sources each
+  // source splits: about 2048 workgroups in all, at most 32 splits, at least 2048 sources each; or,
+  // where that leaves compute units without a workgroup, down to one source per thread, if that
+  // makes four splits or more (a source's kTJ logarithms are a long chain; with two splits 512
+  // nodes took 1.7% longer per solve, and so did points that fill the chip by themselves). 2,304
+  // nodes, 24 bodies, rigid motions: 23.5 us in one split of 3 workgroups, 8.6 in nine
   const long long groups = (long long)((npts + kTJ - 1) / kTJ) * nrhs;
+  const int fine = (int)std::min<long long>({32, g->M / kBlock, 256 / groups});
   int S = (int)std::max<long long>(1, std::min<long long>(32, (2048 + groups - 1) / groups));
-  S = std::max(1, std::min(S, g->M / 2048));
+  S = std::max({1, std::min(S, g->M / 2048), fine >= 4 ? fine : 1});
   const int comps = kind == 0 ? 1 : 3;
   BIE_TRY(g->ws_read.reserve((size_t)S * nrhs * npts * comps * 8));
   double *part = g->ws_read.as<double>();
