@@ -293,6 +293,15 @@ __host__ __device__ inline unsigned long long column_tag(unsigned long long seq)
   return 0x7FF5A00000000000ULL | (seq & 0x00000FFFFFFFFFFFULL);
 }
 int vec_axpby(long long total, double a, const double *x, double b, double *y, hipStream_t s);
+// dst = src (add: dst += src; src NULL: zeros) for each move, in one launch per kMoves of them; the
+// moves' ranges do not overlap. Copies the list: it may go out of scope once this returns.
+struct VecMove {
+  double *dst;
+  const double *src;
+  long long n;
+};
+constexpr int kMoves = 64;
+int vec_move(const std::vector<VecMove> &moves, bool add, hipStream_t s);
 // DCGS2 Arnoldi step pieces (blas.hip): raw[s][0 .. 2nv+1] = (V_l.U, V_l.Z)_l, U.U, U.Z (Z may be
 // NULL); the per-system column and coefficients; the update writing V_j and the next candidate
 int dcgs_dots(const Segments &sg, int nv, const double *V, long long vstride, const double *U,

@@ -239,11 +239,13 @@ int bie_server::cycle() {
   BIE_TRY(seg.build(lens, s, &starts));
   BIE_TRY(flat.reserve(4 * (size_t)N * sizeof(double)));
   double *F = flat.as<double>(), *X = F + N, *R = X + N, *D = R + N;
+  std::vector<VecMove> moves;
   for (size_t i = 0; i < active.size(); ++i) {
-    const size_t bytes = sizeof(double) * active[i]->nrhs * active[i]->n;
-    BIE_HIP_CHECK(hipMemcpyAsync(F + off[i], active[i]->f, bytes, hipMemcpyDeviceToDevice, s));
-    BIE_HIP_CHECK(hipMemcpyAsync(X + off[i], active[i]->x, bytes, hipMemcpyDeviceToDevice, s));
+    const long long n = active[i]->nrhs * active[i]->n;
+    moves.push_back({F + off[i], active[i]->f, n});
+    moves.push_back({X + off[i], active[i]->x, n});
   }
+  BIE_TRY(vec_move(moves, false, s));
   SysSet ss;
   ss.seg = &seg;
   ss.mem = &sm;
@@ -273,6 +275,7 @@ int bie_server::cycle() {
   std::vector<double> itol_all(seg.S, 1.0);
   std::vector<char> retire(active.size(), 0);
   size_t k = 0;
+  moves.clear();
   for (size_t i = 0; i < active.size(); ++i) {
     Request &r = *active[i];
     bool all = true;
@@ -284,10 +287,11 @@ int bie_server::cycle() {
       // (margin 3); with float32 far fields never tighter than inner_tol
       itol_all[k] = c ? 1.0 : std::max(o.precision == BIE_MIXED ? o.inner_tol : 0.0,
                                        o.tol / (3.0 * r.relres[j]));
-      if (c) BIE_HIP_CHECK(hipMemsetAsync(R + seg.h_off[k], 0, sizeof(double) * r.n, s));
+      if (c) moves.push_back({R + seg.h_off[k], nullptr, r.n});
     }
     if (all || r.cycles >= cfg.max_cycles) retire[i] = 1;
   }
+  BIE_TRY(vec_move(moves, false, s));  // converged systems take no part in the cycle
   // ---- retire: results of converged requests go out before the next cycle --------------------
   std::vector<std::shared_ptr<Request>> keep;
   std::vector<long long> keep_old_off;
@@ -321,10 +325,10 @@ int bie_server::cycle() {
       starts2.push_back(off2[i] + j * active[i]->n);
     }
   double *T = X;  // X is no longer needed this cycle: it holds the re-laid-out residual
+  moves.clear();
   for (size_t i = 0; i < active.size(); ++i)
-    BIE_HIP_CHECK(hipMemcpyAsync(T + off2[i], R + keep_old_off[i],
-                                 sizeof(double) * active[i]->nrhs * active[i]->n,
-                                 hipMemcpyDeviceToDevice, s));
+    moves.push_back({T + off2[i], R + keep_old_off[i], active[i]->nrhs * active[i]->n});
+  BIE_TRY(vec_move(moves, false, s));
   BIE_TRY(seg.build(lens2, s, &starts2));
   // right preconditioning of the cycle: GMRES on (A P) u = r, then d = P u (R, no longer read
   // this cycle, holds P u); one launch applies every item's blocks
@@ -379,11 +383,12 @@ int bie_server::cycle() {
   BIE_TRY(gmres_cycle(ss, o.precision, T, D, itol, m, iters, applies, s));
   if (pc_items)  // d = P u, in place (each body is staged before it is written)
     BIE_TRY(pc_apply_batch(pc_n, pc_items, pc_lds, pc_blocks, pc_macs, D, D, s));
+  moves.clear();
   for (size_t i = 0; i < active.size(); ++i) {
-    BIE_TRY(vec_axpby((long long)active[i]->nrhs * active[i]->n, 1.0, D + off2[i], 1.0,
-                      active[i]->x, s));
+    moves.push_back({active[i]->x, D + off2[i], active[i]->nrhs * active[i]->n});
     active[i]->cycles += 1;
   }
+  BIE_TRY(vec_move(moves, true, s));
   std::lock_guard<std::mutex> lk(mu);
   ++n_cycles;
   return BIE_OK;
