@@ -136,7 +136,7 @@ int bie_batch_solve(bie_batch *b, int nitems, const bie_batch_item *items, const
   for (int i = 0; i < nitems; ++i) {
     bie_geom *g = items[i].g;
     mitems[i] = {g, items[i].kind, items[i].nrhs, item_off[i],
-                 method_is_fmm(o.method, g->M), effective_order(o, items[i].kind), g->fmm_leaf, true};
+                 method_is_fmm(o.method, g->M), effective_order(o, items[i].kind), g->fmm_leaf};
     first_sys[i + 1] = first_sys[i] + items[i].nrhs;
   }
   ss.group_ptr = first_sys;  // items: a relaxed mixed solve picks precisions per item

@@ -402,14 +402,14 @@ struct MultiItem {
   long long io;  // start of the item's rhs block in the flat vectors (64-byte aligned)
   bool fmm;      // applied by the single-geometry FMM path
   int fmm_order = 40, fmm_leaf = 64;  // its expansion order and leaf population (FMM items)
-  // whether its BIE_MIXED applies may take the float32 matrix-core sweep, a choice that depends on
-  // nrhs (not for items whose nrhs depends on other callers)
-  bool f32_sweep = false;
+  // whether nrhs depends on other callers: its BIE_MIXED applies then choose no sweep by nrhs, so
+  // that a right-hand side's bits depend on its geometry alone
+  bool merged = false;
 };
 struct MultiPlan;
 // item_f32 (nullptr: every item uses precision): per item, 1 = BIE_MIXED, 0 = BIE_FP64, at most
-// kMaxPrecGroups items. Direct items without f32_sweep or with few right-hand sides are float64
-// either way.
+// kMaxPrecGroups items. Direct items of few right-hand sides are float64 either way, unless they are
+// Stokes items of many nodes.
 int multi_apply(MultiPlan *&plan, const std::vector<MultiItem> &items,
                 const std::vector<char> &active, int precision, const double *in, double *out,
                 hipStream_t s, const std::vector<char> *item_f32 = nullptr);

@@ -36,7 +36,10 @@ struct ItemDesc {
   // float32 sweep (mm: the item has it): lists of 16-target tiles (body, first node) and of source
   // chunks (body, first node, nodes); Smm splits of cper chunks, and one more slot of partial sums
   // for the bodies' own blocks: group r0 at part + r0 (Smm + 1) len
+  // (k_multi_far: splits of bodies, and the item's float32 strengths from s32 on)
   int mm, ntile, nchunk, cper, Smm;
+  long long s32;
+  const int *body_of, *split_body;
   const int2 *tile;
   const int4 *chunk;
   const float2 *xr;
@@ -51,6 +54,14 @@ constexpr int kMmChunk = 64;                       // sources staged at a time (
 constexpr int kMmTiles = 2;                        // 16-target tiles per wave
 constexpr int kMmTile = 16 * kMmTiles * 4;         // targets per workgroup, at most
 
+// Stokes items of at least kFarNodes nodes take the float32 vector sweep instead of the float64 one
+// where they do not take the matrix cores', whatever their right-hand sides (merged items may not
+// choose by their number). Served mobility requests, 1 / 4 / 15 at a time, float64 against float32:
+// 8,672 nodes 2.9 / 6.5 / 16.0 ms against 3.3 / 7.2 / 13.0; 12,352 nodes 5.1 / 11.0 / 30.5 against
+// 4.8 / 10.2 / 20.8; 29,568 nodes 21.0 / 47.5 / 155 against 14.4 / 32.1 / 94.2.
+constexpr int kFarNodes = 12288;
+constexpr int kFarGroup = 4;
+
 // Right-hand side group sizes of each kind.
 constexpr int kGroups[2][5] = {{8, 4, 3, 2, 1}, {4, 3, 2, 1, 0}};
 
@@ -63,11 +74,13 @@ struct MultiPlan {
   hipStream_t pool[kFmmStreams] = {};
   hipEvent_t fork = nullptr, join[kFmmStreams] = {};
   int nsweep = 0, nfin = 0, nlap = 0;  // tasks; finish tasks of Laplace items (they come first)
-  int nmm[2] = {0, 0};                 // float32 sweep tasks per kind
+  int nmm[2] = {0, 0};                 // float32 matrix-core sweep tasks per kind
+  int nfar = 0, npack = 0;             // float32 vector sweep tasks, and those of its strengths
   int4 *sweep_task = nullptr, *fin_task = nullptr, *mm_task[2] = {nullptr, nullptr};
+  int4 *far_task = nullptr, *pack_task = nullptr;
   DevBuf list_buf;  // the items' tile and chunk lists
   ItemDesc *desc = nullptr;
-  long long npart = 0;  // doubles of partial sums
+  long long npart = 0, nfloat = 0;  // doubles of partial sums, floats of strengths
   // the plan is reused while every item matches: geometry id, kind, rhs count, method and
   // offset of its block, and the active flags
   std::vector<unsigned long long> key_gen;
@@ -320,6 +333,114 @@ __global__ __launch_bounds__(kBlock) void k_multi_mm(const int4 *__restrict__ ta
   }
 }
 
+// Float32 Stokes pairs of different bodies on the vector units, for large items (kFarNodes). Lane =
+// target; sources and strengths are wave-uniform and come through scalar registers, coordinates
+// relative to the source body's centroid, a body's float32 sums added into float64. The operations
+// of a right-hand side do not depend on R, so a request has the same bits whichever others it is
+// merged with. Bound by the vector rate: a pair takes about 45 cycles per 64 and 22 more per
+// right-hand side, where the float64 sweep takes 70 and 24 and waits for LDS. Sources staged in LDS
+// (16 targets and four source lanes per tile, as in k_multi_mm) took 39 and 123 ms for the 1 and 15
+// requests on 30,000 nodes that take 14 and 94 here.
+constexpr float kFar32 = 1.0e18f;
+
+template <int R>
+__device__ __forceinline__ void far_task(const int4 &t, const ItemDesc &d,
+                                         const float *__restrict__ s32,
+                                         double *__restrict__ partial) {
+  const int M = d.M, i = t.z + (int)threadIdx.x, ii = min(i, M - 1);
+  const long long len = 2LL * M;
+  const int bi = gload(d.body_of, ii);
+  const float *sv = s32 + d.s32 + (long long)t.y * len;
+  double Gx[R], Gy[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) Gx[r] = Gy[r] = 0.0;
+  const int c0 = gload(d.split_body, t.w), c1 = gload(d.split_body, t.w + 1);
+  const double cxi = gload(d.xc, bi), cyi = gload(d.yc, bi);
+  const float *xr = reinterpret_cast<const float *>(d.xr);
+  const float px = gload(xr, 2LL * ii), py = gload(xr, 2LL * ii + 1);
+  const float nx = (float)gload(d.nx, ii), ny = (float)gload(d.ny, ii);
+  for (int c = c0; c < c1; ++c) {
+    const bool self = c == bi;
+    if (__all(self)) continue;
+    const int k0 = gload(d.body_ptr, c), k1 = gload(d.body_ptr, c + 1);
+    float tx = (float)((cxi - gload(d.xc, c)) + (double)px);
+    float ty = (float)((cyi - gload(d.yc, c)) + (double)py);
+    tx = self ? kFar32 : tx;  // no pair of these lanes is near; their sums are dropped
+    ty = self ? kFar32 : ty;
+    float gx[R], gy[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) gx[r] = gy[r] = 0.0f;
+#pragma unroll 2
+    for (int k = k0; k < k1; ++k) {
+      const float dx = tx - gload(xr, 2LL * k), dy = ty - gload(xr, 2LL * k + 1);
+      const float inv = __builtin_amdgcn_rcpf(fmaf(dx, dx, dy * dy));
+      const float a = fmaf(dx, nx, dy * ny) * (inv * inv);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const float e = fmaf(dx, gload(sv, r * len + 2LL * k), dy * gload(sv, r * len + 2LL * k + 1)) * a;
+        gx[r] = fmaf(e, dx, gx[r]);
+        gy[r] = fmaf(e, dy, gy[r]);
+      }
+    }
+    if (!self) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        Gx[r] += (double)gx[r];
+        Gy[r] += (double)gy[r];
+      }
+    }
+  }
+  if (i >= M) return;
+  // partial sums lie in the groups of 16 that the finishing launch reads
+  const int r0 = t.y / kMmGroup * kMmGroup, G = min(kMmGroup, d.nrhs - r0);
+  double *o = partial + d.part + (long long)r0 * (d.Smm + 1) * len +
+              ((long long)t.w * G + (t.y - r0)) * len + 2LL * i;
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    o[r * len] = -Gx[r] / kPi;
+    o[r * len + 1] = -Gy[r] / kPi;
+  }
+}
+
+// Tasks (item, first rhs | R << 24, first target, split of bodies).
+__global__ __launch_bounds__(kBlock) void k_multi_far(const int4 *__restrict__ tasks,
+                                                      const ItemDesc *__restrict__ D,
+                                                      const float *__restrict__ s32,
+                                                      const ItemMask mm,
+                                                      double *__restrict__ partial) {
+  int4 t = tasks[blockIdx.x];
+  if (!in_mask(mm, t.x)) return;  // (whole workgroup)
+  const ItemDesc &d = D[t.x];
+  const int R = t.y >> 24;
+  t.y &= 0xffffff;
+  switch (R) {
+    case 4: far_task<4>(t, d, s32, partial); break;
+    case 3: far_task<3>(t, d, s32, partial); break;
+    case 2: far_task<2>(t, d, s32, partial); break;
+    default: far_task<1>(t, d, s32, partial); break;
+  }
+}
+
+// The float32 strengths w mu that k_multi_far reads: tasks (item, rhs, first node).
+constexpr int kPackNodes = 2048;
+__global__ __launch_bounds__(kBlock) void k_multi_pack(const int4 *__restrict__ tasks,
+                                                       const ItemDesc *__restrict__ D,
+                                                       const double *__restrict__ mu,
+                                                       const ItemMask mm, float *__restrict__ s32) {
+  const int4 t = tasks[blockIdx.x];
+  if (!in_mask(mm, t.x)) return;
+  const ItemDesc &d = D[t.x];
+  const long long at = (long long)t.y * 2 * d.M;
+  const double *m = mu + d.io + at;
+  float *o = s32 + d.s32 + at;
+  const int k1 = min(t.z + kPackNodes, d.M);
+  for (int k = t.z + threadIdx.x; k < k1; k += kBlock) {
+    const double w = gload(d.w, k);
+    o[2LL * k] = (float)(w * m[2LL * k]);
+    o[2LL * k + 1] = (float)(w * m[2LL * k + 1]);
+  }
+}
+
 // Identity, diagonal limit, completion and the splits' sums (in order) of one body and right-hand
 // side by one wave: task (item, body, rhs r, first rhs of its group | group size << 24).
 template <bool STK>
@@ -408,10 +529,10 @@ int build_plan(MultiPlan &P, const std::vector<MultiItem> &items, const std::vec
                hipStream_t s) {
   const int n = (int)items.size();
   std::vector<ItemDesc> desc(n);
-  std::vector<int4> sweep[2], own[2], fin[2], mm[2], chunks;
+  std::vector<int4> sweep[2], own[2], fin[2], mm[2], fr, pk, chunks;
   std::vector<int2> tiles16;
   std::vector<size_t> tile_at(n, 0), chunk_at(n, 0);
-  long long part = 0;
+  long long part = 0, floats = 0;
   for (int i = 0; i < n; ++i) {
     const MultiItem &m = items[i];
     bie_geom *g = m.g;
@@ -432,8 +553,22 @@ int build_plan(MultiPlan &P, const std::vector<MultiItem> &items, const std::vec
     d.part = part;
     if (!active[i] || m.fmm) continue;
     const long long len = g->M * (m.kind == 0 ? 1LL : 2LL);
-    d.mm = m.f32_sweep && m.nrhs >= kMmRhs && n <= kMaxPrecGroups;
-    if (d.mm) {
+    const bool cores = !m.merged && m.nrhs >= kMmRhs && n <= kMaxPrecGroups;
+    const bool far = !cores && m.kind == 1 && g->M >= kFarNodes && n <= kMaxPrecGroups;
+    d.mm = cores || far;
+    if (far) {
+      d.body_of = g->body_of;
+      d.split_body = g->split_body;
+      d.Smm = g->nsplit;
+      d.s32 = floats;
+      floats += m.nrhs * len;
+      for (int r0 = 0; r0 < m.nrhs; r0 += kFarGroup)
+        for (int sp = 0; sp < d.Smm; ++sp)
+          for (int k = 0; k < g->M; k += kBlock)
+            fr.push_back(make_int4(i, r0 | std::min(kFarGroup, m.nrhs - r0) << 24, k, sp));
+      for (int r = 0; r < m.nrhs; ++r)
+        for (int k = 0; k < g->M; k += kPackNodes) pk.push_back(make_int4(i, r, k, 0));
+    } else if (cores) {
       tile_at[i] = tiles16.size();
       chunk_at[i] = chunks.size();
       for (int b = 0; b < g->N; ++b) {
@@ -451,6 +586,8 @@ int build_plan(MultiPlan &P, const std::vector<MultiItem> &items, const std::vec
       for (int r0 = 0; r0 < m.nrhs; r0 += kMmGroup)
         for (int sp = 0; sp < d.Smm; ++sp)
           for (int t = 0; t < d.ntile; t += kMmTile / 16) mm[m.kind].push_back(make_int4(i, r0, t, sp));
+    }
+    if (d.mm) {
       // the bodies' own blocks in float64, in groups that stay within the groups of 16
       for (int r0 = 0; r0 < m.nrhs;) {
         const int left = std::min(m.nrhs, r0 / kMmGroup * kMmGroup + kMmGroup) - r0;
@@ -485,6 +622,8 @@ int build_plan(MultiPlan &P, const std::vector<MultiItem> &items, const std::vec
   P.nlap = append(fin[0]);
   P.nfin = P.nlap + append(fin[1]);
   for (int k = 0; k < 2; ++k) P.nmm[k] = append(mm[k]);
+  P.nfar = append(fr);
+  P.npack = append(pk);
   BIE_TRY(P.task_buf.reserve(all.size() * sizeof(int4) + 256));
   BIE_TRY(P.desc_buf.reserve(n * sizeof(ItemDesc) + 256));
   BIE_TRY(P.list_buf.reserve(chunks.size() * sizeof(int4) + tiles16.size() * sizeof(int2) + 256));
@@ -492,6 +631,8 @@ int build_plan(MultiPlan &P, const std::vector<MultiItem> &items, const std::vec
   P.fin_task = P.sweep_task + P.nsweep;
   P.mm_task[0] = P.fin_task + P.nfin;
   P.mm_task[1] = P.mm_task[0] + P.nmm[0];
+  P.far_task = P.mm_task[1] + P.nmm[1];
+  P.pack_task = P.far_task + P.nfar;
   if (!all.empty())
     BIE_HIP_CHECK(hipMemcpyAsync(P.sweep_task, all.data(), all.size() * sizeof(int4),
                                  hipMemcpyHostToDevice, s));
@@ -511,6 +652,7 @@ int build_plan(MultiPlan &P, const std::vector<MultiItem> &items, const std::vec
   BIE_HIP_CHECK(hipMemcpyAsync(P.desc, desc.data(), n * sizeof(ItemDesc), hipMemcpyHostToDevice, s));
   BIE_HIP_CHECK(hipStreamSynchronize(s));  // host vectors go out of scope
   P.npart = part;
+  P.nfloat = floats;
   return BIE_OK;
 }
 
@@ -551,8 +693,9 @@ int multi_apply(MultiPlan *&P, const std::vector<MultiItem> &items, const std::v
     P->key_active = active;
     P->valid = true;
   }
-  BIE_TRY(P->ws.reserve((size_t)P->npart * sizeof(double)));
+  BIE_TRY(P->ws.reserve((size_t)P->npart * sizeof(double) + (size_t)P->nfloat * sizeof(float)));
   double *part = P->ws.as<double>();
+  float *s32 = reinterpret_cast<float *>(part + P->npart);
   // inactive items (and FMM items, filled below) start from zero
   for (int i = 0; i < n; ++i)
     if (!active[i]) {
@@ -576,6 +719,13 @@ int multi_apply(MultiPlan *&P, const std::vector<MultiItem> &items, const std::v
       else
         hipLaunchKernelGGL(k_multi_mm<false>, dim3(P->nmm[k]), dim3(kBlock), 0, s, P->mm_task[k],
                            P->desc, in, mm, part);
+    }
+    if (any && P->nfar > 0) {
+      ProfScope prof(BIE_K_FAR_STOKES_F32, s, 0);
+      hipLaunchKernelGGL(k_multi_pack, dim3(P->npack), dim3(kBlock), 0, s, P->pack_task, P->desc, in,
+                         mm, s32);
+      hipLaunchKernelGGL(k_multi_far, dim3(P->nfar), dim3(kBlock), 0, s, P->far_task, P->desc, s32,
+                         mm, part);
     }
     {
       ProfScope prof(P->nlap < P->nfin ? BIE_K_FAR_STOKES_F64 : BIE_K_FAR_LAPLACE_F64, s, 0);

@@ -162,7 +162,7 @@ Layout layout(const std::vector<std::shared_ptr<Request>> &reqs, const bie_opts 
       cur = align8(cur);
       L.first.push_back(i);
       L.items.push_back({r.g, r.kind, 0, cur, uses_fmm(o, r.g), effective_order(o, r.kind),
-                         r.g->fmm_leaf});
+                         r.g->fmm_leaf, true});
     }
     L.off[i] = cur;
     L.items.back().nrhs += r.nrhs;
