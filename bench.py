@@ -473,7 +473,7 @@ def mobility_bench(a):
     for key, kc, flops, bound, kern in (
             ("roofline_m2l", bie2d.BIE_K_FMM_M2L, m2l_flops_per_entry(terms), "mfma",
              f"k_m2l<{terms}>"),
-            ("roofline_near", bie2d.BIE_K_FMM_EVAL, FLOPS_PER_PAIR_STOKES, "alu", "k_near<true>")):
+            ("roofline_near", bie2d.BIE_K_FMM_EVAL, FLOPS_PER_PAIR_STOKES, "alu", "k_near<double, true, 1>")):
         bie2d.bie_profile_select([kc])
         bie2d.bie_profile_enable(True)
         bie2d.bie_mobility_solve(g, ft, o)
@@ -657,12 +657,12 @@ def main():
         "k_lap_far_f32": (bie2d.BIE_K_FAR_LAPLACE_F32, FLOPS_PER_PAIR, "f32", "alu",
                           "k_lap_far_f32<1>"),
         "k_lap_far_f64": (bie2d.BIE_K_FAR_LAPLACE_F64, FLOPS_PER_PAIR, "f64", "alu",
-                          "k_lap_far_f64<1>"),
+                          "k_pair_sweep<0, 1>"),
         "k_m2l": (bie2d.BIE_K_FMM_M2L, m2l_flops_per_entry(order), "f64", "mfma", f"k_m2l<{order}>"),
-        "k_near": (bie2d.BIE_K_FMM_EVAL, FLOPS_PER_PAIR, "f64", "alu", "k_near<false>"),
+        "k_near": (bie2d.BIE_K_FMM_EVAL, FLOPS_PER_PAIR, "f64", "alu", "k_near<double, false, 1>"),
         "k_m2l_f32": (bie2d.BIE_K_FMM_M2L_F32, m2l_flops_per_entry(order32), "f32", "mfma",
                       f"k_m2l_fac_f32<{order32}>"),
-        "k_near_f32": (bie2d.BIE_K_FMM_NEAR_F32, FLOPS_PER_PAIR, "f32", "alu", "k_near_f32<false>"),
+        "k_near_f32": (bie2d.BIE_K_FMM_NEAR_F32, FLOPS_PER_PAIR, "f32", "alu", "k_near<float, false, 1>"),
         "k_lap_epilogue": (bie2d.BIE_K_EPILOGUE, 0, "f64", "alu", "k_lap_epilogue"),
     }
     # one untimed solve with every class recorded picks the dominant kernel class; the timed

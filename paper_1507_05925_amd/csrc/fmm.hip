@@ -681,8 +681,9 @@ __device__ inline V eval_value(const V *b, V w) {
 // self pair, a reciprocal per two pairs and one right-hand side per workgroup: 256,000 Laplace nodes
 // 53 -> 48 us in float64, 31 -> 27.5 us in float32; four right-hand sides of 38,400 nodes
 // 60 -> 33 us; two right-hand sides of 57,600 Stokes nodes 82 -> 70 us. A persistent grid
-// of 256 to 1280 workgroups made whole applies of these four cases up to 1.9 times slower (256:
-// 100 -> 157 us) and at best 0.6% faster (1280, 204,800 unknowns in float32: 89.0 -> 88.5 us).
+// of 256 to 1280 workgroups made whole applies of these four cases up to 1.8 times slower (256:
+// 76 -> 136 us in float32) and at best 0.6% faster (1280, 204,800 unknowns in float32: 89.2 ->
+// 88.7 us).
 constexpr double kNearPad = 16.0;
 template <class T>
 constexpr T near_floor = std::is_same<T, double>::value ? (T)1e-60 : (T)1e-30;
