@@ -690,13 +690,16 @@ constexpr T near_floor = std::is_same<T, double>::value ? (T)1e-60 : (T)1e-30;
 template <class T, int R>
 constexpr int near_occupancy = R > 1 ? 3 : std::is_same<T, double>::value ? 5 : 6;
 
-template <class T, bool STK, int R>
+// VEC (Laplace): the sums are the vectors g = sum s r / |r|^2, whose normal component is taken at the
+// end: for one right-hand side one product fewer per pair than n.g, for more of them more. So
+// it is the form of a lone right-hand side, except in the server's items (FmmFinish::merged): how
+// many right-hand sides those have depends on the requests in flight, and a request's bits must not.
+// (n.g for every lone right-hand side: 0.8 to 1.0% per elastance solve on 256,000 nodes.)
+template <class T, bool STK, int R, bool VEC>
 struct NearShape {
   static constexpr int C = STK ? 2 : 1;
-  // g.x and g.y instead of n.g: one product fewer per pair, float64 only (see near_quad)
-  static constexpr bool G = std::is_same<T, double>::value && !STK && R == 1;
-  static constexpr int V = STK ? 2 * R : G ? 2 : R;  // sums per target
-  static constexpr int ARR = 2 + C * R;                      // staged arrays
+  static constexpr int V = STK || VEC ? 2 * R : R;  // sums per target
+  static constexpr int ARR = 2 + C * R;             // staged arrays
 };
 
 // LDS sources per workgroup (a multiple of 32). A leaf whose runs hold at most this many sources
@@ -708,9 +711,9 @@ constexpr int kNearCap = 512;
 // pair with itself is 1 / near_floor: in float32 it multiplies r.n (zero) before any strength,
 // whose product with 1e30 would overflow from 3e8 on and make that pair infinity times zero. In
 // float64 the product with 1e60 has room for strengths up to 1e248.
-template <class T, bool STK, int R>
+template <class T, bool STK, int R, bool VEC>
 __device__ __forceinline__ void near_quad(const T *buf, int k, T zx, T zy, T nx, T ny,
-                                          T (&acc)[NearShape<T, STK, R>::V]) {
+                                          T (&acc)[NearShape<T, STK, R, VEC>::V]) {
   T dx[4], dy[4], rr[4], inv[4];
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
@@ -727,10 +730,13 @@ __device__ __forceinline__ void near_quad(const T *buf, int k, T zx, T zy, T nx,
   const T *st = buf + 2 * kNearCap + k;
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    if constexpr (NearShape<T, STK, R>::G) {
-      const T t = st[u] * inv[u];
-      acc[0] = fma(dx[u], t, acc[0]);
-      acc[1] = fma(dy[u], t, acc[1]);
+    if constexpr (VEC) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const T t = st[r * kNearCap + u] * inv[u];
+        acc[2 * r] = fma(dx[u], t, acc[2 * r]);
+        acc[2 * r + 1] = fma(dy[u], t, acc[2 * r + 1]);
+      }
     } else {
       const T a = fma(dx[u], nx, dy[u] * ny) * inv[u];
       if constexpr (STK) {
@@ -750,10 +756,10 @@ __device__ __forceinline__ void near_quad(const T *buf, int k, T zx, T zy, T nx,
 }
 
 // Sum over the staged sources [0, n) (n a multiple of 32), eight of this lane's per step.
-template <class T, bool STK, int R>
+template <class T, bool STK, int R, bool VEC>
 __device__ __forceinline__ void near_block(const T *buf, int n, int g, T zx, T zy, T nx, T ny,
-                                           double (&acc)[NearShape<T, STK, R>::V]) {
-  constexpr int V = NearShape<T, STK, R>::V;
+                                           double (&acc)[NearShape<T, STK, R, VEC>::V]) {
+  constexpr int V = NearShape<T, STK, R, VEC>::V;
   for (int k = 0; k < n; k += 32) {
     T sum[V];
     if constexpr (std::is_same<T, double>::value) {
@@ -763,8 +769,8 @@ __device__ __forceinline__ void near_block(const T *buf, int n, int g, T zx, T z
 #pragma unroll
       for (int v = 0; v < V; ++v) sum[v] = (T)0;
     }
-    near_quad<T, STK, R>(buf, k + 4 * g, zx, zy, nx, ny, sum);
-    near_quad<T, STK, R>(buf, k + 16 + 4 * g, zx, zy, nx, ny, sum);
+    near_quad<T, STK, R, VEC>(buf, k + 4 * g, zx, zy, nx, ny, sum);
+    near_quad<T, STK, R, VEC>(buf, k + 16 + 4 * g, zx, zy, nx, ny, sum);
 #pragma unroll
     for (int v = 0; v < V; ++v) {
       if constexpr (std::is_same<T, double>::value) acc[v] = sum[v];
@@ -781,14 +787,14 @@ __device__ __forceinline__ void near_block(const T *buf, int n, int g, T zx, T z
 // chain, and its smaller register footprint leaves room for the chain's waves. Chunks are taken
 // in XCD-contiguous order (xcd_item): neighbouring leaves, which stage mostly the same sources,
 // then run on one XCD and share its L2. q: the charge sets, set r (Laplace) or 3 r (Stokes).
-template <class T, bool STK, int R, class QT>
+template <class T, bool STK, int R, class QT, bool VEC>
 __global__ __launch_bounds__(256, (near_occupancy<T, R>)) void k_near(
     int M, double scale, const int *__restrict__ leaf_start, const double2 *__restrict__ xs,
     const double2 *__restrict__ nrm, const int *__restrict__ perm,
     const int *__restrict__ run_ptr, const int2 *__restrict__ run,
     const int *__restrict__ chunk_leaf, const int *__restrict__ chunk_start,
     const QT *__restrict__ q, double *__restrict__ out) {
-  using N = NearShape<T, STK, R>;
+  using N = NearShape<T, STK, R, VEC>;
   constexpr bool F32 = std::is_same<T, float>::value;
   const int cb = xcd_item(blockIdx.x, gridDim.x);
   const int leaf = chunk_leaf[cb], r0 = blockIdx.y * R;
@@ -841,7 +847,7 @@ __global__ __launch_bounds__(256, (near_occupancy<T, R>)) void k_near(
     }
     pad(total, padded);
     __syncthreads();
-    if (busy) near_block<T, STK, R>(buf, padded, g, zx, zy, nx, ny, acc);
+    if (busy) near_block<T, STK, R, VEC>(buf, padded, g, zx, zy, nx, ny, acc);
   } else {
     for (int e = e0; e < e1; ++e) {
       const int2 kr = run[e];
@@ -851,7 +857,7 @@ __global__ __launch_bounds__(256, (near_occupancy<T, R>)) void k_near(
         stage(base, n, 0);
         pad(n, np);
         __syncthreads();
-        if (busy) near_block<T, STK, R>(buf, np, g, zx, zy, nx, ny, acc);
+        if (busy) near_block<T, STK, R, VEC>(buf, np, g, zx, zy, nx, ny, acc);
       }
     }
   }
@@ -868,8 +874,9 @@ __global__ __launch_bounds__(256, (near_occupancy<T, R>)) void k_near(
       double *u = out + (size_t)(r0 + r) * 2 * M + 2 * (size_t)i;
       u[0] = -(scale / kPi) * acc[2 * r];
       u[1] = -(scale / kPi) * acc[2 * r + 1];
-    } else if constexpr (N::G) {
-      out[(size_t)r0 * M + i] = -(scale / (2.0 * kPi)) * (nv.x * acc[0] + nv.y * acc[1]);
+    } else if constexpr (VEC) {
+      out[(size_t)(r0 + r) * M + i] =
+          -(scale / (2.0 * kPi)) * (nv.x * acc[2 * r] + nv.y * acc[2 * r + 1]);
     } else {
       out[(size_t)(r0 + r) * M + i] = -(scale / (2.0 * kPi)) * acc[r];
     }
@@ -1915,10 +1922,10 @@ void upward_pass(const FmmTree &t, int kind, int nsets, double ih_leaf, const cx
   m2m_passes<P, T>(t, nsets, Mexp, s);
 }
 
-template <class T, bool STK, int R, class QT>
+template <class T, bool STK, int R, bool VEC, class QT>
 void launch_near_group(const FmmTree &t, int groups, double scale, const QT *q, double *out,
                        hipStream_t s) {
-  hipLaunchKernelGGL((k_near<T, STK, R, QT>), dim3(t.nchunk, groups), dim3(256), 0, s, t.M, scale,
+  hipLaunchKernelGGL((k_near<T, STK, R, QT, VEC>), dim3(t.nchunk, groups), dim3(256), 0, s, t.M, scale,
                      t.leaf_start, t.xs, t.nrm, t.perm, t.run_ptr, t.run, t.chunk_leaf,
                      t.chunk_start, q, out);
 }
@@ -1926,10 +1933,13 @@ void launch_near_group(const FmmTree &t, int groups, double scale, const QT *q, 
 // The near field of R right-hand sides, four (Laplace) or two (Stokes) at a time where there are as
 // many: more would need more LDS and registers than the expansion chain leaves.
 template <class T, bool STK, class QT>
-void near_pass(const FmmTree &t, int R, double scale, const QT *q, double *out, hipStream_t s) {
-  if (!STK && R % 4 == 0) launch_near_group<T, STK, STK ? 2 : 4>(t, R / 4, scale, q, out, s);
-  else if (R % 2 == 0) launch_near_group<T, STK, 2>(t, R / 2, scale, q, out, s);
-  else launch_near_group<T, STK, 1>(t, R, scale, q, out, s);
+void near_pass(const FmmTree &t, int R, bool merged, double scale, const QT *q, double *out,
+               hipStream_t s) {
+  constexpr bool vec = std::is_same<T, double>::value && !STK;
+  if (!STK && R % 4 == 0) launch_near_group<T, STK, STK ? 2 : 4, false>(t, R / 4, scale, q, out, s);
+  else if (R % 2 == 0) launch_near_group<T, STK, 2, false>(t, R / 2, scale, q, out, s);
+  else if (vec && !merged) launch_near_group<T, STK, 1, vec>(t, R, scale, q, out, s);
+  else launch_near_group<T, STK, 1, false>(t, R, scale, q, out, s);
 }
 
 constexpr int kNearAtF32 = 0;
@@ -2162,17 +2172,17 @@ int fmm_far_field(bie_geom *g, int kind, int precision, int R, const double *mu,
       ProfScope pe(near32 ? BIE_K_FMM_NEAR_F32 : BIE_K_FMM_EVAL, plan.side,
                    (t.near_pairs - M) * R);
       if (kind == 0 && near32)
-        near_pass<float, false>(t, R, g->pair_scale, reinterpret_cast<const float2 *>(wq), partial,
-                                plan.side);
+        near_pass<float, false>(t, R, finish.merged, g->pair_scale,
+                                reinterpret_cast<const float2 *>(wq), partial, plan.side);
       else if (near32)
-        near_pass<float, true>(t, R, g->pair_scale, reinterpret_cast<const double2 *>(wq), partial,
-                               plan.side);
+        near_pass<float, true>(t, R, finish.merged, g->pair_scale,
+                               reinterpret_cast<const double2 *>(wq), partial, plan.side);
       else if (kind == 0)
-        near_pass<double, false>(t, R, g->pair_scale, reinterpret_cast<const double2 *>(wq), partial,
-                                 plan.side);
+        near_pass<double, false>(t, R, finish.merged, g->pair_scale,
+                                 reinterpret_cast<const double2 *>(wq), partial, plan.side);
       else
-        near_pass<double, true>(t, R, g->pair_scale, reinterpret_cast<const double2 *>(wq), partial,
-                                plan.side);
+        near_pass<double, true>(t, R, finish.merged, g->pair_scale,
+                                reinterpret_cast<const double2 *>(wq), partial, plan.side);
       BIE_HIP_CHECK(hipGetLastError());
     }
     if (finish.with_L) {  // the body sums for the evaluation, behind the near field, which ends

@@ -223,13 +223,15 @@ namespace bie {
 // ---- kernels.hip: operator pieces -------------------------------------------------------
 // kind: 0 = Laplace (len = M per rhs), 1 = Stokes (len = 2M per rhs); 2 and 3 are the
 // completed double layers of the capacitance and resistance problems (Laplace, Stokes)
+// merged: how many right-hand sides go together depends on other callers; FMM applies then give
+// each the same bits whatever their number
 int apply_operator(bie_geom *g, int kind, int precision, int method, int with_L, double alpha,
-                   int nrhs, const double *mu, double *out, hipStream_t s);
+                   int nrhs, const double *mu, double *out, hipStream_t s, bool merged = false);
 // the same with a caller-provided workspace of ws_bytes >= apply_workspace_bytes(...) bytes
 // (kinds 0 and 1; method BIE_DIRECT or BIE_FMM)
 int apply_operator_ws(bie_geom *g, int kind, int precision, int method, int with_L,
                       double alpha, int nrhs, const double *mu, double *out, void *ws,
-                      size_t ws_bytes, hipStream_t s);
+                      size_t ws_bytes, hipStream_t s, bool merged = false);
 size_t apply_workspace_bytes(const bie_geom *g, int kind, int method, int nrhs);
 int incident_density(bie_geom *g, int kind, int nrhs, const double *data, double *dens,
                      hipStream_t s);
@@ -349,6 +351,7 @@ struct FmmFinish {
   double *out = nullptr;
   double alpha = 1.0;
   int with_L = 0;
+  bool merged = false;  // see apply_operator
 };
 int fmm_far_field(bie_geom *g, int kind, int precision, int nrhs, const double *mu, double *s64,
                   double *partial, hipStream_t s, int order, int leaf,

@@ -646,7 +646,7 @@ static size_t direct_workspace_bytes(const bie_geom *g, int kind) {
 // Far-field partials per rhs chunk and the epilogue. Chunks of <= 8 (Laplace) / 4 (Stokes) rhs
 // share each pair's geometry work.
 int apply_operator(bie_geom *g, int kind, int precision, int method, int with_L, double alpha,
-                   int nrhs, const double *mu, double *out, hipStream_t st) {
+                   int nrhs, const double *mu, double *out, hipStream_t st, bool merged) {
   if (kind == 2 || kind == 3) return dl_apply(g, kind - 2, with_L, alpha, nrhs, mu, out, st);
   if (method == BIE_AUTO) method = method_is_fmm(method, g->M) ? BIE_FMM : BIE_DIRECT;
   if (nrhs < 1) {
@@ -656,12 +656,12 @@ int apply_operator(bie_geom *g, int kind, int precision, int method, int with_L,
   BIE_TRY(g->ws_apply.reserve(std::max(apply_workspace_bytes(g, kind, method, nrhs),
                                        direct_workspace_bytes(g, kind))));
   return apply_operator_ws(g, kind, precision, method, with_L, alpha, nrhs, mu, out,
-                           g->ws_apply.ptr, g->ws_apply.bytes, st);
+                           g->ws_apply.ptr, g->ws_apply.bytes, st, merged);
 }
 
 int apply_operator_ws(bie_geom *g, int kind, int precision, int method, int with_L,
                       double alpha, int nrhs, const double *mu, double *out, void *ws,
-                      size_t ws_bytes, hipStream_t st) {
+                      size_t ws_bytes, hipStream_t st, bool merged) {
   if (precision != BIE_FP64 && precision != BIE_MIXED) {
     set_error("precision must be BIE_FP64 or BIE_MIXED");
     return BIE_EINVAL;
@@ -721,6 +721,7 @@ int apply_operator_ws(bie_geom *g, int kind, int precision, int method, int with
       fin.out = out + off;
       fin.alpha = alpha;
       fin.with_L = with_L;
+      fin.merged = merged;
       BIE_TRY(fmm_far_field(g, kind, precision, R, mu + off, s64 + off, partial, st, g->fmm_order,
                             leaf, fin));
       r0 += R;

@@ -766,7 +766,8 @@ int multi_apply(MultiPlan *&P, const std::vector<MultiItem> &items, const std::v
       items[i].g->fmm_order = items[i].fmm_order;  // the caller's expansion order and leaf size
       items[i].g->fmm_leaf = items[i].fmm_leaf;
       rc = apply_operator(items[i].g, items[i].kind, f32_of(i) ? BIE_MIXED : BIE_FP64, BIE_FMM, 1,
-                          1.0, items[i].nrhs, in + items[i].io, out + items[i].io, P->pool[on[i]]);
+                          1.0, items[i].nrhs, in + items[i].io, out + items[i].io, P->pool[on[i]],
+                          items[i].merged);
     }
   for (int k = 0; k < used; ++k) {
     BIE_HIP_CHECK(hipEventRecord(P->join[k], P->pool[k]));
