@@ -181,12 +181,14 @@ int gmres(SysSet &ss, int precision, const double *f, double *x, bool x_is_zero,
   // system), the tag base, (from x = 0) the norms of f, and the staging of the coefficients y
   const size_t slot = (size_t)S * hs + S, fn_at = 2 * slot + 1, y_at = fn_at + S;
   BIE_TRY(mem.ensure_pinned((y_at + (size_t)S * hs) * sizeof(double)));
-  // From x = 0 the first cycle starts from r = f without a host round trip: its Givens
-  // recurrence runs on f / ||f|| (beta 1, relative residuals directly), and the norms, copied to
-  // pinned memory behind the norm kernel, are read once the cycle's steps are complete, to scale
-  // its coefficients y. Every system then starts active (a zero f gives V_0 = 0 and a zero
-  // correction); with a tolerance of 1 or more a system would start converged, and its device
-  // norm would have to be cleared from the host: those calls read the norms first.
+  // From x = 0 the first cycle starts from r = f: its Givens recurrence runs on f / ||f||
+  // (beta 1, relative residuals directly), and its coefficients y are scaled by the norms at its
+  // end. The norms are then not needed before the cycle's steps are complete: copied to pinned
+  // memory behind the norm kernel, they cost no host round trip. Every system then starts active (a
+  // zero f gives V_0 = 0 and a zero correction); with a tolerance of 1 or more a system would
+  // start converged, and its device norm would have to be cleared from the host: those calls
+  // read the norms first. (Only that: the recurrence is the same, as a converged system of another
+  // item or request must not change a bit of this one's.)
   bool defer = x_is_zero;
   for (int r = 0; r < S; ++r) defer = defer && tol[r] < 1.0;
   bool fn_pending = false;
@@ -255,7 +257,8 @@ int gmres(SysSet &ss, int precision, const double *f, double *x, bool x_is_zero,
     if (zeroed) BIE_TRY(write_dev(mem, wk.nrm, beta, s));
     BIE_TRY(seg_scale_to(sg, from_f ? f : wk.r, wk.nrm, wk.V, s));
     std::fill(gv.begin(), gv.end(), 0.0);
-    for (int r = 0; r < S; ++r) gv[(size_t)r * (m + 1)] = beta[r];
+    for (int r = 0; r < S; ++r)
+      gv[(size_t)r * (m + 1)] = from_f ? (beta[r] > 0.0 ? 1.0 : 0.0) : beta[r];
     std::vector<int> jdone(S, -1);
     int jend = -1;
     // Arnoldi step j: apply, CGS2 against V_0..V_j, V_{j+1} = w / ||w||, and the new Hessenberg
@@ -447,7 +450,7 @@ int gmres(SysSet &ss, int precision, const double *f, double *x, bool x_is_zero,
         col[j + 1] = 0.0;
         gg[j + 1] = -sv[j] * gg[j];
         gg[j] = c[j] * gg[j];
-        const double res = std::fabs(gg[j + 1]) / fnorm[r];
+        const double res = std::fabs(gg[j + 1]) / (from_f ? 1.0 : fnorm[r]);
         gworst[group_of[r]] = std::max(gworst[group_of[r]], res / tol[r]);
         if (verbosity() >= 2 && r == 0)
           std::fprintf(stderr, "[bie]   j=%d est rel res=%.3e hn=%.3e\n", j, res, hn);
@@ -465,11 +468,11 @@ int gmres(SysSet &ss, int precision, const double *f, double *x, bool x_is_zero,
     // next basis vector and candidate), and that the copy of the norms of f, queued before the
     // first step, is complete.
     // the first cycle from f ran on f / ||f||: its coefficients scale by ||f||
-    std::vector<double> yscale(S, 1.0);
     if (fn_pending) {
-      for (int r = 0; r < S; ++r) fnorm[r] = yscale[r] = mem.pinned[fn_at + r];
+      for (int r = 0; r < S; ++r) fnorm[r] = mem.pinned[fn_at + r];
       fn_pending = false;
     }
+    const std::vector<double> yscale = from_f ? fnorm : std::vector<double>(S, 1.0);
     // y = H^{-1} g (upper triangular), x += V y
     const int nv = jend + 1;
     std::vector<double> yv((size_t)S * hs, 0.0);
