@@ -691,10 +691,12 @@ template <class T, int R>
 constexpr int near_occupancy = R > 1 ? 3 : std::is_same<T, double>::value ? 5 : 6;
 
 // VEC (Laplace): the sums are the vectors g = sum s r / |r|^2, whose normal component is taken at the
-// end: for one right-hand side one product fewer per pair than n.g, for more of them more. So
-// it is the form of a lone right-hand side, except in the server's items (FmmFinish::merged): how
-// many right-hand sides those have depends on the requests in flight, and a request's bits must not.
-// (n.g for every lone right-hand side: 0.8 to 1.0% per elastance solve on 256,000 nodes.)
+// end, in float64. In float32 always: n.g per pair would round the normal (at the same cost for one
+// right-hand side; for four of 256,000 nodes 100 us against 119). In float64 it is one product
+// fewer per pair for one right-hand side, and more for more of them: the form of a lone right-hand
+// side, except in the server's items (FmmFinish::merged): how many right-hand sides those have
+// depends on the requests in flight, and a request's bits must not. (n.g for every lone right-hand
+// side: 0.8 to 1.0% per elastance solve on 256,000 nodes.)
 template <class T, bool STK, int R, bool VEC>
 struct NearShape {
   static constexpr int C = STK ? 2 : 1;
@@ -708,7 +710,7 @@ struct NearShape {
 constexpr int kNearCap = 512;
 
 // Adds the quad of staged sources at position k to one target's sums. The reciprocal of a target's
-// pair with itself is 1 / near_floor: in float32 it multiplies r.n (zero) before any strength,
+// pair with itself is 1 / near_floor: in float32 it multiplies r (zero) before any strength,
 // whose product with 1e30 would overflow from 3e8 on and make that pair infinity times zero. In
 // float64 the product with 1e60 has room for strengths up to 1e248.
 template <class T, bool STK, int R, bool VEC>
@@ -730,7 +732,14 @@ __device__ __forceinline__ void near_quad(const T *buf, int k, T zx, T zy, T nx,
   const T *st = buf + 2 * kNearCap + k;
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    if constexpr (VEC) {
+    if constexpr (VEC && std::is_same<T, float>::value) {
+      const T ux = dx[u] * inv[u], uy = dy[u] * inv[u];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        acc[2 * r] = fma(ux, st[r * kNearCap + u], acc[2 * r]);
+        acc[2 * r + 1] = fma(uy, st[r * kNearCap + u], acc[2 * r + 1]);
+      }
+    } else if constexpr (VEC) {
 #pragma unroll
       for (int r = 0; r < R; ++r) {
         const T t = st[r * kNearCap + u] * inv[u];
@@ -1935,11 +1944,11 @@ void launch_near_group(const FmmTree &t, int groups, double scale, const QT *q, 
 template <class T, bool STK, class QT>
 void near_pass(const FmmTree &t, int R, bool merged, double scale, const QT *q, double *out,
                hipStream_t s) {
-  constexpr bool vec = std::is_same<T, double>::value && !STK;
-  if (!STK && R % 4 == 0) launch_near_group<T, STK, STK ? 2 : 4, false>(t, R / 4, scale, q, out, s);
-  else if (R % 2 == 0) launch_near_group<T, STK, 2, false>(t, R / 2, scale, q, out, s);
-  else if (vec && !merged) launch_near_group<T, STK, 1, vec>(t, R, scale, q, out, s);
-  else launch_near_group<T, STK, 1, false>(t, R, scale, q, out, s);
+  constexpr bool f32 = std::is_same<T, float>::value && !STK;  // vector sums for any R
+  if (!STK && R % 4 == 0) launch_near_group<T, STK, STK ? 2 : 4, f32>(t, R / 4, scale, q, out, s);
+  else if (R % 2 == 0) launch_near_group<T, STK, 2, f32>(t, R / 2, scale, q, out, s);
+  else if (!merged) launch_near_group<T, STK, 1, !STK>(t, R, scale, q, out, s);
+  else launch_near_group<T, STK, 1, f32>(t, R, scale, q, out, s);
 }
 
 constexpr int kNearAtF32 = 0;
