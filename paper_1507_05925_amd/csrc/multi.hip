@@ -174,17 +174,20 @@ __global__ __launch_bounds__(kBlock, 2) void k_multi_sweep(const int4 *__restric
 }
 
 // Float32 pairs of different bodies on the matrix cores: for 16 targets and four sources a lane forms
-// one kernel value (target lane % 16, source lane / 16), the A operand of a 16 x 16 x 4 product
-// whose B operand holds the sources' strengths of 16 right-hand sides. A Laplace value is one
-// operand, a Stokes pair's symmetric 2 x 2 block three, used in four products. A workgroup takes up
+// one pair's kernel (target lane % 16, source lane / 16), the A operands of 16 x 16 x 4 products
+// whose B operand holds the sources' strengths of 16 right-hand sides. Laplace: r / |r|^2, two
+// operands, the normal component taken at the end in float64; Stokes: the symmetric 2 x 2 block,
+// three operands in four products. A workgroup takes up
 // to eight 16-target tiles (two per wave, each of one body) against one split's source chunks
-// (at most 64 nodes of one body): coordinates relative to the source body's centroid in float32, a
-// chunk's products added into float64 (the float32 scheme of the single-geometry sweep, which
-// adds once per body). Bound by the vector work per value and the products, which do not overlap:
-// per 64 pairs and 16 right-hand sides about 75 (Laplace) and 200 (Stokes) cycles, where the vector
-// sweep took 34 (Stokes) cycles per right-hand side. P and M of 32 geometries of 8 to 128 bodies:
-// 5.4 -> 4.0 s with the block preconditioner, 19.6 -> 13.3 s without (in float64 throughout: 5.6
-// and 23.9 s).
+// (at most 64 nodes of one body): coordinates relative to the source body's centroid in float32.
+// Two products (eight sources) are summed at a time, those sums over a chunk, the chunks in
+// float64; and the Stokes block's reciprocal takes a Newton step. So the error is at most that
+// of the single-geometry float32 sweep, whose sums run over a body (one sum per chunk and rounded
+// Laplace normals: up to 1.36 times it at 32 nodes per body; now 0.93 at 32 and 0.6 at 96). Bound
+// by the vector work per pair and the products, which do not overlap: per 64 pairs and 16
+// right-hand sides about 120 (Laplace) and 230 (Stokes) cycles, where the vector sweep took 34
+// (Stokes) cycles per right-hand side. P and M of 32 geometries of 8 to 128 bodies with the block
+// preconditioner: 4.0 s, by the vector sweep 5.4 (in float64 throughout: 5.6).
 typedef float mm_f4 __attribute__((ext_vector_type(4)));
 
 template <bool STK>
@@ -194,6 +197,7 @@ __global__ __launch_bounds__(kBlock) void k_multi_mm(const int4 *__restrict__ ta
                                                      const ItemMask mm,
                                                      double *__restrict__ partial) {
   constexpr int C = STK ? 2 : 1;
+  constexpr int STEPS = 2;               // products per accumulator before they join the chunk's sum
   constexpr int ROW = kMmGroup * C + 2;  // floats per staged source (padded: writes spread over banks)
   __shared__ float2 xs[kMmChunk];
   __shared__ float ss[kMmChunk * ROW];
@@ -208,8 +212,8 @@ __global__ __launch_bounds__(kBlock) void k_multi_mm(const int4 *__restrict__ ta
   int body[kMmTiles], first[kMmTiles];
   double cx[kMmTiles], cy[kMmTiles];
   float2 pr[kMmTiles];
-  float nx[kMmTiles], ny[kMmTiles], tx[kMmTiles], ty[kMmTiles];
-  double acc[kMmTiles][C][4];
+  float nx[kMmTiles], ny[kMmTiles], tx[kMmTiles], ty[kMmTiles];  // (normals: Stokes only)
+  double acc[kMmTiles][2][4];
 #pragma unroll
   for (int u = 0; u < kMmTiles; ++u) {
     const int ti = t.z + wv * kMmTiles + u;
@@ -223,11 +227,11 @@ __global__ __launch_bounds__(kBlock) void k_multi_mm(const int4 *__restrict__ ta
       cy[u] = gload(d.yc, body[u]);
       const float *p = reinterpret_cast<const float *>(d.xr);
       pr[u] = make_float2(gload(p, 2LL * i), gload(p, 2LL * i + 1));
-      nx[u] = (float)gload(d.nx, i);
-      ny[u] = (float)gload(d.ny, i);
+      nx[u] = STK ? (float)gload(d.nx, i) : 0.0f;
+      ny[u] = STK ? (float)gload(d.ny, i) : 0.0f;
     }
 #pragma unroll
-    for (int c = 0; c < C; ++c)
+    for (int c = 0; c < 2; ++c)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[u][c][e] = 0.0;
   }
@@ -278,39 +282,55 @@ __global__ __launch_bounds__(kBlock) void k_multi_mm(const int4 *__restrict__ ta
         ty[u] = (float)((cy[u] - sy) + (double)pr[u].y);
       }
     }
-    mm_f4 y[kMmTiles][C];
+    mm_f4 y[kMmTiles][2];
 #pragma unroll
     for (int u = 0; u < kMmTiles; ++u)
 #pragma unroll
-      for (int a = 0; a < C; ++a) y[u][a] = mm_f4{0.0f, 0.0f, 0.0f, 0.0f};
-    for (int kb = 0; kb < n; kb += 4) {
-      const int k = kb + q;
-      const float2 p = xs[k];
-      float b[C];
+      for (int a = 0; a < 2; ++a) y[u][a] = mm_f4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int kb = 0; kb < n; kb += 4 * STEPS) {
+      mm_f4 z[kMmTiles][2];
 #pragma unroll
-      for (int a = 0; a < C; ++a) b[a] = ss[k * ROW + C * j + a];
+      for (int u = 0; u < kMmTiles; ++u)
 #pragma unroll
-      for (int u = 0; u < kMmTiles; ++u) {
-        if (body[u] == cb || body[u] < 0) continue;  // (wave-uniform)
-        const float dx = tx[u] - p.x, dy = ty[u] - p.y;
-        const float inv = __builtin_amdgcn_rcpf(fmaf(dx, dx, dy * dy));
-        const float a = fmaf(dx, nx[u], dy * ny[u]) * inv;
-        if constexpr (STK) {
-          const float g = a * inv, gx = g * dx, gy = g * dy;
-          const float xx = gx * dx, xy = gx * dy, yy = gy * dy;
-          y[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xx, b[0], y[u][0], 0, 0, 0);
-          y[u][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(xy, b[0], y[u][1], 0, 0, 0);
-          y[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xy, b[C - 1], y[u][0], 0, 0, 0);
-          y[u][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(yy, b[C - 1], y[u][1], 0, 0, 0);
-        } else {
-          y[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b[0], y[u][0], 0, 0, 0);
+        for (int a = 0; a < 2; ++a) z[u][a] = mm_f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int w = 0; w < STEPS; ++w) {
+        if (kb + 4 * w >= n) break;
+        const int k = kb + 4 * w + q;
+        const float2 p = xs[k];
+        float b[C];
+#pragma unroll
+        for (int a = 0; a < C; ++a) b[a] = ss[k * ROW + C * j + a];
+#pragma unroll
+        for (int u = 0; u < kMmTiles; ++u) {
+          if (body[u] == cb || body[u] < 0) continue;  // (wave-uniform)
+          const float dx = tx[u] - p.x, dy = ty[u] - p.y;
+          const float rr = fmaf(dx, dx, dy * dy);
+          float inv = __builtin_amdgcn_rcpf(rr);
+          if constexpr (STK) {
+            inv = fmaf(inv, fmaf(-rr, inv, 1.0f), inv);
+            const float a = fmaf(dx, nx[u], dy * ny[u]) * inv;
+            const float g = a * inv, gx = g * dx, gy = g * dy;
+            const float xx = gx * dx, xy = gx * dy, yy = gy * dy;
+            z[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xx, b[0], z[u][0], 0, 0, 0);
+            z[u][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(xy, b[0], z[u][1], 0, 0, 0);
+            z[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xy, b[C - 1], z[u][0], 0, 0, 0);
+            z[u][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(yy, b[C - 1], z[u][1], 0, 0, 0);
+          } else {
+            z[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(dx * inv, b[0], z[u][0], 0, 0, 0);
+            z[u][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(dy * inv, b[0], z[u][1], 0, 0, 0);
+          }
         }
       }
+#pragma unroll
+      for (int u = 0; u < kMmTiles; ++u)
+#pragma unroll
+        for (int a = 0; a < 2; ++a) y[u][a] += z[u][a];
     }
 #pragma unroll
     for (int u = 0; u < kMmTiles; ++u)
 #pragma unroll
-      for (int a = 0; a < C; ++a)
+      for (int a = 0; a < 2; ++a)
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[u][a][e] += (double)y[u][a][e];
     __syncthreads();  // the chunk is no longer read
@@ -327,8 +347,12 @@ __global__ __launch_bounds__(kBlock) void k_multi_mm(const int4 *__restrict__ ta
     for (int e = 0; e < 4; ++e) {
       const int i = first[u] + 4 * q + e;
       if (i >= b1) continue;
-#pragma unroll
-      for (int a = 0; a < C; ++a) o[(long long)C * i + a] = f * acc[u][a][e];
+      if constexpr (STK) {
+        o[2LL * i] = f * acc[u][0][e];
+        o[2LL * i + 1] = f * acc[u][1][e];
+      } else {
+        o[i] = f * (gload(d.nx, i) * acc[u][0][e] + gload(d.ny, i) * acc[u][1][e]);
+      }
     }
   }
 }
