@@ -61,6 +61,10 @@ constexpr int kMmTile = 16 * kMmTiles * 4;         // targets per workgroup, at 
 // 4.8 / 10.2 / 20.8; 29,568 nodes 21.0 / 47.5 / 155 against 14.4 / 32.1 / 94.2.
 constexpr int kFarNodes = 12288;
 constexpr int kFarGroup = 4;
+// They take the matrix cores' sweep from kMmRhsLarge right-hand sides on (8 / 10 / 12 / 16 on 19,872
+// nodes without preconditioner: vector 79 / 103 / 115 / 151 ms, matrix cores 102 / 111 / 116 / 131;
+// on 30,688 174 / 231 / 259 / 341 and 234 / 257 / 267 / 305).
+constexpr int kMmRhsLarge = 12;
 
 // Right-hand side group sizes of each kind.
 constexpr int kGroups[2][5] = {{8, 4, 3, 2, 1}, {4, 3, 2, 1, 0}};
@@ -535,11 +539,26 @@ __global__ __launch_bounds__(kBlock) void k_multi_finish(int ntask, int nlap,
   else finish_task<true>(t, d, f32, mu, partial, out);
 }
 
-// Source splits of an item: from the geometry alone, about 256 workgroups per rhs group with at
-// least kBlock sources each (a batch has several groups and items to fill the compute units).
-int item_splits(int M) {
-  const int tiles = (M + kSweepTile - 1) / kSweepTile;
-  return std::max(1, std::min(256 / tiles, M / kBlock));
+// Source splits of an item whose targets make `tiles` workgroups, from the geometry alone: up to about
+// 256 workgroups per rhs group (a batch has several groups and items to fill the compute units), and
+// from 8,192 nodes on, where one item may be the whole batch, up to 1,024 with at least 2,048 sources
+// each. Of these counts the one whose fullest compute unit is done first (within 3% the smallest),
+// a lone workgroup running at 0.85 of the rate of several on a compute unit. One elastance request
+// on 17,248 nodes 5.3 -> 3.1 ms per solve with 7 splits instead of one, 16 mobility ones 47 -> 30; on
+// 8,416 nodes 1.4 with 3 splits (198 workgroups) and 1.6 with 4 (264).
+int item_splits(int M, int tiles) {
+  const int most = std::max(256 / tiles, std::min(1024 / tiles, M / 2048));
+  int best = 1;
+  double least = 1e300;
+  for (int S = 1; S <= most; ++S) {
+    const int n = (S * tiles + 255) / 256;
+    const double time = n / (double)S / (n > 1 ? 1.0 : 0.85);
+    if (time < 0.97 * least) {
+      least = time;
+      best = S;
+    }
+  }
+  return best;
 }
 
 // The next right-hand side group of kind's items when `left` remain.
@@ -561,7 +580,8 @@ int build_plan(MultiPlan &P, const std::vector<MultiItem> &items, const std::vec
     const MultiItem &m = items[i];
     bie_geom *g = m.g;
     ItemDesc &d = desc[i];
-    const int want = item_splits(g->M);
+    const int want = std::max(1, std::min(item_splits(g->M, (g->M + kSweepTile - 1) / kSweepTile),
+                                          g->M / kBlock));
     d = ItemDesc{};
     d.M = g->M;
     d.N = g->N;
@@ -577,8 +597,9 @@ int build_plan(MultiPlan &P, const std::vector<MultiItem> &items, const std::vec
     d.part = part;
     if (!active[i] || m.fmm) continue;
     const long long len = g->M * (m.kind == 0 ? 1LL : 2LL);
-    const bool cores = !m.merged && m.nrhs >= kMmRhs && n <= kMaxPrecGroups;
-    const bool far = !cores && m.kind == 1 && g->M >= kFarNodes && n <= kMaxPrecGroups;
+    const bool large = m.kind == 1 && g->M >= kFarNodes;
+    const bool cores = !m.merged && m.nrhs >= (large ? kMmRhsLarge : kMmRhs) && n <= kMaxPrecGroups;
+    const bool far = !cores && large && n <= kMaxPrecGroups;
     d.mm = cores || far;
     if (far) {
       d.body_of = g->body_of;
@@ -604,7 +625,9 @@ int build_plan(MultiPlan &P, const std::vector<MultiItem> &items, const std::vec
       d.ntile = (int)(tiles16.size() - tile_at[i]);
       d.nchunk = (int)(chunks.size() - chunk_at[i]);
       const int wgs = (d.ntile + kMmTile / 16 - 1) / (kMmTile / 16);
-      const int smm = std::max(1, std::min(256 / wgs, d.nchunk / 4));
+      const int groups = (m.nrhs + kMmGroup - 1) / kMmGroup;  // (several fill the chip by themselves)
+      const int smm = std::max(1, std::min(wgs * groups < 768 ? item_splits(g->M, wgs) : 256 / wgs,
+                                           d.nchunk / 4));
       d.cper = (d.nchunk + smm - 1) / smm;
       d.Smm = (d.nchunk + d.cper - 1) / d.cper;
       for (int r0 = 0; r0 < m.nrhs; r0 += kMmGroup)
