@@ -114,12 +114,15 @@ void multi_destroy(MultiPlan *p) {
 
 namespace {
 
-// The items that take the float32 sweep in an apply: those whose bit is set, where they have it.
+// The items that take the float32 sweep in an apply, where they have it: none, all, or (sets of at
+// most kMaxPrecGroups items only) those whose bit is set.
+enum MaskMode { kNone = 0, kAll = 1, kBits = 2 };
 struct ItemMask {
+  int mode;
   unsigned long long w[kMaxPrecGroups / 64];
 };
 __device__ __forceinline__ bool in_mask(const ItemMask &m, int it) {
-  return (m.w[it >> 6] >> (it & 63)) & 1ull;
+  return m.mode == kBits ? (m.w[it >> 6] >> (it & 63)) & 1ull : m.mode == kAll;
 }
 
 // Float64 sweep task: all sources of split sp, or (own) body sp's block of its own targets, which
@@ -598,8 +601,8 @@ int build_plan(MultiPlan &P, const std::vector<MultiItem> &items, const std::vec
     if (!active[i] || m.fmm) continue;
     const long long len = g->M * (m.kind == 0 ? 1LL : 2LL);
     const bool large = m.kind == 1 && g->M >= kFarNodes;
-    const bool cores = !m.merged && m.nrhs >= (large ? kMmRhsLarge : kMmRhs) && n <= kMaxPrecGroups;
-    const bool far = !cores && large && n <= kMaxPrecGroups;
+    const bool cores = !m.merged && m.nrhs >= (large ? kMmRhsLarge : kMmRhs);
+    const bool far = !cores && large;
     d.mm = cores || far;
     if (far) {
       d.body_of = g->body_of;
@@ -751,8 +754,9 @@ int multi_apply(MultiPlan *&P, const std::vector<MultiItem> &items, const std::v
     }
   if (P->nsweep > 0) {
     ItemMask mm{};
-    bool any = false;
-    for (int i = 0; i < n && n <= kMaxPrecGroups; ++i)
+    mm.mode = item_f32 ? kBits : precision == BIE_MIXED ? kAll : kNone;
+    bool any = mm.mode == kAll;
+    for (int i = 0; item_f32 && i < n; ++i)
       if (f32_of(i)) {
         mm.w[i >> 6] |= 1ull << (i & 63);
         any = true;
