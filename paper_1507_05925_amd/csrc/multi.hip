@@ -46,10 +46,16 @@ struct ItemDesc {
   const double *xc, *yc;
 };
 
-// Right-hand sides per group of the float32 matrix-core sweep, and the fewest an item (and a group)
-// has for it.
+// Right-hand sides per group of the float32 matrix-core sweep, and the fewest an item of each kind has
+// for it: a half-empty group costs as much as a full one. Laplace 8 / 16 / 24 / 32 / 48 on six
+// geometries of 4,400 nodes without preconditioner: float64 5.4 / 9.6 / 13.4 / 17.6 / 25.8 ms, matrix
+// cores 8.0 / 9.5 / 13.8 / 15.8 / 23.9; Stokes 8 / 16 / 48: 35 / 67 / 202 and 34 / 46 / 131.
+// Laplace items of fewer than kMmNodes nodes per body on average stay in float64: their error would
+// be above that of the single-geometry float32 sweep (1.02 times at 16 nodes per body, 1.04 at 8,
+// 0.78 at 32).
 constexpr int kMmGroup = 16;
-constexpr int kMmRhs = 8;
+constexpr int kMmRhs[2] = {25, 8};
+constexpr int kMmNodes = 32;
 constexpr int kMmChunk = 64;                       // sources staged at a time (one body's)
 constexpr int kMmTiles = 2;                        // 16-target tiles per wave
 constexpr int kMmTile = 16 * kMmTiles * 4;         // targets per workgroup, at most
@@ -181,20 +187,19 @@ __global__ __launch_bounds__(kBlock, 2) void k_multi_sweep(const int4 *__restric
 }
 
 // Float32 pairs of different bodies on the matrix cores: for 16 targets and four sources a lane forms
-// one pair's kernel (target lane % 16, source lane / 16), the A operands of 16 x 16 x 4 products
-// whose B operand holds the sources' strengths of 16 right-hand sides. Laplace: r / |r|^2, two
-// operands, the normal component taken at the end in float64; Stokes: the symmetric 2 x 2 block,
-// three operands in four products. A workgroup takes up
+// one kernel value (target lane % 16, source lane / 16), the A operand of a 16 x 16 x 4 product
+// whose B operand holds the sources' strengths of 16 right-hand sides. A Laplace value is one
+// operand, a Stokes pair's symmetric 2 x 2 block three, used in four products. A workgroup takes up
 // to eight 16-target tiles (two per wave, each of one body) against one split's source chunks
 // (at most 64 nodes of one body): coordinates relative to the source body's centroid in float32.
-// Two products (eight sources) are summed at a time, those sums over a chunk, the chunks in
-// float64; and the Stokes block's reciprocal takes a Newton step. So the error is at most that
-// of the single-geometry float32 sweep, whose sums run over a body (one sum per chunk and rounded
-// Laplace normals: up to 1.36 times it at 32 nodes per body; now 0.93 at 32 and 0.6 at 96). Bound
-// by the vector work per pair and the products, which do not overlap: per 64 pairs and 16
-// right-hand sides about 120 (Laplace) and 230 (Stokes) cycles, where the vector sweep took 34
-// (Stokes) cycles per right-hand side. P and M of 32 geometries of 8 to 128 bodies with the block
-// preconditioner: 4.0 s, by the vector sweep 5.4 (in float64 throughout: 5.6).
+// Laplace normals are pairs of floats, the Stokes block's reciprocal takes a Newton step, and two
+// products (eight sources) are summed at a time, those sums over a chunk, the chunks in float64. So the
+// error is at most that of the single-geometry float32 sweep, whose sums run over a body (one sum
+// per chunk and rounded normals: up to 1.36 times it at 32 nodes per body; now 0.78 Laplace and
+// 0.93 Stokes at 32, 0.5 at 96). Bound by the vector work per value and the products, which do not
+// overlap: per 64 pairs and 16 right-hand sides about 100 (Laplace) and 230 (Stokes) cycles, where the
+// vector sweep took 34 (Stokes) cycles per right-hand side. P and M of 32 geometries of 8 to 128
+// bodies with the block preconditioner: 4.0 s, by the vector sweep 5.4 (in float64 throughout: 5.6).
 typedef float mm_f4 __attribute__((ext_vector_type(4)));
 
 template <bool STK>
@@ -219,8 +224,9 @@ __global__ __launch_bounds__(kBlock) void k_multi_mm(const int4 *__restrict__ ta
   int body[kMmTiles], first[kMmTiles];
   double cx[kMmTiles], cy[kMmTiles];
   float2 pr[kMmTiles];
-  float nx[kMmTiles], ny[kMmTiles], tx[kMmTiles], ty[kMmTiles];  // (normals: Stokes only)
-  double acc[kMmTiles][2][4];
+  float nx[kMmTiles], ny[kMmTiles], tx[kMmTiles], ty[kMmTiles];
+  float nxl[kMmTiles], nyl[kMmTiles];  // Laplace: the normals' low parts
+  double acc[kMmTiles][C][4];
 #pragma unroll
   for (int u = 0; u < kMmTiles; ++u) {
     const int ti = t.z + wv * kMmTiles + u;
@@ -234,11 +240,14 @@ __global__ __launch_bounds__(kBlock) void k_multi_mm(const int4 *__restrict__ ta
       cy[u] = gload(d.yc, body[u]);
       const float *p = reinterpret_cast<const float *>(d.xr);
       pr[u] = make_float2(gload(p, 2LL * i), gload(p, 2LL * i + 1));
-      nx[u] = STK ? (float)gload(d.nx, i) : 0.0f;
-      ny[u] = STK ? (float)gload(d.ny, i) : 0.0f;
+      const double n1 = gload(d.nx, i), n2 = gload(d.ny, i);
+      nx[u] = (float)n1;
+      ny[u] = (float)n2;
+      nxl[u] = (float)(n1 - (double)nx[u]);
+      nyl[u] = (float)(n2 - (double)ny[u]);
     }
 #pragma unroll
-    for (int c = 0; c < 2; ++c)
+    for (int c = 0; c < C; ++c)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[u][c][e] = 0.0;
   }
@@ -289,17 +298,17 @@ __global__ __launch_bounds__(kBlock) void k_multi_mm(const int4 *__restrict__ ta
         ty[u] = (float)((cy[u] - sy) + (double)pr[u].y);
       }
     }
-    mm_f4 y[kMmTiles][2];
+    mm_f4 y[kMmTiles][C];
 #pragma unroll
     for (int u = 0; u < kMmTiles; ++u)
 #pragma unroll
-      for (int a = 0; a < 2; ++a) y[u][a] = mm_f4{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int a = 0; a < C; ++a) y[u][a] = mm_f4{0.0f, 0.0f, 0.0f, 0.0f};
     for (int kb = 0; kb < n; kb += 4 * STEPS) {
-      mm_f4 z[kMmTiles][2];
+      mm_f4 z[kMmTiles][C];
 #pragma unroll
       for (int u = 0; u < kMmTiles; ++u)
 #pragma unroll
-        for (int a = 0; a < 2; ++a) z[u][a] = mm_f4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int a = 0; a < C; ++a) z[u][a] = mm_f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
       for (int w = 0; w < STEPS; ++w) {
         if (kb + 4 * w >= n) break;
@@ -324,20 +333,21 @@ __global__ __launch_bounds__(kBlock) void k_multi_mm(const int4 *__restrict__ ta
             z[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(xy, b[C - 1], z[u][0], 0, 0, 0);
             z[u][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(yy, b[C - 1], z[u][1], 0, 0, 0);
           } else {
-            z[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(dx * inv, b[0], z[u][0], 0, 0, 0);
-            z[u][1] = __builtin_amdgcn_mfma_f32_16x16x4f32(dy * inv, b[0], z[u][1], 0, 0, 0);
+            const float low = fmaf(dx, nxl[u], dy * nyl[u]);
+            const float a = fmaf(dx, nx[u], fmaf(dy, ny[u], low)) * inv;
+            z[u][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b[0], z[u][0], 0, 0, 0);
           }
         }
       }
 #pragma unroll
       for (int u = 0; u < kMmTiles; ++u)
 #pragma unroll
-        for (int a = 0; a < 2; ++a) y[u][a] += z[u][a];
+        for (int a = 0; a < C; ++a) y[u][a] += z[u][a];
     }
 #pragma unroll
     for (int u = 0; u < kMmTiles; ++u)
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int a = 0; a < C; ++a)
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[u][a][e] += (double)y[u][a][e];
     __syncthreads();  // the chunk is no longer read
@@ -354,12 +364,8 @@ __global__ __launch_bounds__(kBlock) void k_multi_mm(const int4 *__restrict__ ta
     for (int e = 0; e < 4; ++e) {
       const int i = first[u] + 4 * q + e;
       if (i >= b1) continue;
-      if constexpr (STK) {
-        o[2LL * i] = f * acc[u][0][e];
-        o[2LL * i + 1] = f * acc[u][1][e];
-      } else {
-        o[i] = f * (gload(d.nx, i) * acc[u][0][e] + gload(d.ny, i) * acc[u][1][e]);
-      }
+#pragma unroll
+      for (int a = 0; a < C; ++a) o[(long long)C * i + a] = f * acc[u][a][e];
     }
   }
 }
@@ -601,7 +607,8 @@ int build_plan(MultiPlan &P, const std::vector<MultiItem> &items, const std::vec
     if (!active[i] || m.fmm) continue;
     const long long len = g->M * (m.kind == 0 ? 1LL : 2LL);
     const bool large = m.kind == 1 && g->M >= kFarNodes;
-    const bool cores = !m.merged && m.nrhs >= (large ? kMmRhsLarge : kMmRhs);
+    const bool cores = !m.merged && m.nrhs >= (large ? kMmRhsLarge : kMmRhs[m.kind]) &&
+                       (m.kind == 1 || g->M >= (long long)kMmNodes * g->N);
     const bool far = !cores && large;
     d.mm = cores || far;
     if (far) {

@@ -18,7 +18,7 @@ pytestmark = [pytest.mark.gpu,
 def test_float32_sweeps_of_many_items(kind, items):
     rng = np.random.default_rng(kind)
     g = bie2d.Geometry.from_curves(wl.mixed_grid(rng, 3, np.full(3, 64)))
-    X = torch.as_tensor(rng.standard_normal((9, g.N * (3 if kind else 1))), device="cuda")
+    X = torch.as_tensor(rng.standard_normal((8 if kind else 25, g.N * (3 if kind else 1))), device="cuda")
     o = bie2d.default_opts(tol=1e-10, restart=30, precision=bie2d.BIE_MIXED)
     b = bie2d.Batch()
     ref = bie2d.bie_batch_solve(b, [(g, kind, X)], o)[0][0]

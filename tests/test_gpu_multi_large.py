@@ -19,11 +19,11 @@ pytestmark = [pytest.mark.gpu,
 def test_large_items(kind, bodies, nodes):
     rng = np.random.default_rng(bodies)
     g = bie2d.Geometry.from_curves(wl.mixed_grid(rng, bodies, np.full(bodies, nodes)))
-    X = torch.as_tensor(rng.standard_normal((17, bodies * (3 if kind else 1))), device="cuda")
+    X = torch.as_tensor(rng.standard_normal((25, bodies * (3 if kind else 1))), device="cuda")
     solve = bie2d.bie_mobility_solve if kind else bie2d.bie_elastance_solve
     ref = solve(g, X, bie2d.default_opts(tol=1e-11, restart=100))[0]
     b = bie2d.Batch()
-    for n in (1, 7, 8, 11, 12, 17):
+    for n in (1, 7, 8, 11, 12, 17, 24, 25):
         o = bie2d.default_opts(tol=1e-11, restart=100, precision=bie2d.BIE_MIXED)
         out = bie2d.bie_batch_solve(b, [(g, kind, X[:n].contiguous())], o)[0][0]
         assert float((out - ref[:n]).abs().max() / ref.abs().max()) < 1e-9, n
