@@ -30,3 +30,20 @@ def test_merged_fmm_requests_have_the_bits_of_lone_ones(kind, precision):
     for i, ((out, info), ref) in enumerate(zip(got, alone)):
         assert info["status"] == 0, info
         assert np.array_equal(out, ref), i
+
+
+def test_read_off_keeps_its_kinds_order():
+    """Elastance and mobility requests in flight on one geometry, whose expansion orders differ (both
+    from one target error): an elastance answer has the bits of the same request alone."""
+    rng = np.random.default_rng(5)
+    g = bie2d.Geometry.from_curves(wl.mixed_grid(rng, 12, np.full(12, 96)))
+    opts = bie2d.default_opts(method=bie2d.BIE_FMM, tol=1e-9, restart=8, fmm_eps=1e-7, fmm_leaf=32)
+    assert bie2d.bie_fmm_terms(opts, 0) != bie2d.bie_fmm_terms(opts, 1)
+    q, ft = rng.standard_normal((1, g.N)), rng.standard_normal((1, 3 * g.N))
+    srv = bie2d.Server(opts)
+    alone = srv.wait(srv.submit(g, 0, q), timeout=100)[0]
+    tickets = [srv.submit(g, kind, x) for kind, x in ((1, ft), (0, q), (1, 2 * ft), (0, q))]
+    got = [srv.wait(t, timeout=100) for t in tickets]
+    srv.close()
+    assert max(info["inflight"] for _, info in got) > 2
+    assert np.array_equal(got[1][0], alone) and np.array_equal(got[3][0], alone)
