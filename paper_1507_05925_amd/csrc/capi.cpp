@@ -303,7 +303,8 @@ static int geom_create(int nbodies, const int32_t *nodes_per_body, const double 
   // the caller's samples (device memory) are checked on the host before anything is built
   int warn = BIE_OK;
   std::string warn_msg;
-  double pair_scale = 1.0;
+  double diam_scale = 1.0;
+  int raise = 0;
   {
     hipStream_t s0 = as_stream(stream);
     std::vector<double> hc(6 * (size_t)M), hi(interior ? 2 * (size_t)nbodies : 0);
@@ -323,7 +324,16 @@ static int geom_create(int nbodies, const int32_t *nodes_per_body, const double 
     const auto x = std::minmax_element(hc.begin(), hc.begin() + M);
     const auto y = std::minmax_element(hc.begin() + M, hc.begin() + 2 * M);
     const double diag = std::hypot(*x.second - *x.first, *y.second - *y.first);
-    pair_scale = std::ldexp(1.0, -std::max(-1000, std::min(1000, std::ilogb(diag))));
+    diam_scale = std::ldexp(1.0, -std::max(-1000, std::min(1000, std::ilogb(diag))));
+    double finest = diag;  // about the smallest node spacing
+    for (long long b = 0, k = 0; b < nbodies; ++b) {
+      double slow = std::max(std::fabs(hc[2 * M + k]), std::fabs(hc[3 * M + k]));
+      for (const long long k1 = k + nodes_per_body[b]; k < k1; ++k)
+        slow = std::min(slow, std::max(std::fabs(hc[2 * M + k]), std::fabs(hc[3 * M + k])));
+      finest = std::min(finest, 6.28 / nodes_per_body[b] * slow);
+    }
+    if (finest * diam_scale < 0x1p-100)
+      raise = finest > 0.0 ? std::min(118, -100 - std::ilogb(finest * diam_scale)) : 118;
   }
   bie_geom *g = new (std::nothrow) bie_geom();
   if (!g) {
@@ -335,7 +345,9 @@ static int geom_create(int nbodies, const int32_t *nodes_per_body, const double 
   g->N = nbodies;
   g->M = (int)M;
   g->max_nodes = maxn;
-  g->pair_scale = pair_scale;
+  g->diam_scale = diam_scale;
+  g->pair_scale = std::ldexp(diam_scale, std::min(raise, 1023 - std::ilogb(diam_scale)));
+  g->pair_away = std::ldexp(16.0, raise);
   hipGetDevice(&g->device);
   g->h_body_ptr.resize(nbodies + 1);
   g->h_body_ptr[0] = 0;

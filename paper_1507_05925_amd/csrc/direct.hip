@@ -169,7 +169,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_pair_small(const int2 *__rest
       }
     }
   for (int base = 0; base < M; base += kSmallThreads) {
-    rec.store(src.scale, base + t < M, buf, kSmallThreads, t);
+    rec.store(src, base + t < M, buf, kSmallThreads, t);
     __syncthreads();
     rec.load(src, min(base + kSmallThreads + t, M - 1));
     const int nq = (min(M - base, kSmallThreads) + 3) >> 2;
@@ -229,7 +229,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_pair_small(const int2 *__rest
 }
 
 PairSources sources_of(const bie_geom *g, const double *mu, long long len) {
-  return PairSources{g->xy, g->nx, g->ny, g->w, mu, len, g->pair_scale};
+  return PairSources{g->xy, g->nx, g->ny, g->w, mu, len, g->pair_scale, g->pair_away};
 }
 
 // The traction kernels' constants, -1/(2 pi) and -1/pi.

@@ -318,7 +318,7 @@ void launch_sweep(bie_geom *g, int S, bool with_C, const double *mu, long long l
   const int tiles = (g->M + kSweepTile - 1) / kSweepTile, nmom = with_C ? g->N * R : 0;
   hipLaunchKernelGGL((k_dl_sweep<KIND, R>), dim3(nmom + tiles * S), dim3(kBlock), 0, st, g->M,
                      (g->M + S - 1) / S, tiles, nmom, moment_args(g, len, mu, mom),
-                     PairSources{g->xy, g->nx, g->ny, g->w, mu, len, g->pair_scale},
+                     PairSources{g->xy, g->nx, g->ny, g->w, mu, len, g->pair_scale, g->pair_away},
                      (KIND == kPairStkDl ? 1.0 : 0.5) / kPi, partial);
 }
 

@@ -674,7 +674,7 @@ __device__ inline V eval_value(const V *b, V w) {
 // coordinates are relative to the chunk's first target (one float64 difference, rounded once),
 // pair terms and the sums of eight sources are float32, and those are added into float64: the
 // float32 rounding of r stays at eps32 times the neighbourhood's size rather than the geometry's.
-// Lengths are scaled by the geometry's diameter (bie_geom::pair_scale). Sources that pad a staged
+// Lengths are scaled by the geometry's diameter (bie_geom::diam_scale). Sources that pad a staged
 // block have no strength and lie well outside the geometry.
 //
 // Measured beside the expansion chain, against records of 32 B (float32: 16 B), a masked
@@ -2181,16 +2181,16 @@ int fmm_far_field(bie_geom *g, int kind, int precision, int R, const double *mu,
       ProfScope pe(near32 ? BIE_K_FMM_NEAR_F32 : BIE_K_FMM_EVAL, plan.side,
                    (t.near_pairs - M) * R);
       if (kind == 0 && near32)
-        near_pass<float, false>(t, R, finish.merged, g->pair_scale,
+        near_pass<float, false>(t, R, finish.merged, g->diam_scale,
                                 reinterpret_cast<const float2 *>(wq), partial, plan.side);
       else if (near32)
-        near_pass<float, true>(t, R, finish.merged, g->pair_scale,
+        near_pass<float, true>(t, R, finish.merged, g->diam_scale,
                                reinterpret_cast<const double2 *>(wq), partial, plan.side);
       else if (kind == 0)
-        near_pass<double, false>(t, R, finish.merged, g->pair_scale,
+        near_pass<double, false>(t, R, finish.merged, g->diam_scale,
                                  reinterpret_cast<const double2 *>(wq), partial, plan.side);
       else
-        near_pass<double, true>(t, R, finish.merged, g->pair_scale,
+        near_pass<double, true>(t, R, finish.merged, g->diam_scale,
                                 reinterpret_cast<const double2 *>(wq), partial, plan.side);
       BIE_HIP_CHECK(hipGetLastError());
     }

@@ -180,9 +180,11 @@ struct bie_geom {
   double *dl_scale = nullptr;  // [1] length scale R of the completed double layers
   double2 *xy = nullptr;    // [M] float64 source coordinates
   float2 *xr = nullptr;     // [M] float32 coordinates relative to the body centroid
-  // power of two that brings the nodes' bounding-box diagonal into [1, 2): the pair sums work in
-  // scaled lengths, so that products of several squared distances stay in range
-  double pair_scale = 1.0;
+  // Powers of two. diam_scale brings the nodes' bounding-box diagonal into [1, 2). The float64 pair
+  // sums work in lengths scaled by pair_scale, so that products of four squared distances stay in
+  // range: the same, or more where node spacings would lie below 2^-100 of the diagonal (up to
+  // 2^118 more: spacings of 2^-218 of it, 2e-66). pair_away is 16 diagonals in those lengths.
+  double diam_scale = 1.0, pair_scale = 1.0, pair_away = 16.0;
   // targets of the one-launch direct apply (direct.hip): (body, first node) per tile; none for
   // geometries that take the split sweep
   int nsmall = 0;

@@ -32,7 +32,7 @@ struct ItemDesc {
   const int *body_ptr;
   const double *nx, *ny, *w, *kappa, *px, *py;
   const double2 *xy;
-  double scale;       // bie_geom::pair_scale
+  double scale, away;  // bie_geom::pair_scale, pair_away
   // float32 sweep (mm: the item has it): lists of 16-target tiles (body, first node) and of source
   // chunks (body, first node, nodes); Smm splits of cper chunks, and one more slot of partial sums
   // for the bodies' own blocks: group r0 at part + r0 (Smm + 1) len
@@ -138,7 +138,7 @@ __device__ __forceinline__ void sweep_task(const int4 &t, const ItemDesc &d, boo
                                            const double *__restrict__ mu,
                                            double *__restrict__ partial, double *buf) {
   const long long len = (long long)d.M * PairShape<KIND, R>::COMPS;
-  const PairSources src{d.xy, d.nx, d.ny, d.w, mu + d.io + t.y * len, len, d.scale};
+  const PairSources src{d.xy, d.nx, d.ny, d.w, mu + d.io + t.y * len, len, d.scale, d.away};
   const int sp = t.w & 0xfffff;
   int i1, k0, k1;
   long long at;
@@ -603,6 +603,7 @@ int build_plan(MultiPlan &P, const std::vector<MultiItem> &items, const std::vec
     d.px = g->px; d.py = g->py; d.xy = g->xy;
     d.xr = g->xr; d.xc = g->xc; d.yc = g->yc;
     d.scale = g->pair_scale;
+    d.away = g->pair_away;
     d.part = part;
     if (!active[i] || m.fmm) continue;
     const long long len = g->M * (m.kind == 0 ? 1LL : 2LL);

@@ -106,7 +106,7 @@ struct PairSources {
   const double *nx, *ny, *w;
   const double *mu;  // [R][len], node-major
   long long len;
-  double scale;
+  double scale, away;  // bie_geom::pair_scale, pair_away
 };
 
 // Source k as it lies in memory (kk: any source of the geometry where k is past the end), and its
@@ -131,10 +131,11 @@ struct PairRaw {
       for (int c = 0; c < S::COMPS; ++c)
         mu[r * S::COMPS + c] = gload(a.mu, (long long)r * a.len + (long long)S::COMPS * kk + c);
   }
-  __device__ __forceinline__ void store(double scale, bool valid, double *buf, int stride, int t) const {
-    const double away = valid ? 0.0 : 16.0;  // the geometry's scaled diameter lies in [1, 2)
-    buf[t] = fma(z.x, scale, away);
-    buf[stride + t] = fma(z.y, scale, away);
+  __device__ __forceinline__ void store(const PairSources &a, bool valid, double *buf, int stride,
+                                        int t) const {
+    const double away = valid ? 0.0 : a.away;
+    buf[t] = fma(z.x, a.scale, away);
+    buf[stride + t] = fma(z.y, a.scale, away);
     if (S::DL) {
       buf[2 * stride + t] = nx;
       buf[3 * stride + t] = ny;
@@ -187,7 +188,7 @@ __device__ __forceinline__ void pair_sweep_tile(int i0, int i1, int k0, int k1,
   const int t = threadIdx.x;
   rec.load(src, min(k0 + t, k1 - 1));
   for (int base = k0; base < k1; base += kStage) {
-    rec.store(src.scale, base + t < k1, buf, kStage, t);
+    rec.store(src, base + t < k1, buf, kStage, t);
     __syncthreads();
     rec.load(src, min(base + kStage + t, k1 - 1));  // the next block, during this block's pairs
     const int nq = (min(k1 - base, kStage) + 3) >> 2;  // quads (the last one padded)
