@@ -58,9 +58,12 @@ extern "C" {
 #define BIE_MIXED 1  /* float32 far field in the late GMRES steps (or the inner solves of a
                         refinement: mixed_strategy). Direct: float32 pair sums (body-relative
                         coordinates, float64 accumulation across source bodies), float64
-                        self-body blocks; small geometries (up to about 4,000 nodes) and the
-                        direct items of batches and the server stay in float64, which takes no
-                        longer there. FMM: float32 near field pair terms (float64
+                        self-body blocks; but float64 throughout, which takes no longer there,
+                        on geometries of up to about 4,000 nodes, and in batches and the server,
+                        where float32 is left to Stokes items of 12,288 nodes or more and,
+                        in batches, to Stokes items of 8 or more right-hand sides and Laplace items
+                        of 25 or more on bodies of 32 or more nodes on average. FMM: float32
+                        near field pair terms (target normals in float64 for Laplace; float64
                         accumulation), expansions of about half the order, float32 for Laplace
                         (multipoles, M2M, M2L, evaluation), float64 for Stokes. Both: float64
                         diagonal, completion, Arnoldi and true residuals (float64 operator). */

@@ -254,11 +254,11 @@ void small(bie_geom *g, const FinishArgs &a, long long len, hipStream_t st) {
 // Source splits of the sweep: workgroups all take about the same time and `resident` of them run
 // at once, so the count that fills whole rounds best is taken, the smallest within 3 % (more splits
 // cost more partial sums), with at least kBlock sources per split (64 up to 12 splits) and at
-// most four rounds: 25,600 nodes take 238 us per Laplace apply with 10 splits (2,000 workgroups
-// in two rounds of 1,024) and 246 with 11 (three rounds); 12,139 nodes 63 us with 21 and 68 with
-// 43. Below one round more splits shorten the sweep but lengthen the sum over them: the Stokes
-// double layer of three densities on 1,000 nodes takes 23 us with 3 splits and 14 with 7, on
-// 2,560 nodes 19 us with 10 and 22 with 20.
+// most four rounds: a Laplace apply on 25,600 nodes takes 240 us with 10 splits (2,000 workgroups in
+// two rounds of 1,024) and 244 with 11 (three rounds); on 12,139 nodes (61 bodies) 63 us with 21, 69
+// with 11 and 67 with 43. Below one round more splits shorten the sweep but lengthen the sum over
+// them: a Stokes double layer of three densities on 1,000 nodes takes 18 us with 3 splits and 15
+// with 7, on 2,560 nodes 16 us with 10 and 19 with 43.
 int pair_splits(int M, int V) {
   const int tiles = (M + kSweepTile - 1) / kSweepTile, resident = 256 * sweep_occupancy(V);
   const int most = std::max({1, M / kBlock, std::min(12, M / 64)});

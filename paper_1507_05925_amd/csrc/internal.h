@@ -413,8 +413,8 @@ struct MultiItem {
 };
 struct MultiPlan;
 // item_f32 (nullptr: every item uses precision): per item, 1 = BIE_MIXED, 0 = BIE_FP64, at most
-// kMaxPrecGroups items. Direct items of few right-hand sides are float64 either way, unless they are
-// Stokes items of many nodes.
+// kMaxPrecGroups items. Which direct items have a float32 sweep: see multi.hip; the others are float64
+// either way.
 int multi_apply(MultiPlan *&plan, const std::vector<MultiItem> &items,
                 const std::vector<char> &active, int precision, const double *in, double *out,
                 hipStream_t s, const std::vector<char> *item_f32 = nullptr);

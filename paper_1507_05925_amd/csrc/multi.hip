@@ -4,16 +4,19 @@
 // changes:
 //   sweep task  = (item, first rhs of a group of R, tile of kSweepTile targets, source split)
 //   finish task = (item, body, rhs, group)
-// The sweep is the single-geometry float64 sweep (pairs.h) over all pairs. With BIE_MIXED, items of a
-// batch with kMmRhs or more right-hand sides take their pairs of different bodies in float32 on the
-// matrix cores instead (k_multi_mm: 16 right-hand sides at a time) and the bodies' own blocks in
-// float64; fewer right-hand sides stay in float64, where float32 takes no less time per pair. (The
-// server's items always do: how many right-hand sides its items have depends on the other requests in
-// flight, and a request's arithmetic must not.) Float64 right-hand sides go in groups of up to eight (Laplace) or
-// four (Stokes); splits and summation order depend on the geometry alone, and every group size
-// forms a column's sums in the same order, so a system's result depends neither on the rest of the
-// batch nor on the other right-hand sides of its item. Items above the FMM threshold are applied
-// by the single-geometry path.
+// The sweep is the single-geometry float64 sweep (pairs.h) over all pairs. With BIE_MIXED some items
+// take their pairs of different bodies in float32 instead, and the bodies' own blocks in float64:
+// items of a batch with many right-hand sides on the matrix cores (k_multi_mm, 16 right-hand sides at
+// a time, from kMmRhs on), and large Stokes items otherwise on the vector units (k_multi_far,
+// kFarNodes). The rest stay in float64, where float32 takes no less time. Merged items (the server's:
+// how many right-hand sides they have depends on the other requests in flight) never choose by that
+// number. Float64 right-hand sides go in groups of up to eight (Laplace) or four (Stokes). Splits and
+// summation order of the float64 sweep and of k_multi_far depend on the geometry alone, and every group
+// size forms a column's sums in the same order: a system's applies depend neither on the rest of the
+// batch nor, in float64 and in merged items, on the other right-hand sides of its item. (With
+// BIE_MIXED the number of those chooses an unmerged item's sweep; and the single-geometry kernels that
+// form an item's right-hand side and read its answer off round by that number.) Items above the
+// FMM threshold are applied by the single-geometry path.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -63,8 +66,8 @@ constexpr int kMmTile = 16 * kMmTiles * 4;         // targets per workgroup, at 
 // Stokes items of at least kFarNodes nodes take the float32 vector sweep instead of the float64 one
 // where they do not take the matrix cores', whatever their right-hand sides (merged items may not
 // choose by their number). Served mobility requests, 1 / 4 / 15 at a time, float64 against float32:
-// 8,672 nodes 2.9 / 6.5 / 16.0 ms against 3.3 / 7.2 / 13.0; 12,352 nodes 5.1 / 11.0 / 30.5 against
-// 4.8 / 10.2 / 20.8; 29,568 nodes 21.0 / 47.5 / 155 against 14.4 / 32.1 / 94.2.
+// 9,536 nodes 3.1 / 6.4 / 16.1 ms against 3.5 / 7.0 / 13.6; 12,896 nodes 4.1 / 9.0 / 25.9 against
+// 4.8 / 9.7 / 21.1; 30,688 nodes 17.5 / 41.9 / 137 against 14.0 / 30.8 / 90.7.
 constexpr int kFarNodes = 12288;
 constexpr int kFarGroup = 4;
 // They take the matrix cores' sweep from kMmRhsLarge right-hand sides on (8 / 10 / 12 / 16 on 19,872

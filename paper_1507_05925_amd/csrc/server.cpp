@@ -80,7 +80,9 @@ bool uses_fmm(const bie_opts &o, const bie_geom *g) {
 
 // Device bytes of one request's solver state: its buffers (incident density, rhs, iterate,
 // result), its share of the flat vectors (F, X, R, D), of the Krylov basis (restart + 1
-// vectors) and of the apply workspace (float64 and float32 strengths).
+// vectors), and 12 bytes per unknown for the apply. (The batched apply's own workspace, partial
+// sums shared by the requests in flight and kept between cycles, is not charged: up to 11 doubles per
+// unknown, for Stokes items of 12,288 nodes and more up to 65 and their float32 strengths.)
 long long footprint(const bie_server_config &c, bie_geom *g, int kind, int nrhs) {
   const long long n = kind == 0 ? g->M : 2LL * g->M;
   const int width = kind == 0 ? g->N : 3 * g->N;
