@@ -654,7 +654,7 @@ int apply_operator(bie_geom *g, int kind, int precision, int method, int with_L,
     return BIE_EINVAL;
   }
   BIE_TRY(g->ws_apply.reserve(std::max(apply_workspace_bytes(g, kind, method, nrhs),
-                                       direct_workspace_bytes(g, kind))));
+                                       method == BIE_FMM ? 0 : direct_workspace_bytes(g, kind))));
   return apply_operator_ws(g, kind, precision, method, with_L, alpha, nrhs, mu, out,
                            g->ws_apply.ptr, g->ws_apply.bytes, st, merged);
 }
