@@ -254,17 +254,24 @@ void small(bie_geom *g, const FinishArgs &a, long long len, hipStream_t st) {
 // Source splits of the sweep: workgroups all take about the same time and `resident` of them run
 // at once, so the count that fills whole rounds best is taken, the smallest within 3 % (more splits
 // cost more partial sums), with at least kBlock sources per split (64 up to 12 splits) and at
-// most four rounds: a Laplace apply on 25,600 nodes takes 240 us with 10 splits (2,000 workgroups in
+// most four rounds on small geometries: a Laplace apply on 25,600 nodes takes 240 us with 10 splits (2,000 workgroups in
 // two rounds of 1,024) and 244 with 11 (three rounds); on 12,139 nodes (61 bodies) 63 us with 21, 69
 // with 11 and 67 with 43. Below one round more splits shorten the sweep but lengthen the sum over
 // them: a Stokes double layer of three densities on 1,000 nodes takes 18 us with 3 splits and 15
 // with 7, on 2,560 nodes 16 us with 10 and 19 with 43.
+// On large ones four rounds leave the last one up to a quarter empty, and the sums over more splits
+// are small beside the sweep. With more than two values per node (Stokes of two columns and up): from
+// 28,672 nodes up to 12 rounds, Stokes of four columns on 100,096 nodes 11.2 ms with 5 splits and 14.5
+// without, on 60,000 3.83 with 12 and 4.32 without. With one or two: from 49,152 nodes up to 8 rounds, one
+// Laplace column on 60,000 nodes 1.29 ms against 1.43 within four; below that they gain nothing (45,056
+// nodes 0.77 ms with 14 splits, 0.73 with 8).
 int pair_splits(int M, int V) {
   const int tiles = (M + kSweepTile - 1) / kSweepTile, resident = 256 * sweep_occupancy(V);
   const int most = std::max({1, M / kBlock, std::min(12, M / 64)});
+  const int rounds_most = M < (V > 2 ? 28672 : 49152) ? 4 : V > 2 ? 12 : 8;
   int best = 1;
   double fill = 0.0;
-  for (int S = 1; S <= most && S * tiles <= std::max(4 * resident, tiles); ++S) {
+  for (int S = 1; S <= most && S * tiles <= std::max(rounds_most * resident, tiles); ++S) {
     const int W = S * tiles, rounds = (W + resident - 1) / resident;
     const double f = (double)W / ((double)rounds * resident);
     if (f > fill + 0.03) {

@@ -631,8 +631,8 @@ size_t apply_workspace_bytes(const bie_geom *g, int kind, int method, int nrhs) 
 }
 
 // Bytes of the float64 direct sweep's partial sums, over the right-hand side counts a call may
-// use. Where the sources are split, splits x target tiles stay within four rounds of resident
-// workgroups (a few tens of MiB at most); else one partial per target.
+// use. Where the sources are split, splits x target tiles stay within 12 rounds of resident
+// workgroups (48 MiB at most); else one partial per target.
 static size_t direct_workspace_bytes(const bie_geom *g, int kind) {
   if (g->nsmall > 0) return 0;
   const size_t len = (size_t)g->M * (kind == 0 ? 1 : 2);
